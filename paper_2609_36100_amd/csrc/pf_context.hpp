@@ -171,11 +171,25 @@ inline bool fe_needed(const ArkTable& t, int i) {
     if (t.AE[k][i] != 0.0) return true;
   return false;
 }
-inline bool fi_needed(const ArkTable& t, int i) {
-  if (t.bI[i] != 0.0 || (t.has_emb && t.bI[i] - t.bt[i] != 0.0)) return true;
-  for (int k = i + 1; k < t.s; ++k)
-    if (t.AI[k][i] != 0.0) return true;
-  return false;
+
+// The coefficients of a step of size dt, as the kernels take them.
+inline void fill_tab(const ArkTable& t, double dt, ArkTab& k) {
+  std::memset(&k, 0, sizeof(k));
+  int l = t.s - 1;  // the last explicit derivative
+  while (l > 0 && !fe_needed(t, l)) --l;
+  for (int i = 0; i < t.s; ++i) {
+    for (int j = 0; j < i; ++j) {
+      k.cE[i][j] = dt * t.AE[i][j];
+      k.cI[i][j] = dt * t.AI[i][j];
+    }
+    k.ub[i] = t.bI[i];
+    if (t.has_emb) k.eb[i] = t.bI[i] - t.bt[i];
+  }
+  k.gdt = dt * t.AI[t.s - 1][t.s - 1];
+  k.dt = dt;
+  k.bl = dt * t.bE[l];
+  if (t.has_emb) k.dl = dt * (t.bE[l] - t.bt[l]);
+  k.want_err = t.has_emb;
 }
 
 // ---- context -----------------------------------------------------------------
@@ -188,11 +202,8 @@ struct pf_ctx {
   pf::Geo g;
   pf::ModelK mk;
   pf::ArkTable tab;
-  bool fe_need[6], fi_need[6];
-  bool fi0_derived = false;  // F^I_1 = L y recomputed, never stored (explicit first stage)
-  // the last stage forms the update and error sums (U into the last stage's
-  // F^I buffer, E into the unused F^I_1 buffer); the update reads y, U, E, F^E_s
-  bool fold_last = false;
+  pf::ArkTab at;
+  bool fe_need[6];
   int mixed = 0;
   bool norm_real = false;  // WRMS of the error in real space (norm_space = 1)
   bool inhom = false;      // Reuss-averaged stiffness, Hu-Chen iteration (elastic_inhom = 1)
@@ -206,7 +217,7 @@ struct pf_ctx {
   pf::cx<double>* y = nullptr;
   pf::cx<double>* ynew = nullptr;
   pf::cx<double>* ycopy = nullptr;  // norm_space = 1: the previous state, transformed back
-  pf::cx<double>* FI[6] = {nullptr};
+  pf::cx<double>* err = nullptr;    // norm_space = 1: the step's error estimate
   void* FE[6] = {nullptr};  // cx<double> (FP64) or cx<float> (mixed)
   void* scratch = nullptr;  // T1 (4 fields) | T3 (3 fields) of the FFT precision
   size_t scratch_bytes = 0;

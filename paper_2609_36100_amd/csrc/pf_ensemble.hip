@@ -50,7 +50,6 @@ struct EMemb {
   Geo g;
   ModelK mk;
   cx<double>* ybuf[2];
-  cx<double>* FI[6];
   cx<TE>* FE[6];
   cx<T>* T1;
   cx<T>* T3;
@@ -70,22 +69,10 @@ struct EState {
   int prevrej;  // the last attempt was rejected (caps the next proposal's growth)
 };
 
-struct StageCoef {
-  double aE[6], aI[6], aii;
-  int fi_out, fe_need;
-  int fi0_from_y;  // F^I_1 = L(k) y formed in place (explicit first stage)
-  // last stage: update / error sums into FI[stage] (U) and FI[0] (E), with
-  // weights b and b - b~ (times each member's dt), as in the single grid
-  int fold;
-  double ub[6], eb[6], ubs, ebs;
-};
-
-struct FinCoef {
-  double bE[6], bI[6], dE[6], dI[6];
-  int s, want_err;
-  int fi0_from_y;  // as in StageCoef
-  int fold;        // y_new = U + ..., error = E + ... (U in FI[s-1], E in FI[0])
-};
+// A member's coefficients (its own dt), read through the scalar cache: uniform
+// operands that no kernel of a pass writes.
+typedef const __attribute__((address_space(4))) ArkTab* TabK;
+__device__ inline TabK member_tab(const ArkTab* tabs, int m) { return (TabK)(uintptr_t)(tabs + m); }
 
 // kernel kinds with their own work list and work-group size
 enum EKind { EK_STAGE = 0, EK_YFFT4, EK_YFFT3, EK_THETA, EK_ELASTIC, EK_DRIVE, EK_FWD_AC, EK_COUNT };
@@ -135,44 +122,39 @@ __device__ inline int find_member(const int* start, int M, int b) {
 }
 
 // ---- batched kernels -------------------------------------------------------
+// The member's arrays for one attempted step (its current and spare state).
+template <typename T, typename TE>
+__device__ inline StepArgs<TE> member_step(const EMemb<T, TE>& e, const EState& x) {
+  StepArgs<TE> sa;
+  sa.y = e.ybuf[x.cur];
+#pragma unroll
+  for (int j = 0; j < 6; ++j) sa.FE[j] = e.FE[j];
+  sa.FI_out = nullptr;
+  sa.FEc_out = nullptr;
+  sa.ynew = e.ybuf[1 - x.cur];
+  sa.err_out = nullptr;
+  sa.rtol = x.rtol;
+  sa.atol = x.atol;
+  sa.sc = 1.0 / sqrt((double)e.g.nx * e.g.ny * e.g.nz);
+  return sa;
+}
+
 template <typename T, typename TE, int EB, int NP>
 __global__ void __launch_bounds__(EB) kb_stage(const EMemb<T, TE>* mem, const EState* st, const int* start, int M,
-                                               StageCoef sc) {
+                                               const ArkTab* tabs) {
   __shared__ cx<T> lds[ens_lds(EB)];
   const int m = find_member(start, M, blockIdx.x);
   if (st[m].done) return;
   const EMemb<T, TE>& e = mem[m];
-  const int tile = blockIdx.x - start[m];
-  const double dt = st[m].dt;
-  StageArgs<TE> sa;
-  sa.y = e.ybuf[st[m].cur];
-#pragma unroll
-  for (int j = 0; j < 6; ++j) {
-    sa.FE[j] = j < NP ? e.FE[j] : nullptr;
-    sa.FI[j] = j < NP ? e.FI[j] : nullptr;
-    sa.cE[j] = j < NP ? dt * sc.aE[j] : 0.0;
-    sa.cI[j] = j < NP ? dt * sc.aI[j] : 0.0;
-  }
-  sa.nprev = NP;
-  sa.gdt = dt * sc.aii;
-  sa.FI_out = sc.fi_out ? e.FI[NP] : nullptr;
-  sa.fi0_from_y = sc.fi0_from_y;
-  sa.U_out = sc.fold ? e.FI[NP] : nullptr;
-  sa.E_out = sc.fold ? e.FI[0] : nullptr;
-#pragma unroll
-  for (int j = 0; j < 6; ++j) {
-    sa.ub[j] = sc.ub[j];
-    sa.eb[j] = sc.eb[j];
-  }
-  sa.ubs = sc.ubs;
-  sa.ebs = sc.ebs;
-  sa.fdt = dt;
-  sa.FEc_out = e.mk.fEa != 0.0 ? e.FE[NP] : nullptr;
+  const int item = blockIdx.x - start[m];
+  StepArgs<TE> sa = member_step(e, st[m]);
+  const TabK tb = member_tab(tabs, m);
+  if (e.mk.fEa != 0.0) sa.FEc_out = e.FE[NP];
   switch (e.g.nz) {
-#define PF_C(N)                                                                                       \
-  case N:                                                                                             \
-    body_stage_invz<T, TE, N, ens_tx(EB, N, 8), 8, NP, true>(sa, e.g, e.mk, e.twN, e.T1, tile,        \
-                                                              threadIdx.x, lds);                      \
+#define PF_C(N)                                                                                              \
+  case N:                                                                                                    \
+    body_stage<T, TE, N, ens_tx(EB, N, 8), 8, NP, true>(sa, tb, e.g, e.mk, e.T3, e.twN, e.T1, item,            \
+                                                        threadIdx.x, lds);                                  \
     break;
     PF_ENS_SIZES(PF_C)
 #undef PF_C
@@ -272,63 +254,27 @@ __global__ void __launch_bounds__(EB) kb_fwd_ac(const EMemb<T, TE>* mem, const E
   }
 }
 
-// update + embedded error + WRMS partial sums; fixed work-group count per member
-template <typename T, typename TE>
-__global__ void __launch_bounds__(256) kb_finalize(const EMemb<T, TE>* mem, const EState* st, const int* start,
-                                                   int M, FinCoef fc, double* partial) {
+// Update + embedded error + WRMS partial sums, one pair per work-group.
+template <typename T, typename TE, int EB, int S>
+__global__ void __launch_bounds__(EB) kb_final(const EMemb<T, TE>* mem, const EState* st, const int* start, int M,
+                                               const ArkTab* tabs, double* partial) {
+  __shared__ cx<T> lds[ens_lds(EB)];
   __shared__ double sh[16];
   const int m = find_member(start, M, blockIdx.x);
   if (st[m].done) return;  // uniform per block: the partials of done members are never read
   const EMemb<T, TE>& e = mem[m];
-  const Geo& g = e.g;
-  const double dt = st[m].dt;
-  const cx<double>* y = e.ybuf[st[m].cur];
-  cx<double>* ynew = e.ybuf[1 - st[m].cur];
-  const double rtol = st[m].rtol, atol = st[m].atol;
-  const double sc = 1.0 / sqrt((double)g.nx * g.ny * g.nz);
-  const long long nrow = (long long)g.nz * g.ny;
-  const long long total = 4 * nrow * g.nxh;
-  const int nb = start[m + 1] - start[m];
-  const int lb = blockIdx.x - start[m];
+  const int item = blockIdx.x - start[m];
+  const StepArgs<TE> sa = member_step(e, st[m]);
+  const TabK tb = member_tab(tabs, m);
   double acc = 0.0, bad = 0.0;
-  for (long long i = lb * 256LL + threadIdx.x; i < total; i += 256LL * nb) {
-    const int x = (int)(i % g.nxh);
-    const long long fr = i / g.nxh;  // f * nrow + row
-    const long long idx = fr * g.P + x;
-    const cx<double> y0 = y[idx];
-    // all the stage loads of one element are issued before any is used
-    cx<double> fi[6], fe[6];
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-      const bool hasI = j < fc.s && (fc.bI[j] != 0.0 || (fc.want_err && fc.dI[j] != 0.0));
-      const bool hasE = j < fc.s && (fc.bE[j] != 0.0 || (fc.want_err && fc.dE[j] != 0.0));
-      fi[j] = (hasI && !(j == 0 && fc.fi0_from_y)) ? e.FI[j][idx] : mk(0.0, 0.0);
-      fe[j] = hasE ? to_d(e.FE[j][idx]) : mk(0.0, 0.0);
-    }
-    if (fc.fi0_from_y) {
-      const int f = (int)(fr / nrow);
-      const int row = (int)(fr % nrow);
-      const int yy = row % g.ny, z = row / g.ny;
-      const double kx = x * g.kfx, ky = mode_of(yy, g.ny) * g.kfy, kz = mode_of(z, g.nz) * g.kfz;
-      const double k2 = kx * kx + ky * ky + kz * kz;
-      fi[0] = lsym(e.mk, f, k2) * y0;
-    }
-    cx<double> inc = mk(0.0, 0.0), err = fc.fold ? e.FI[0][idx] : mk(0.0, 0.0);
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-      if (j >= fc.s) break;
-      inc = inc + ((dt * fc.bI[j]) * fi[j] + (dt * fc.bE[j]) * fe[j]);
-      err = err + ((dt * fc.dI[j]) * fi[j] + (dt * fc.dE[j]) * fe[j]);
-    }
-    const cx<double> yn = (fc.fold ? e.FI[fc.s - 1][idx] : y0) + inc;
-    ynew[idx] = yn;
-    if (!isfinite(yn.re) || !isfinite(yn.im)) bad += 1.0;
-    if (fc.want_err) {
-      const double mult = (x == 0 || 2 * x == g.nx) ? 1.0 : 2.0;
-      const double ay = sqrt(y0.re * y0.re + y0.im * y0.im) * sc;
-      const double wgt = 1.0 / (rtol * ay + atol);
-      acc += mult * (err.re * err.re + err.im * err.im) * sc * sc * wgt * wgt;
-    }
+  switch (e.g.nz) {
+#define PF_C(N)                                                                                               \
+  case N:                                                                                                     \
+    body_final<T, TE, N, ens_tx(EB, N, 8), 8, S, true>(sa, tb, e.g, e.mk, e.T3, e.twN, item, threadIdx.x, lds, \
+                                                       acc, bad);                                            \
+    break;
+    PF_ENS_SIZES(PF_C)
+#undef PF_C
   }
   const double s0 = block_sum(acc, sh);
   const double s1 = block_sum(bad, sh);
@@ -345,24 +291,10 @@ __device__ inline double ctrl_factor(double dt, double err, int q, bool after_re
   return dt * fac;
 }
 
-// One work-group per member: sum its partials in a fixed order, then the
-// accept / reject decision and the next step size (thread 0).
-template <typename T, typename TE>
-__global__ void __launch_bounds__(256) kb_control(const EMemb<T, TE>* mem, EState* st, const int* fstart,
-                                                  const double* partial, int q, int has_emb, int nrhs) {
-  __shared__ double sh[16];
-  const int m = blockIdx.x;
-  if (st[m].done) return;
-  double a = 0.0, b = 0.0;
-  for (int i = fstart[m] + threadIdx.x; i < fstart[m + 1]; i += blockDim.x) {
-    a += partial[2 * i];
-    b += partial[2 * i + 1];
-  }
-  a = block_sum(a, sh);
-  b = block_sum(b, sh);
-  if (threadIdx.x != 0) return;
-  EState s = st[m];
-  const Geo& g = mem[m].g;
+// Accept / reject decision and next step size of a member from its summed
+// error terms a and non-finite count b; returns the next attempt's dt.
+__device__ inline double control_member(const Geo& g, EState& st, double a, double b, int q, int has_emb, int nrhs) {
+  EState s = st;
   const double n3 = (double)g.nx * g.ny * g.nz;
   double err = has_emb ? sqrt(a / (4.0 * n3)) : 0.0;
   const bool finite = b == 0.0 && isfinite(err);
@@ -401,7 +333,42 @@ __global__ void __launch_bounds__(256) kb_control(const EMemb<T, TE>* mem, EStat
   // t_final; the proposal itself is kept for a later advance
   s.dt_next = nxt;
   s.dt = fmin(fmin(nxt, s.dt_max), s.tf - s.t);
-  st[m] = s;
+  st = s;
+  return s.dt;
+}
+
+// One work-group per member: sum its partials in a fixed order, then the
+// accept / reject decision and the next step size (thread 0).
+template <typename T, typename TE>
+__global__ void __launch_bounds__(256) kb_control(const EMemb<T, TE>* mem, EState* st, const int* fstart,
+                                                  const double* partial, int q, int has_emb, int nrhs,
+                                                  ArkTab unit, ArkTab* tabs) {
+  __shared__ double sh[16];
+  __shared__ double next_dt;
+  const int m = blockIdx.x;
+  if (st[m].done) return;
+  double a = 0.0, b = 0.0;
+  for (int i = fstart[m] + threadIdx.x; i < fstart[m + 1]; i += blockDim.x) {
+    a += partial[2 * i];
+    b += partial[2 * i + 1];
+  }
+  a = block_sum(a, sh);
+  b = block_sum(b, sh);
+  if (threadIdx.x == 0) next_dt = control_member(mem[m].g, st[m], a, b, q, has_emb, nrhs);
+  __syncthreads();
+  // the member's coefficients for its next attempt
+  const double dt = next_dt;
+  ArkTab& tb = tabs[m];
+  if (threadIdx.x < 36) {
+    const int k = threadIdx.x / 6, j = threadIdx.x % 6;
+    tb.cE[k][j] = dt * unit.cE[k][j];
+    tb.cI[k][j] = dt * unit.cI[k][j];
+  } else if (threadIdx.x == 36) {
+    tb.gdt = dt * unit.gdt;
+    tb.dt = dt;
+    tb.bl = dt * unit.bl;
+    tb.dl = dt * unit.dl;
+  }
 }
 
 }  // namespace pf
@@ -421,15 +388,13 @@ struct pf_ens {
   EState* st_host = nullptr;  // pinned
   int* start[EK_COUNT][2] = {{nullptr}};
   int ntiles[EK_COUNT][2] = {{0}};
-  int* fin_start = nullptr;
-  int nfin = 0;
   double* partial = nullptr;
   int var[EK_COUNT] = {1, 1, 1, 1, 1, 1, 1};
   double tune_ms[EK_COUNT][2] = {{0}};
   ArkTable tab;
-  bool fe_need[6], fi_need[6];
-  bool fi0_derived = false;  // explicit first stage: F^I_1 = L y, never stored
-  bool fold_last = false;    // last stage forms the update and error sums
+  ArkTab unit;                 // coefficients for dt = 1
+  ArkTab* tab_dev = nullptr;   // each member's, for its next attempt
+  ArkTab* tab_host = nullptr;  // pinned
   hipGraphExec_t exec = nullptr;
   hipGraph_t graph = nullptr;
   std::map<int, std::pair<cx<double>*, cx<double>*>> tw64;  // N -> (w_N, w_{N/2})
@@ -468,6 +433,7 @@ static int row_tiles(int n) {
 template <int EB>
 static int kind_tiles(int kind, int n) {
   switch (kind) {
+    case EK_STAGE: return 4 * col_tiles<EB>(n, 8);  // one field per work-group (also the update's)
     case EK_ELASTIC: return col_tiles<EB>(n, 4);
     case EK_THETA:
     case EK_DRIVE: return row_tiles<EB>(n);
@@ -486,17 +452,8 @@ static pf_status build_lists(pf_ens* E) {
       PF_HIP(hipMemcpy(E->start[k][v], st.data(), sizeof(int) * (E->M + 1), hipMemcpyHostToDevice));
       E->ntiles[k][v] = st[E->M];
     }
-  std::vector<int> fs(E->M + 1, 0);
-  for (int m = 0; m < E->M; ++m) {
-    const long long n = E->prm[m].nz;
-    const long long total = 4 * n * n * (n / 2 + 1);
-    fs[m + 1] = fs[m] + (int)std::min<long long>(1024, (total + 2047) / 2048);
-  }
-  E->nfin = fs[E->M];
-  pf_status s = ens_alloc(E, (void**)&E->fin_start, sizeof(int) * (E->M + 1));
-  if (s != PF_OK) return s;
-  PF_HIP(hipMemcpy(E->fin_start, fs.data(), sizeof(int) * (E->M + 1), hipMemcpyHostToDevice));
-  return ens_alloc(E, (void**)&E->partial, sizeof(double) * 2 * E->nfin);
+  return ens_alloc(E, (void**)&E->partial,
+                   sizeof(double) * 2 * std::max(E->ntiles[EK_STAGE][0], E->ntiles[EK_STAGE][1]));
 }
 
 template <typename T, typename TE>
@@ -509,37 +466,24 @@ static void launch_kind(pf_ens* E, int kind, int stage) {
   auto go = [&](auto EBC) {
     constexpr int EB = decltype(EBC)::value;
     switch (kind) {
-      case EK_STAGE: {
-        StageCoef sc;
-        std::memset(&sc, 0, sizeof(sc));
-        for (int j = 0; j < 6; ++j) {
-          sc.aE[j] = (j < stage && E->fe_need[j]) ? E->tab.AE[stage][j] : 0.0;
-          sc.aI[j] = (j < stage && E->fi_need[j]) ? E->tab.AI[stage][j] : 0.0;
-        }
-        sc.aii = E->tab.AI[stage][stage];
-        sc.fi0_from_y = E->fi0_derived ? 1 : 0;
-        sc.fi_out = (E->fi_need[stage] && !(stage == 0 && E->fi0_derived)) ? 1 : 0;
-        if (E->fold_last && stage == E->tab.s - 1) {
-          const ArkTable& tb = E->tab;
-          sc.fold = 1;
-          sc.fi_out = 0;
-          for (int j = 0; j < stage; ++j) {  // b^E = b^I here (fold_last)
-            sc.ub[j] = tb.bI[j];
-            sc.eb[j] = tb.bI[j] - tb.bt[j];
+      case EK_STAGE:
+        if (stage == E->tab.s) {  // the step's update; embedded pairs only
+          switch (E->tab.s) {
+            case 3: kb_final<T, TE, EB, 3><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, E->tab_dev, E->partial); break;
+            case 4: kb_final<T, TE, EB, 4><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, E->tab_dev, E->partial); break;
+            default: kb_final<T, TE, EB, 6><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, E->tab_dev, E->partial); break;
           }
-          sc.ubs = tb.bI[stage];
-          sc.ebs = tb.bI[stage] - tb.bt[stage];
+          break;
         }
         switch (stage) {
-          case 0: kb_stage<T, TE, EB, 0><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, sc); break;
-          case 1: kb_stage<T, TE, EB, 1><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, sc); break;
-          case 2: kb_stage<T, TE, EB, 2><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, sc); break;
-          case 3: kb_stage<T, TE, EB, 3><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, sc); break;
-          case 4: kb_stage<T, TE, EB, 4><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, sc); break;
-          default: kb_stage<T, TE, EB, 5><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, sc); break;
+          case 0: kb_stage<T, TE, EB, 0><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, E->tab_dev); break;
+          case 1: kb_stage<T, TE, EB, 1><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, E->tab_dev); break;
+          case 2: kb_stage<T, TE, EB, 2><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, E->tab_dev); break;
+          case 3: kb_stage<T, TE, EB, 3><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, E->tab_dev); break;
+          case 4: kb_stage<T, TE, EB, 4><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, E->tab_dev); break;
+          default: kb_stage<T, TE, EB, 5><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, E->tab_dev); break;
         }
         break;
-      }
       case EK_YFFT4:
         if (stage < 0)
           kb_ypass<T, TE, EB, -1, 4><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M);
@@ -564,15 +508,12 @@ static void launch_kind(pf_ens* E, int kind, int stage) {
     go(std::integral_constant<int, 128>{});
 }
 
-// One attempted step of every active member: 6 x 9 pass launches, finalize, control.
+// One attempted step of every active member: 6 x 8 pass launches (mixed: 9), update, control.
 template <typename T, typename TE>
 static void enqueue_step(pf_ens* E) {
   const ArkTable& tb = E->tab;
-  int nrhs = 0;
   for (int i = 0; i < tb.s; ++i) {
     launch_kind<T, TE>(E, EK_STAGE, i);
-    if (!E->fe_need[i]) continue;
-    ++nrhs;
     launch_kind<T, TE>(E, EK_YFFT4, +1);  // inverse y of the state
     launch_kind<T, TE>(E, EK_THETA, i);
     launch_kind<T, TE>(E, EK_YFFT3, -1);  // forward y of theta
@@ -580,31 +521,20 @@ static void enqueue_step(pf_ens* E) {
     launch_kind<T, TE>(E, EK_YFFT3, +1);  // inverse y of the elastic potentials
     launch_kind<T, TE>(E, EK_DRIVE, i);
     launch_kind<T, TE>(E, EK_YFFT3, -1);  // forward y of the driving force
-    launch_kind<T, TE>(E, EK_FWD_AC, i);
+    if (!fresh_fe<T>) launch_kind<T, TE>(E, EK_FWD_AC, i);
   }
-  FinCoef fc;
-  std::memset(&fc, 0, sizeof(fc));
-  for (int j = 0; j < tb.s; ++j) {
-    fc.bE[j] = E->fe_need[j] ? tb.bE[j] : 0.0;
-    fc.bI[j] = E->fi_need[j] ? tb.bI[j] : 0.0;
-    fc.dE[j] = (tb.has_emb && E->fe_need[j]) ? tb.bE[j] - tb.bt[j] : 0.0;
-    fc.dI[j] = (tb.has_emb && E->fi_need[j]) ? tb.bI[j] - tb.bt[j] : 0.0;
-  }
-  fc.s = tb.s;
-  fc.want_err = tb.has_emb;
-  fc.fi0_from_y = E->fi0_derived ? 1 : 0;
-  if (E->fold_last) {
-    const int l = tb.s - 1;
-    for (int j = 0; j < tb.s; ++j) fc.bE[j] = fc.bI[j] = fc.dE[j] = fc.dI[j] = 0.0;
-    fc.bE[l] = tb.bE[l];
-    fc.dE[l] = tb.bE[l] - tb.bt[l];
-    fc.fi0_from_y = 0;
-    fc.fold = 1;
-  }
+  launch_kind<T, TE>(E, EK_STAGE, tb.s);
   const EMemb<T, TE>* mem = (const EMemb<T, TE>*)E->mem_dev;
-  kb_finalize<T, TE><<<E->nfin, 256, 0, E->stream>>>(mem, E->st_dev, E->fin_start, E->M, fc, E->partial);
-  kb_control<T, TE><<<E->M, 256, 0, E->stream>>>(mem, E->st_dev, E->fin_start, E->partial, tb.emb_order,
-                                                  tb.has_emb, nrhs);
+  kb_control<T, TE><<<E->M, 256, 0, E->stream>>>(mem, E->st_dev, E->start[EK_STAGE][E->var[EK_STAGE]], E->partial,
+                                                  tb.emb_order, tb.has_emb, tb.s, E->unit, E->tab_dev);
+}
+
+// Members' states and coefficients (for the dt of their next attempt) to the device.
+static pf_status upload_states(pf_ens* E) {
+  for (int m = 0; m < E->M; ++m) fill_tab(E->tab, E->st_host[m].dt, E->tab_host[m]);
+  PF_HIP(hipMemcpyAsync(E->st_dev, E->st_host, sizeof(EState) * E->M, hipMemcpyHostToDevice, E->stream));
+  PF_HIP(hipMemcpyAsync(E->tab_dev, E->tab_host, sizeof(ArkTab) * E->M, hipMemcpyHostToDevice, E->stream));
+  return PF_OK;
 }
 
 static void drop_graph(pf_ens* E) {
@@ -638,10 +568,7 @@ static pf_status build_members(pf_ens* E) {
     e.mk = v->mk;
     e.ybuf[0] = v->y;
     e.ybuf[1] = v->ynew;
-    for (int j = 0; j < 6; ++j) {
-      e.FI[j] = v->FI[j];
-      e.FE[j] = (cx<TE>*)v->FE[j];
-    }
+    for (int j = 0; j < 6; ++j) e.FE[j] = (cx<TE>*)v->FE[j];
     e.T1 = (cx<T>*)v->scratch;
     e.T3 = e.T1 + 4 * v->g.fs;
     if constexpr (sizeof(T) == 8) {
@@ -692,17 +619,7 @@ pf_status pf_ensemble_init(int32_t n, const pf_params* per_member, void* stream,
     E->own_stream = true;
   }
   E->tab = table_for(p0.method);
-  for (int i = 0; i < 6; ++i) {
-    E->fe_need[i] = fe_needed(E->tab, i);
-    E->fi_need[i] = fi_needed(E->tab, i);
-  }
-  E->fi0_derived = E->tab.AI[0][0] == 0.0 && E->fi_need[0];
-  {
-    bool same_b = true;
-    for (int j = 0; j < E->tab.s; ++j) same_b = same_b && E->tab.bE[j] == E->tab.bI[j];
-    E->fold_last = E->tab.has_emb && same_b && E->fi0_derived && E->tab.s >= 2 && E->fe_need[E->tab.s - 1] &&
-                   E->fi_need[E->tab.s - 1];
-  }
+  fill_tab(E->tab, 1.0, E->unit);
   pf_status s = PF_OK;
   // per-size twiddle tables
   for (int m = 0; m < n && s == PF_OK; ++m) {
@@ -748,10 +665,7 @@ pf_status pf_ensemble_init(int32_t n, const pf_params* per_member, void* stream,
     if (s == PF_OK) s = ens_alloc(E, (void**)&v->ynew, k64);
     E->yb0.push_back(v->y);
     E->yb1.push_back(v->ynew);
-    for (int i = 0; i < 6 && s == PF_OK; ++i) {
-      s = ens_alloc(E, (void**)&v->FI[i], k64);
-      if (s == PF_OK) s = ens_alloc(E, &v->FE[i], fe);
-    }
+    for (int i = 0; i < E->tab.s && s == PF_OK; ++i) s = ens_alloc(E, &v->FE[i], fe);
     if (s == PF_OK) s = ens_alloc(E, &v->scratch, v->scratch_bytes);
     if (s == PF_OK) s = ens_alloc(E, (void**)&v->partial, sizeof(double) * 4 * v->nblk_red);
     if (s == PF_OK) s = ens_alloc(E, (void**)&v->red, sizeof(double) * 8);
@@ -768,6 +682,8 @@ pf_status pf_ensemble_init(int32_t n, const pf_params* per_member, void* stream,
   if (s == PF_OK) s = build_lists(E);
   if (s == PF_OK) s = ens_alloc(E, (void**)&E->st_dev, sizeof(EState) * n);
   if (s == PF_OK && hipHostMalloc((void**)&E->st_host, sizeof(EState) * n, 0) != hipSuccess) s = PF_ERR_OOM;
+  if (s == PF_OK) s = ens_alloc(E, (void**)&E->tab_dev, sizeof(ArkTab) * n);
+  if (s == PF_OK && hipHostMalloc((void**)&E->tab_host, sizeof(ArkTab) * n, 0) != hipSuccess) s = PF_ERR_OOM;
   if (s == PF_OK) {
     for (int m = 0; m < n; ++m) {
       EState& x = E->st_host[m];
@@ -804,6 +720,7 @@ void pf_ensemble_finalize(pf_ens* E) {
   }
   for (void* p : E->allocs) hipFree(p);
   if (E->st_host) hipHostFree(E->st_host);
+  if (E->tab_host) hipHostFree(E->tab_host);
   if (E->own_stream && E->stream) hipStreamDestroy(E->stream);
   delete E;
 }
@@ -915,7 +832,8 @@ pf_status pf_ensemble_advance(pf_ens* E, const double* t_final, int32_t max_step
     x.done = (x.t >= x.tf * (1.0 - 1e-15)) ? 1 : 0;
     if (!x.done) x.dt = std::min(std::min(x.dt_next, x.dt_max), x.tf - x.t);
   }
-  PF_HIP(hipMemcpyAsync(E->st_dev, E->st_host, sizeof(EState) * E->M, hipMemcpyHostToDevice, E->stream));
+  pf_status up = upload_states(E);
+  if (up != PF_OK) return up;
   if (!E->exec) {
     pf_status s = capture_step(E);
     if (s != PF_OK) return s;
@@ -978,7 +896,8 @@ pf_status pf_ensemble_autotune(pf_ens* E, int32_t reps) {
   // time each kind on all members (state untouched: the stage arrays and
   // temporaries are overwritten, the state buffers only read)
   for (int m = 0; m < E->M; ++m) E->st_host[m].done = 0;
-  PF_HIP(hipMemcpyAsync(E->st_dev, E->st_host, sizeof(EState) * E->M, hipMemcpyHostToDevice, E->stream));
+  pf_status up = upload_states(E);
+  if (up != PF_OK) return up;
   hipEvent_t e0, e1;
   PF_HIP(hipEventCreate(&e0));
   PF_HIP(hipEventCreate(&e1));
@@ -988,10 +907,10 @@ pf_status pf_ensemble_autotune(pf_ens* E, int32_t reps) {
     for (int v = 0; v < 2; ++v) {
       E->var[k] = v;
       const int stage = (k == EK_YFFT4 || k == EK_YFFT3) ? 1 : 0;
-      // the stage kernel differs per stage (number of previous stages, the
-      // last stage's update sums): time the whole sequence of a step
+      // the stage kernel differs per stage (number of previous stages): time
+      // the whole sequence of a step, its update included
       const int s0 = (k == EK_STAGE) ? 0 : stage;
-      const int s1 = (k == EK_STAGE) ? E->tab.s : stage + 1;
+      const int s1 = (k == EK_STAGE) ? E->tab.s + 1 : stage + 1;
       auto run = [&]() {
         for (int st = s0; st < s1; ++st) {
           if (E->mixed)

@@ -1,11 +1,12 @@
 // HIP kernels of one ImEx-ARK stage for the pseudospectral phase-field model.
 //
 // A stage (Methods, "Time integration", Eq. ARK_stage, with the right-hand
-// side of Eqs. composition / order) is nine HBM-streaming passes over the
+// side of Eqs. composition / order) is eight or nine HBM-streaming passes over the
 // half spectrum [field][z][y][kx] (row pitch P complex values):
 //
-//  stage_invz    combine previous stage derivatives, implicit solve per mode,
-//                F^I = L z, inverse z-FFT of the 4 state fields      (z pass)
+//  stage_invz    FP64: forward z-FFT of the previous stage's driving force,
+//                F^E_eta = -L g~; combine previous stage derivatives, implicit
+//                solve per mode, inverse z-FFT of the 4 state fields (z pass)
 //  ypass<+1>     inverse y-FFT of the 4 state fields                   (y pass)
 //  xpass_theta   c2r of eta_v, theta_v = h(eta_v), r2c of theta_v      (x pass)
 //  ypass<-1>     forward y-FFT of theta                                (y pass)
@@ -14,10 +15,10 @@
 //  ypass<+1>     inverse y-FFT of e~                                   (y pass)
 //  xpass_drive   c2r of c, eta_v, e_v, driving force, r2c              (x pass)
 //  ypass<-1>     forward y-FFT of the driving force                    (y pass)
-//  zpass_fwd_ac  forward z-FFT, F^E_eta = -L g~                        (z pass)
+//  zpass_fwd_ac  mixed form and pf_rhs: forward z-FFT, F^E_eta = -L g~ (z pass)
 //
-// followed once per step by `finalize` (update, embedded error, WRMS partial
-// sums).  z and y passes give each work-group TX consecutive kx columns of one
+// followed once per step by `finalize` (FP64: the last forward z-FFT; update,
+// embedded error, WRMS partial sums).  z and y passes give each work-group TX consecutive kx columns of one
 // plane so every global access is TX contiguous complex values; x passes give
 // each work-group RB whole rows.  Line FFTs run in LDS with Stockham passes;
 // inputs and outputs of a line stay in registers so the pointwise and
@@ -281,156 +282,199 @@ struct ColGeo {
 };
 
 // ---- K-A: stage combine + implicit solve + inverse z-FFT -------------------
-template <typename TE>
-struct StageArgs {
-  const cx<double>* y;
-  const cx<TE>* FE[6];
-  const cx<double>* FI[6];
-  double cE[6], cI[6];     // dt * A^E_ij, dt * A^I_ij for j < i
-  int nprev;
-  double gdt;              // dt * A^I_ii
-  cx<double>* FI_out;      // F^I_i (may be null when unused)
-  cx<TE>* FEc_out;         // split A: explicit CH part from z_c (may be null)
-  // 1: F^I_1 is not read from FI[0] but formed as L(k) y.  With an explicit
-  // first stage (A^I_11 = 0) the first stage value is the state itself, so
-  // F^I_1 = L y exactly and the array is never stored.
-  int fi0_from_y;
-  // Last stage of an embedded method whose explicit and implicit weights
-  // agree (b^E = b^I = b; one embedded b~), U_out non-null: the update and
-  // error sums of the step (Eqs. ARK_method, ARK_embedding) over every term
-  // but the last stage's explicit derivative are formed here, from values
-  // this kernel loads anyway plus the last stage's own F^I (never stored):
-  //   U = y + dt (sum_{j<i} ub_j (F^E_j + F^I_j) + ub_i F^I_i),
-  //   E =     dt (sum_{j<i} eb_j (F^E_j + F^I_j) + eb_i F^I_i),
-  // with ub = b and eb = b - b~ (zero where a stage array is not kept).  The
-  // update then reads y, U, E and F^E_i.  One weight set for both parts keeps
-  // the uniform operands few (they live in scalar registers).
-  cx<double>* U_out;
-  cx<double>* E_out;
-  double ub[6], eb[6];  // indices < i; ub[i], eb[i] in ubs, ebs
-  double ubs, ebs;
-  double fdt;           // dt
+// The pair's coefficients for one attempted step, as the kernels read them
+// (uniform operands).  Every pair here has an explicit first stage and one
+// diagonal coefficient; the embedded ones share b between both parts.
+struct ArkTab {
+  double cE[6][6], cI[6][6];  // dt A^E_kj, dt A^I_kj (j < k)
+  double gdt;                 // dt A^I_kk, k >= 2
+  double dt;
+  double ub[6], eb[6];        // b and b - b~
+  double bl, dl;              // dt b_s, dt (b_s - b~_s) of the last explicit derivative
+  int want_err;
 };
 
-// Stage combination for one element (Eq. ARK_stage restricted to the
-// previous stages), then the implicit solve z = r / (1 - dt A^I_ii L(k)).
-template <typename TE, int NP>
-__device__ inline cx<double> stage_value(const StageArgs<TE>& sa, long long idx, double L, cx<double>* FIo,
-                                         cx<TE>* FEo, double fea_k2, int f) {
-  const cx<double> y0 = sa.y[idx];
-  const bool fold = sa.U_out != nullptr;  // uniform
-  cx<double> fe[NP > 0 ? NP : 1], fi[NP > 0 ? NP : 1];
+// Arrays and scalars of one attempted step.
+template <typename TE>
+struct StepArgs {
+  const cx<double>* y;
+  cx<TE>* FE[6];         // F^E_j
+  cx<double>* FI_out;    // f^I(y) for a caller (first stage only; may be null)
+  cx<TE>* FEc_out;       // split A: explicit CH part from z_c (may be null)
+  // update and error (body_final)
+  cx<double>* ynew;
+  cx<double>* err_out;   // the error estimate, for a norm taken in real space (may be null)
+  double rtol, atol, sc; // sc = 1/sqrt(N^3)
+};
+
+// Stage values of one mode of one field (Eq. ARK_stage): z_1 = y and, for
+// k = 2 .. NP + 1, z_k = (y + dt sum_{j<k} (A^E_kj F^E_j + A^I_kj F^I_j)) /
+// (1 - dt A^I_kk L) with F^I_j = L z_j.  Returns z_{NP+1}; fi[0..NP] receives
+// F^I_1 .. F^I_{NP+1}.
+//
+// The linear part is diagonal in k, so every earlier F^I follows from the
+// state and the explicit derivatives: it is formed again here (NP (NP + 1)
+// complex multiply-adds, at most 0.6 ms of FP64 arithmetic per pass at 512^3)
+// instead of being kept in arrays of its own: a step at 512^3 moves 32 % less
+// in its stage and update passes in FP64, 44 % less in the mixed form.  Each
+// F^I is pinned, so that it is rounded as a stored one would be.
+template <int NP, class TabP>
+__device__ inline cx<double> ark_chain(TabP tb, double L, cx<double> y0, const cx<double>* fe, cx<double>* fi) {
+  cx<double> z = y0;
+  fi[0] = L * y0;
+  pin(fi[0]);
 #pragma unroll
-  for (int j = 0; j < NP; ++j) {
-    const bool useF = fold && (sa.ub[j] != 0.0 || sa.eb[j] != 0.0);
-    const bool useE = sa.cE[j] != 0.0 || useF;
-    const bool useI = sa.cI[j] != 0.0 || useF;
-    fe[j] = useE ? to_d(sa.FE[j][idx]) : mk(0.0, 0.0);
-    if (j == 0 && sa.fi0_from_y)
-      fi[0] = L * y0;
-    else
-      fi[j] = useI ? sa.FI[j][idx] : mk(0.0, 0.0);
+  for (int k = 1; k <= NP; ++k) {
+    cx<double> r = y0;
+#pragma unroll
+    for (int j = 0; j < k; ++j) r = r + (tb->cE[k][j] * fe[j] + tb->cI[k][j] * fi[j]);
+    z = (1.0 / (1.0 - tb->gdt * L)) * r;
+    fi[k] = L * z;
+    pin(fi[k]);
   }
-  cx<double> r = y0;
-#pragma unroll
-  for (int j = 0; j < NP; ++j) r = r + (sa.cE[j] * fe[j] + sa.cI[j] * fi[j]);
-  const cx<double> zz = (sa.gdt != 0.0) ? (1.0 / (1.0 - sa.gdt * L)) * r : r;
-  const cx<double> fin = L * zz;
-  if (FIo) FIo[idx] = fin;
-  if (f == 0 && FEo) FEo[idx] = to_t<TE>((-fea_k2) * zz);
-  if (fold) {
-    cx<double> u = sa.ubs * fin, e = sa.ebs * fin;
-#pragma unroll
-    for (int j = 0; j < NP; ++j) {
-      const cx<double> fj = fe[j] + fi[j];
-      u = u + sa.ub[j] * fj;
-      e = e + sa.eb[j] * fj;
-    }
-    sa.U_out[idx] = y0 + sa.fdt * u;
-    sa.E_out[idx] = sa.fdt * e;
-  }
-  return zz;
+  return z;
 }
 
-template <typename T, typename TE, int N, int TX, int RE, int NP, bool GUARD = false>
-__device__ inline void body_stage_invz(const StageArgs<TE>& sa, const Geo& g, const ModelK& m, const cx<T>* twz,
-                                       cx<T>* out, int tile, int tid, cx<T>* lds) {
+// Place of a thread in a z-column pass over single fields: blocks run over
+// (field, kx tile, y), the tiles of one field next to each other.  One field
+// per block: four times the blocks of a loop over the fields, which on small
+// grids is what fills the chip (64^3: 320 work-groups of one wavefront each
+// before).
+template <int N, int TX, int RE, bool GUARD>
+struct ZItem {
+  int f, col, bf, x, y;
+  uint32_t base, lstride;
+  bool act, valid;
+  __device__ inline ZItem(const Geo& g, int item, int tid) {
+    using CG = ColGeo<N, TX, RE>;
+    const int nbx = (g.nxh + TX - 1) / TX;
+    const int ntile = nbx * g.ny;
+    f = item / ntile;
+    const int tile = item % ntile;
+    y = tile / nbx;
+    col = tid % TX;
+    bf = tid / TX;
+    x = (tile % nbx) * TX + col;
+    act = !GUARD || tid < CG::THREADS;
+    valid = act && x < g.nxh;
+    lstride = (uint32_t)(g.ny * g.P);
+    base = (uint32_t)(y * g.P + x);
+  }
+};
+
+// Forward z-transform of the driving force g of order parameter f - 1 and
+// F^E = -L g~, left in LDS at the thread's own positions (rounded to TE).
+template <typename T, typename TE, int N, int TX, int RE, bool GUARD, class Buf>
+__device__ inline void fresh_explicit(const cx<T>* gk, const ZItem<N, TX, RE, GUARD>& q, const Geo& g, const ModelK& m,
+                                      const cx<T>* twz, Buf buf) {
   using CG = ColGeo<N, TX, RE>;
-  const bool act = !GUARD || tid < CG::THREADS;
-  const int nbx = (g.nxh + TX - 1) / TX;
-  const int xb = tile % nbx;
-  const int y = tile / nbx;
-  const int col = tid % TX;
-  const int bf = tid / TX;
-  const int x = xb * TX + col;
-  const bool valid = act && x < g.nxh;
-  const double kx = x * g.kfx;
-  const double ky = mode_of(y, g.ny) * g.kfy;
-  auto buf = [&](int pos) -> cx<T>& { return lds[pos * CG::LD + col]; };
-  for (int f = 0; f < 4; ++f) {
-    // combine + solve position by position into LDS (bounded unroll keeps the
-    // stage-array loads of a few positions in flight, not all of them)
-    __syncthreads();
+  const cx<T>* src = gk + (q.f - 1) * g.fs;
+  cx<T> a[CG::R0];
+#pragma unroll
+  for (int t = 0; t < CG::R0; ++t)
+    a[t] = q.valid ? at32(src, q.base + (uint32_t)(q.bf + t * CG::TL) * q.lstride) : mk<T>(0, 0);
+  line_fft<T, N, -1, RE>(a, q.bf, twz, buf, q.act);
+  const T nl = (T)(-m.L);
+  if (q.act) {
+#pragma unroll
+    for (int t = 0; t < CG::R0; ++t) buf(q.bf + t * CG::TL) = nl * a[t];
+  }
+}
+
+// Whether the stage and update passes take an order parameter's newest F^E
+// straight from the forward z-transform of its driving force (FP64: at 512^3
+// that saves one read of three fields per stage).  In the mixed form F^E comes
+// from k_zpass_fwd_ac, as pf_rhs gives it: the FP32 transform compiled into
+// these passes rounds its butterflies in another order, which the step's
+// result would show at 4e-8.
+template <typename T>
+constexpr bool fresh_fe = sizeof(T) == 8;
+
+// Operands of one mode as they come from memory: the state, and F^E_1 .. F^E_NE
+// (FRESH: the last one only for the composition; an order parameter's is in LDS).
+template <typename TE, int NE, bool FRESH>
+struct StageRow {
+  cx<double> y;
+  cx<TE> e[NE > 0 ? NE : 1];
+  __device__ inline void load(const StepArgs<TE>& sa, const Geo& g, int f, uint32_t i) {
+    const long long fo = f * g.fs;
+    y = at32(sa.y + fo, i);
+#pragma unroll
+    for (int j = 0; j < NE - 1; ++j) e[j] = at32((const cx<TE>*)sa.FE[j] + fo, i);
+    if constexpr (NE > 0) {
+      if (!FRESH || f == 0) e[NE - 1] = at32((const cx<TE>*)sa.FE[NE - 1] + fo, i);
+    }
+  }
+};
+
+// Stage NP + 1: with fresh_fe, for an order parameter the forward z-transform of
+// the previous stage's driving force (its F^E is written once, and used from
+// LDS); the stage value, and its inverse z-transform into `out`.  Bound by HBM
+// at large sizes, by the serial loads of a line's positions at small ones: the
+// next position's operands are loaded while this one's are combined.  A fixed
+// ARK4 step at 512^3 took 114 ms with this pass and the update as below (130
+// with F^I stored and four fields per work-group), the mixed step at 256^3 8.8
+// (10.8), an adaptive one at 64^3 0.40 (0.53).
+template <typename T, typename TE, int N, int TX, int RE, int NP, bool GUARD = false, class TabP>
+__device__ inline void body_stage(const StepArgs<TE>& sa, TabP tb, const Geo& g, const ModelK& m,
+                                  const cx<T>* gk, const cx<T>* twz, cx<T>* out, int item, int tid, cx<T>* lds) {
+  using CG = ColGeo<N, TX, RE>;
+  const ZItem<N, TX, RE, GUARD> q(g, item, tid);
+  auto buf = [&](int pos) -> cx<T>& { return lds[pos * CG::LD + q.col]; };
+  if constexpr (NP > 0 && fresh_fe<T>) {
+    if (q.f > 0) fresh_explicit<T, TE, N, TX, RE, GUARD>(gk, q, g, m, twz, buf);
+  }
+  const double kx = q.x * g.kfx, ky = mode_of(q.y, g.ny) * g.kfy;
+    const long long fo = q.f * g.fs;
+  StageRow<TE, NP, fresh_fe<T>> nxt;
+  if (q.valid) nxt.load(sa, g, q.f, q.base + (uint32_t)q.bf * q.lstride);
 #pragma unroll 1
-    for (int t = 0; t < CG::R0; ++t) {
-      const int z = bf + t * CG::TL;
-      const long long idx = f * g.fs + ((long long)z * g.ny + y) * g.P + x;
-      cx<double> r = mk(0.0, 0.0);
-      if (valid) {
-        const double kz = mode_of(z, g.nz) * g.kfz;
-        const double k2 = kx * kx + ky * ky + kz * kz;
-        r = m.inv_n3 * stage_value<TE, NP>(sa, idx, lsym(m, f, k2), sa.FI_out, sa.FEc_out, m.fEa * k2, f);
-      }
-      if (act) buf(z) = to_t<T>(r);
-    }
-    __syncthreads();
-    cx<T> a[CG::R0];
+  for (int t = 0; t < CG::R0; ++t) {
+    const int z = q.bf + t * CG::TL;
+    const uint32_t i = q.base + (uint32_t)z * q.lstride;
+    const StageRow<TE, NP, fresh_fe<T>> cur = nxt;
+    if (q.valid && t + 1 < CG::R0) nxt.load(sa, g, q.f, i + (uint32_t)CG::TL * q.lstride);
+    cx<double> r = mk(0.0, 0.0);
+    if (q.valid) {
+      const double kz = mode_of(z, g.nz) * g.kfz;
+      const double k2 = kx * kx + ky * ky + kz * kz;
+      const double L = lsym(m, q.f, k2);
+      cx<double> fe[NP > 0 ? NP : 1], fi[NP + 1];
 #pragma unroll
-    for (int t = 0; t < CG::R0; ++t) a[t] = act ? buf(bf + t * CG::TL) : mk<T>(0, 0);
-    line_fft<T, N, +1, RE>(a, bf, twz, buf, act);
-    if (valid) {
-#pragma unroll
-      for (int t = 0; t < CG::R0; ++t) {
-        const int z = bf + t * CG::TL;
-        out[f * g.fs + ((long long)z * g.ny + y) * g.P + x] = a[t];
+      for (int j = 0; j < NP; ++j) fe[j] = to_d(cur.e[j]);
+      if constexpr (NP > 0 && fresh_fe<T>) {
+        if (q.f > 0) {
+          const cx<T> v = buf(z);
+          const cx<TE> e = mk<TE>((TE)v.re, (TE)v.im);
+          at32(sa.FE[NP - 1] + fo, i) = e;
+          fe[NP - 1] = to_d(e);
+        }
       }
+      const cx<double> zz = ark_chain<NP>(tb, L, cur.y, fe, fi);
+      if constexpr (NP == 0) {
+        if (sa.FI_out) at32(sa.FI_out + fo, i) = fi[0];
+      }
+      if (q.f == 0 && sa.FEc_out) at32(sa.FEc_out, i) = to_t<TE>((-m.fEa * k2) * zz);
+      r = m.inv_n3 * zz;
     }
+    if (q.act) buf(z) = to_t<T>(r);
+  }
+  cx<T> a[CG::R0];
+#pragma unroll
+  for (int t = 0; t < CG::R0; ++t) a[t] = q.act ? buf(q.bf + t * CG::TL) : mk<T>(0, 0);
+  line_fft<T, N, +1, RE>(a, q.bf, twz, buf, q.act);
+  if (q.valid) {
+    cx<T>* of = out + fo;
+#pragma unroll
+    for (int t = 0; t < CG::R0; ++t) at32(of, q.base + (uint32_t)(q.bf + t * CG::TL) * q.lstride) = a[t];
   }
 }
 
 template <typename T, typename TE, int N, int TX, int RE, int NP>
 __global__ void __launch_bounds__((ColGeo<N, TX, RE>::THREADS))
-k_stage_invz(StageArgs<TE> sa, Geo g, ModelK m, const cx<T>* twz, cx<T>* __restrict__ out) {
+k_stage_invz(StepArgs<TE> sa, ArkTab tb, Geo g, ModelK m, const cx<T>* gk, const cx<T>* twz, cx<T>* out) {
   __shared__ cx<T> lds[N * ColGeo<N, TX, RE>::LD];
-  body_stage_invz<T, TE, N, TX, RE, NP>(sa, g, m, twz, out, xcd_tile(blockIdx.x, gridDim.x), threadIdx.x, lds);
-}
-
-// Stage combination and implicit solve only (a stage whose explicit
-// derivative is never used, e.g. the implicit stage of IMEX Euler).
-template <typename TE>
-__global__ void __launch_bounds__(256) k_combine(StageArgs<TE> sa, Geo g, ModelK m) {
-  const long long nrow = (long long)g.nz * g.ny;
-  const long long total = 4 * nrow * g.nxh;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int x = (int)(i % g.nxh);
-    const long long fr = i / g.nxh;
-    const int f = (int)(fr / nrow);
-    const long long row = fr % nrow;
-    const int y = (int)(row % g.ny), z = (int)(row / g.ny);
-    const double kx = x * g.kfx, ky = mode_of(y, g.ny) * g.kfy, kz = mode_of(z, g.nz) * g.kfz;
-    const double k2 = kx * kx + ky * ky + kz * kz;
-    const long long idx = fr * g.P + x;
-    const double L = lsym(m, f, k2);
-    const cx<double> y0 = sa.y[idx];
-    cx<double> r = y0;
-    for (int j = 0; j < sa.nprev; ++j) {
-      if (sa.cE[j] != 0.0) r = r + sa.cE[j] * to_d(sa.FE[j][idx]);
-      if (sa.cI[j] != 0.0) r = r + sa.cI[j] * ((j == 0 && sa.fi0_from_y) ? L * y0 : sa.FI[j][idx]);
-    }
-    const cx<double> zz = (sa.gdt != 0.0) ? (1.0 / (1.0 - sa.gdt * L)) * r : r;
-    if (sa.FI_out) sa.FI_out[idx] = L * zz;
-  }
+  body_stage<T, TE, N, TX, RE, NP>(sa, &tb, g, m, gk, twz, out, xcd_tile(blockIdx.x, gridDim.x), threadIdx.x, lds);
 }
 
 // ---- generic column FFT along y or z (in or out of place) -----------------
@@ -1165,83 +1209,104 @@ __device__ inline double block_sum(double v, double* sh) {
 }
 
 // ---- finalize: update, embedded error, WRMS partial sums ------------------
-template <typename TE>
-struct FinArgs {
-  const cx<double>* y;
-  cx<double>* ynew;
-  const cx<TE>* FE[6];
-  const cx<double>* FI[6];
-  double bE[6], bI[6];   // update weights (times dt)
-  double dE[6], dI[6];   // error weights (b - b~) times dt
-  int s;
-  int want_err;
-  int fi0_from_y;         // F^I_1 = L(k) y (explicit first stage), FI[0] unread
-  // partial sums from the last stage (null: off): y_new = U + sum(...),
-  // error = E + sum(...); the weights then hold only the last stage's F^E term
-  const cx<double>* U;
-  const cx<double>* E;
-  double rtol, atol, sc;  // sc = 1/sqrt(N^3)
-  double* partial;        // [2 * gridDim.x]: sum of squares, non-finite count
-  // non-null: the error estimate is also stored here (it may be E or FI[0]:
-  // each element is read before it is written, by the same thread), for a
-  // norm taken in real space
-  cx<double>* err_out;
-};
-
-template <typename TE>
-__global__ void __launch_bounds__(256) k_finalize(FinArgs<TE> fa, Geo g, ModelK m) {
-  __shared__ double sh[16];
-  // 32-bit indices: 4 nz ny (nx/2+1) < 2^31 on every supported grid
-  const unsigned nrow = (unsigned)(g.nz * g.ny);
-  const unsigned nxh = (unsigned)g.nxh;
-  const unsigned total = 4u * nrow * nxh;
-  double acc = 0.0, bad = 0.0;
-  for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
-    const unsigned x = i % nxh;
-    const unsigned fr = i / nxh;  // f * nrow + row
-    const long long idx = (long long)fr * g.P + x;
-    const cx<double> y0 = fa.y[idx];
-    // every stage array this step reads is loaded before any is used, so the
-    // loads of one element are in flight together (unused weights are zero)
-    cx<double> fi[6], fe[6];
+// The update y_new = y + dt sum_j (b^E_j F^E_j + b^I_j F^I_j), the embedded
+// error and the WRMS terms of one z column of one field, over S stages with
+// every F^I formed again (ark_chain).  With fresh_fe an order parameter's newest
+// F^E comes straight from the forward z-transform of its driving force and is
+// never stored.  S == 2 is IMEX Euler, whose last stage has no explicit derivative.
+// acc and bad receive the thread's error terms and count of non-finite values.
+template <typename T, typename TE, int N, int TX, int RE, int S, bool GUARD = false, class TabP>
+__device__ inline void body_final(const StepArgs<TE>& sa, TabP tb, const Geo& g, const ModelK& m,
+                                  const cx<T>* gk, const cx<T>* twz, int item, int tid, cx<T>* lds, double& acc,
+                                  double& bad) {
+  using CG = ColGeo<N, TX, RE>;
+  constexpr int NF = S == 2 ? 1 : S;  // explicit derivatives of the pair
+  const ZItem<N, TX, RE, GUARD> q(g, item, tid);
+  auto buf = [&](int pos) -> cx<T>& { return lds[pos * CG::LD + q.col]; };
+  if constexpr (fresh_fe<T>) {
+    if (q.f > 0) fresh_explicit<T, TE, N, TX, RE, GUARD>(gk, q, g, m, twz, buf);
+  }
+  acc = bad = 0.0;
+  if (!q.valid) return;
+  const double kx = q.x * g.kfx, ky = mode_of(q.y, g.ny) * g.kfy;
+    const double mult = (q.x == 0 || 2 * q.x == g.nx) ? 1.0 : 2.0;
+  const long long fo = q.f * g.fs;
+  StageRow<TE, NF, fresh_fe<T>> nxt;
+  nxt.load(sa, g, q.f, q.base + (uint32_t)q.bf * q.lstride);
+#pragma unroll 1
+  for (int t = 0; t < CG::R0; ++t) {
+    const int z = q.bf + t * CG::TL;
+    const uint32_t i = q.base + (uint32_t)z * q.lstride;
+    const StageRow<TE, NF, fresh_fe<T>> cur = nxt;
+    if (t + 1 < CG::R0) nxt.load(sa, g, q.f, i + (uint32_t)CG::TL * q.lstride);
+    const double kz = mode_of(z, g.nz) * g.kfz;
+    const double L = lsym(m, q.f, kx * kx + ky * ky + kz * kz);
+    cx<double> fe[NF], fi[S];
 #pragma unroll
-    for (int j = 0; j < 6; ++j) {
-      const bool hasI = j < fa.s && (fa.bI[j] != 0.0 || (fa.want_err && fa.dI[j] != 0.0));
-      const bool hasE = j < fa.s && (fa.bE[j] != 0.0 || (fa.want_err && fa.dE[j] != 0.0));
-      fi[j] = (hasI && !(j == 0 && fa.fi0_from_y)) ? fa.FI[j][idx] : mk(0.0, 0.0);
-      fe[j] = hasE ? to_d(fa.FE[j][idx]) : mk(0.0, 0.0);
+    for (int j = 0; j < NF; ++j) fe[j] = to_d(cur.e[j]);
+    if constexpr (fresh_fe<T>) {
+      if (q.f > 0) {
+        const cx<T> v = buf(z);
+        fe[NF - 1] = to_d(mk<TE>((TE)v.re, (TE)v.im));
+      }
     }
-    if (fa.fi0_from_y) {
-      const unsigned f = fr / nrow, row = fr % nrow;
-      const int yy = (int)(row % (unsigned)g.ny), z = (int)(row / (unsigned)g.ny);
-      const double kx = (int)x * g.kfx, ky = mode_of(yy, g.ny) * g.kfy, kz = mode_of(z, g.nz) * g.kfz;
-      const double k2 = kx * kx + ky * ky + kz * kz;
-      fi[0] = lsym(m, (int)f, k2) * y0;
-    }
-    cx<double> inc = mk(0.0, 0.0), err = fa.E ? fa.E[idx] : mk(0.0, 0.0);
+    ark_chain<S - 1>(tb, L, cur.y, fe, fi);
+    // the newest explicit derivative's term on its own, the rest summed first
+    cx<double> last = tb->bl * fe[NF - 1], yn, err = mk(0.0, 0.0);
+    pin(last);
+    if constexpr (S == 2) {
+      cx<double> im = tb->dt * fi[1];
+      pin(im);
+      yn = cur.y + (last + im);
+    } else {
+      cx<double> u = tb->ub[S - 1] * fi[S - 1], e = tb->eb[S - 1] * fi[S - 1];
 #pragma unroll
-    for (int j = 0; j < 6; ++j) {
-      if (j >= fa.s) break;
-      inc = inc + (fa.bI[j] * fi[j] + fa.bE[j] * fe[j]);
-      err = err + (fa.dI[j] * fi[j] + fa.dE[j] * fe[j]);
+      for (int j = 0; j < S - 1; ++j) {
+        const cx<double> fj = fe[j] + fi[j];
+        u = u + tb->ub[j] * fj;
+        e = e + tb->eb[j] * fj;
+      }
+      u = cur.y + tb->dt * u;
+      e = tb->dt * e;
+      cx<double> le = tb->dl * fe[NF - 1];
+      pin(u);
+      pin(e);
+      pin(le);
+      yn = u + last;
+      err = e + le;
     }
-    const cx<double> yn = (fa.U ? fa.U[idx] : y0) + inc;
-    fa.ynew[idx] = yn;
+    at32(sa.ynew + fo, i) = yn;
     if (!isfinite(yn.re) || !isfinite(yn.im)) bad += 1.0;
-    if (fa.err_out) fa.err_out[idx] = err;
-    if (fa.want_err) {
-      const double mult = (x == 0 || 2 * (int)x == g.nx) ? 1.0 : 2.0;
-      const double ay = sqrt(y0.re * y0.re + y0.im * y0.im) * fa.sc;
-      const double wgt = 1.0 / (fa.rtol * ay + fa.atol);
-      const double e2 = (err.re * err.re + err.im * err.im) * fa.sc * fa.sc;
-      acc += mult * e2 * wgt * wgt;
+    if (tb->want_err) {
+      if (sa.err_out) at32(sa.err_out + fo, i) = err;
+      const double ay = sqrt(cur.y.re * cur.y.re + cur.y.im * cur.y.im) * sa.sc;
+      const double wgt = 1.0 / (sa.rtol * ay + sa.atol);
+      acc += mult * ((err.re * err.re + err.im * err.im) * sa.sc * sa.sc) * wgt * wgt;
     }
   }
-  const double s0 = block_sum(acc, sh);
-  const double s1 = block_sum(bad, sh);
+}
+
+// Threads of an update block: its columns' threads, filled up to whole
+// wavefronts for the block sums.
+template <int N, int TX, int RE>
+constexpr int final_threads() {
+  return (ColGeo<N, TX, RE>::THREADS + 63) / 64 * 64;
+}
+
+template <typename T, typename TE, int N, int TX, int RE, int S>
+__global__ void __launch_bounds__((final_threads<N, TX, RE>()))
+k_finalize(StepArgs<TE> sa, ArkTab tb, Geo g, ModelK m, const cx<T>* gk, const cx<T>* twz, double* partial) {
+  __shared__ cx<T> lds[N * ColGeo<N, TX, RE>::LD];
+  __shared__ double sh[16];
+  double acc, bad;
+  constexpr bool fill = final_threads<N, TX, RE>() != ColGeo<N, TX, RE>::THREADS;
+  body_final<T, TE, N, TX, RE, S, fill>(sa, &tb, g, m, gk, twz, xcd_tile(blockIdx.x, gridDim.x), threadIdx.x, lds,
+                                        acc, bad);
+  acc = block_sum(acc, sh);
+  bad = block_sum(bad, sh);
   if (threadIdx.x == 0) {
-    fa.partial[2 * blockIdx.x] = s0;
-    fa.partial[2 * blockIdx.x + 1] = s1;
+    partial[2 * blockIdx.x] = acc;
+    partial[2 * blockIdx.x + 1] = bad;
   }
 }
 
@@ -1249,19 +1314,21 @@ __global__ void __launch_bounds__(256) k_finalize(FinArgs<TE> fa, Geo g, ModelK 
 // than one translation unit.
 namespace {
 
-// Sums n (value, flag) partial pairs in a fixed order into out[0], out[1].
+// Sums n (value, flag) partial pairs in a fixed order: block b of G adds its
+// G-th of them into out[2 b], out[2 b + 1].
 __global__ void __launch_bounds__(256) k_reduce_pairs(const double* partial, int n, double* out) {
   __shared__ double sh[16];
   double a = 0.0, b = 0.0;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+  const int i0 = (int)((long long)n * blockIdx.x / gridDim.x), i1 = (int)((long long)n * (blockIdx.x + 1) / gridDim.x);
+  for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
     a += partial[2 * i];
     b += partial[2 * i + 1];
   }
   a = block_sum(a, sh);
   b = block_sum(b, sh);
   if (threadIdx.x == 0) {
-    out[0] = a;
-    out[1] = b;
+    out[2 * blockIdx.x] = a;
+    out[2 * blockIdx.x + 1] = b;
   }
 }
 

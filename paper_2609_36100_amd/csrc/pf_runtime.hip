@@ -21,107 +21,12 @@
 #include "pf_context.hpp"
 #include "pf_inhom.hpp"
 #include "pf_kernels.hpp"
+#include "pf_plans.hpp"
+#include "pf_stage.hpp"
 
 using namespace pf;
 
-// ---- supported line lengths --------------------------------------------
-// Column passes (y, z) take N; row passes (x) take M = nx / 2.
-#define PF_COL_SIZES(X)                                                                                  \
-  X(8) X(16) X(24) X(32) X(40) X(48) X(56) X(64) X(80) X(96) X(128) X(160) X(168) X(192) X(256) X(320) X(336) \
-  X(384) X(504) X(512)
-#define PF_ROW_SIZES(X)                                                                                         \
-  X(4) X(8) X(12) X(16) X(20) X(24) X(28) X(32) X(40) X(48) X(64) X(80) X(84) X(96) X(128) X(160) X(168) X(192) \
-  X(252) X(256)
-
-template <class F>
-static bool col_dispatch(int n, F&& f) {
-  switch (n) {
-#define PF_CASE(N)                          \
-  case N:                                   \
-    f(std::integral_constant<int, N>{});    \
-    return true;
-    PF_COL_SIZES(PF_CASE)
-#undef PF_CASE
-    default:
-      return false;
-  }
-}
-
-template <class F>
-static bool row_dispatch(int m, F&& f) {
-  switch (m) {
-#define PF_CASE(N)                          \
-  case N:                                   \
-    f(std::integral_constant<int, N>{});    \
-    return true;
-    PF_ROW_SIZES(PF_CASE)
-#undef PF_CASE
-    default:
-      return false;
-  }
-}
-
-static bool col_supported(int n) {
-  return col_dispatch(n, [](auto) {});
-}
-static bool row_supported(int m) {
-  return row_dispatch(m, [](auto) {});
-}
-
-// Column-pass tiles: TX consecutive kx columns per work-group, end radix RE.
-// Two tile variants per kernel kind, chosen per context by the autotuner
-// (pf_autotune): variant 0 gives each row segment `seg0` contiguous bytes,
-// variant 1 twice that.  Small lines get wider tiles so a work-group has at
-// least one full wavefront; lines shorter than 64 have only variant 0.
 static const char* const ck_names[CK_COUNT] = {"colfft", "stage_invz", "zpass_elastic", "zpass_fwd_ac"};
-// Largest end radix of each kind's line plan (elem_bytes: 16 FP64, 8 FP32
-// complex values).  The FP64 elastic pass holds three fields in registers, so
-// it takes narrower tiles and its ends stay at radix 4 where 16 divides the
-// line length (half the registers per field of radix 8; radix 8 gained
-// nothing at 512^3); lines that 36 divides but 16 does not (504) take radix-6
-// ends, since the radix-3 ends they would otherwise get cost the pass a
-// quarter more time.  In FP32 the three fields fit at radix 8 (113 VGPRs at
-// 512: 8-column tiles ran 1.03 ms against 1.43 ms for 4-column radix-4 ones).
-constexpr int col_re(int kind, int elem_bytes = 16) {
-  return kind != CK_ELASTIC ? 8 : elem_bytes == 8 ? 8 : 6;
-}
-constexpr int col_tx(int n, int kind, int elem_bytes, int v) {
-  const int seg = (kind == CK_ELASTIC ? 32 : 64) << ((n >= 64) ? v : 0);
-  int tx = seg / elem_bytes;
-  if (tx < 1) tx = 1;
-  while (tx * line_threads(n, col_re(kind, elem_bytes)) < 64 && tx < 16) tx *= 2;
-  // long lines with small end radices (504 in the elastic pass: 168 threads
-  // per line) stay within 1024 threads per work-group
-  while (tx > 1 && tx * line_threads(n, col_re(kind, elem_bytes)) > 1024) tx /= 2;
-  return tx;
-}
-// Whether the wave-specialised column FFT (variant 2 of "colfft") exists for
-// lines of length n with elements of elem_bytes.
-static bool ws_supported(int n, int elem_bytes) {
-  bool ok = false;
-  col_dispatch(n, [&](auto NC) {
-    constexpr int N = decltype(NC)::value;
-    ok = elem_bytes == 16 ? ws_ok<double, N, col_tx(N, CK_FFT, 16, 1)>()
-                          : ws_ok<float, N, col_tx(N, CK_FFT, 8, 1)>();
-  });
-  return ok;
-}
-template <class F>
-static void with_variant(int v, F&& f) {
-  if (v)
-    f(std::integral_constant<int, 1>{});
-  else
-    f(std::integral_constant<int, 0>{});
-}
-// Rows per row-pass work-group: about 256 threads.
-constexpr int rb_of(int m) { return line_threads(m) >= 256 ? 1 : 256 / line_threads(m); }
-// Rows per work-group of the stage cycle's theta and drive passes: 128
-// threads where the line's thread count divides 128 (their drive pass ran
-// 9-16 % faster so, their FP64 theta pass 3-8 %, at 512^3 and 256^3), else
-// the general rule (lines of 42 or 84 threads would leave part-filled waves).
-constexpr int rb_x(int m) {
-  return line_threads(m) <= 128 && 128 % line_threads(m) == 0 ? 128 / line_threads(m) : rb_of(m);
-}
 
 #define PF_HIP(call)                                   \
   do {                                                 \
@@ -167,14 +72,6 @@ static pf_status upload_twiddles(pf_ctx* c, int slot, int n) {
   delete[] h64;
   delete[] h32;
   return s;
-}
-
-template <typename T>
-static const cx<T>* tw(const pf_ctx* c, int slot) {
-  if constexpr (sizeof(T) == 8)
-    return c->tw64[slot];
-  else
-    return c->tw32[slot];
 }
 
 static void setup_model(pf_ctx* c) {
@@ -245,40 +142,6 @@ static void setup_model(pf_ctx* c) {
 }
 
 // ---- launchers ----------------------------------------------------------------
-template <typename T, typename TE, int NP>
-static void launch_stage_np(pf_ctx* c, const StageArgs<TE>& sa, cx<T>* out) {
-  const Geo& g = c->g;
-  col_dispatch(g.nz, [&](auto NC) {
-    constexpr int N = decltype(NC)::value;
-    with_variant(c->var[CK_STAGE], [&](auto VC) {
-      constexpr int RE = col_re(CK_STAGE);
-      constexpr int TX = col_tx(N, CK_STAGE, sizeof(cx<T>), decltype(VC)::value);
-      const int nbx = (g.nxh + TX - 1) / TX;
-      k_stage_invz<T, TE, N, TX, RE, NP><<<dim3(nbx * g.ny), dim3(ColGeo<N, TX, RE>::THREADS), 0, c->stream>>>(
-          sa, g, c->mk, tw<T>(c, 0), out);
-    });
-  });
-}
-
-template <typename T, typename TE>
-static bool launch_stage_invz(pf_ctx* c, const StageArgs<TE>& sa, cx<T>* out, int do_fft) {
-  if (!col_supported(c->g.nz)) return false;
-  if (!do_fft) {
-    k_combine<TE><<<dim3(1024), dim3(256), 0, c->stream>>>(sa, c->g, c->mk);
-    return true;
-  }
-  switch (sa.nprev) {
-    case 0: launch_stage_np<T, TE, 0>(c, sa, out); break;
-    case 1: launch_stage_np<T, TE, 1>(c, sa, out); break;
-    case 2: launch_stage_np<T, TE, 2>(c, sa, out); break;
-    case 3: launch_stage_np<T, TE, 3>(c, sa, out); break;
-    case 4: launch_stage_np<T, TE, 4>(c, sa, out); break;
-    case 5: launch_stage_np<T, TE, 5>(c, sa, out); break;
-    default: return false;
-  }
-  return true;
-}
-
 template <typename T, int S, int AXIS>
 static bool launch_colfft(pf_ctx* c, const cx<T>* in, cx<T>* out, int nf, T scale) {
   const Geo& g = c->g;
@@ -556,8 +419,8 @@ static pf_status el_solve(pf_ctx* c, cx<double>* T1, cx<double>* FE0, int accumu
 }
 
 // The explicit right-hand side after the state's inverse z and y transforms,
-// with the inhomogeneous elastic force: equilibrium strain, driving forces,
-// forward transforms into FE (fields 1..3; field 0 from the strain's start).
+// with the inhomogeneous elastic force: equilibrium strain, driving forces and
+// their forward y transforms (T3); F^E_c from the strain's start.
 static pf_status run_rhs_inhom(pf_ctx* c, cx<double>* T1, cx<double>* FE, int accumulate) {
   const Geo& g = c->g;
   cx<double>* T3 = T1 + 4 * g.fs;
@@ -572,151 +435,129 @@ static pf_status run_rhs_inhom(pf_ctx* c, cx<double>* T1, cx<double>* FE, int ac
   prof_begin(c);
   ok = ok && launch_colfft<double, -1, 1>(c, T3, T3, 3, 1.0);
   prof_end(c, KC_YFFT, 6 * fk);
-  prof_begin(c);
-  ok = ok && launch_zpass_fwd_ac<double, double>(c, T3, FE);
-  prof_end(c, KC_ZFWD_AC, 6 * fk);
   if (!ok) return PF_ERR_UNSUPPORTED_SIZE;
   if (hipGetLastError() != hipSuccess) return PF_ERR_HIP;
   return PF_OK;
 }
 
-// ---- one stage: combine / implicit solve, then the explicit RHS chain ---------
+// F^E of the order parameters from their driving forces in T3.
 template <typename T, typename TE>
-static pf_status run_stage(pf_ctx* c, const StageArgs<TE>& sa, bool need_rhs, cx<TE>* FE_out) {
+static pf_status run_fwd_ac(pf_ctx* c, cx<TE>* FE) {
+  const double nv = (double)c->g.nz * c->g.ny * c->g.nxh;
+  prof_begin(c);
+  if (!launch_zpass_fwd_ac<T, TE>(c, (const cx<T>*)c->scratch + 4 * c->g.fs, FE)) return PF_ERR_UNSUPPORTED_SIZE;
+  prof_end(c, KC_ZFWD_AC, 3 * nv * (sizeof(cx<T>) + sizeof(cx<TE>)));
+  return hipGetLastError() == hipSuccess ? PF_OK : PF_ERR_HIP;
+}
+
+// ---- one stage: combine / implicit solve, then the explicit RHS chain ---------
+// The stage pass over np previous stages, then the explicit chain: F^E of the
+// composition into FE[0] and, with `fwd`, of the order parameters into its
+// fields 1..3; without it their driving forces are left in T3 after the
+// forward y transform (the next stage's pass or the update takes them on).
+template <typename T, typename TE>
+static pf_status run_stage(pf_ctx* c, const StepArgs<TE>& sa, int np, cx<TE>* FE, bool fwd) {
   cx<T>* T1 = (cx<T>*)c->scratch;
   cx<T>* T3 = T1 + 4 * c->g.fs;
   // algorithmic bytes: one valid half-spectrum field in T, TE and FP64
   const double nv = (double)c->g.nz * c->g.ny * c->g.nxh;
   const double fT = nv * sizeof(cx<T>), fE = nv * sizeof(cx<TE>), f64 = nv * sizeof(cx<double>);
-  double b_stage = 4 * f64;  // state read
-  const bool fold = sa.U_out != nullptr;
-  for (int j = 0; j < sa.nprev; ++j) {
-    const bool useF = fold && (sa.ub[j] != 0.0 || sa.eb[j] != 0.0);
-    const bool useE = sa.cE[j] != 0.0 || useF;
-    const bool useI = sa.cI[j] != 0.0 || useF;
-    b_stage += 4 * ((useE ? fE : 0.0) + ((useI && !(j == 0 && sa.fi0_from_y)) ? f64 : 0.0));
-  }
-  b_stage += (sa.FI_out ? 4 * f64 : 0.0) + (sa.FEc_out ? fE : 0.0) + (need_rhs ? 4 * fT : 0.0);
-  b_stage += fold ? 2 * 4 * f64 : 0.0;  // U and E
+  double b_stage = 4 * f64 + 4 * fT;                          // state read, stage value written
+  if (np > 0) b_stage += 4 * np * fE + (fresh_fe<T> ? 3 * fT : 0.0);  // F^E_j read (the newest's eta: T3 read, stored)
+  b_stage += (sa.FI_out ? 4 * f64 : 0.0) + (sa.FEc_out ? fE : 0.0);
   prof_begin(c);
-  if (!launch_stage_invz<T, TE>(c, sa, T1, need_rhs ? 1 : 0)) return PF_ERR_UNSUPPORTED_SIZE;
+  if (!launch_stage<T, TE>(c, sa, np, T3, T1)) return PF_ERR_UNSUPPORTED_SIZE;
   prof_end(c, KC_STAGE, b_stage);
-  if (need_rhs) {
-    const int acc = (sa.FEc_out != nullptr) ? 1 : 0;
-    bool ok = true;
-    prof_begin(c);
-    ok = ok && launch_colfft<T, +1, 1>(c, T1, T1, 4, (T)1);
-    prof_end(c, KC_YFFT, 8 * fT);
-    if constexpr (std::is_same<T, double>::value && std::is_same<TE, double>::value) {
-      if (c->inhom) {
-        if (!ok) return PF_ERR_UNSUPPORTED_SIZE;
-        return run_rhs_inhom(c, T1, FE_out, acc);
-      }
+  const int acc = (sa.FEc_out != nullptr) ? 1 : 0;
+  bool ok = true;
+  prof_begin(c);
+  ok = ok && launch_colfft<T, +1, 1>(c, T1, T1, 4, (T)1);
+  prof_end(c, KC_YFFT, 8 * fT);
+  if constexpr (std::is_same<T, double>::value && std::is_same<TE, double>::value) {
+    if (c->inhom) {
+      if (!ok) return PF_ERR_UNSUPPORTED_SIZE;
+      pf_status s = run_rhs_inhom(c, T1, FE, acc);
+      return s == PF_OK && fwd ? run_fwd_ac<T, TE>(c, FE) : s;
     }
-    prof_begin(c);
-    ok = ok && launch_xpass_theta<T>(c, T1, T3);
-    prof_end(c, KC_THETA, 6 * fT);
-    prof_begin(c);
-    ok = ok && launch_colfft<T, -1, 1>(c, T3, T3, 3, (T)1);
-    prof_end(c, KC_YFFT, 6 * fT);
-    prof_begin(c);
-    ok = ok && launch_zpass_elastic<T, TE>(c, T3, FE_out, acc);
-    prof_end(c, KC_ELASTIC, 6 * fT + (acc ? 2 : 1) * fE);
-    prof_begin(c);
-    ok = ok && launch_colfft<T, +1, 1>(c, T3, T3, 3, (T)1);
-    prof_end(c, KC_YFFT, 6 * fT);
-    prof_begin(c);
-    ok = ok && launch_xpass_drive<T>(c, T1, T3);
-    prof_end(c, KC_DRIVE, 10 * fT);
-    prof_begin(c);
-    ok = ok && launch_colfft<T, -1, 1>(c, T3, T3, 3, (T)1);
-    prof_end(c, KC_YFFT, 6 * fT);
-    prof_begin(c);
-    ok = ok && launch_zpass_fwd_ac<T, TE>(c, T3, FE_out);
-    prof_end(c, KC_ZFWD_AC, 3 * fT + 3 * fE);
-    if (!ok) return PF_ERR_UNSUPPORTED_SIZE;
   }
+  prof_begin(c);
+  ok = ok && launch_xpass_theta<T>(c, T1, T3);
+  prof_end(c, KC_THETA, 6 * fT);
+  prof_begin(c);
+  ok = ok && launch_colfft<T, -1, 1>(c, T3, T3, 3, (T)1);
+  prof_end(c, KC_YFFT, 6 * fT);
+  prof_begin(c);
+  ok = ok && launch_zpass_elastic<T, TE>(c, T3, FE, acc);
+  prof_end(c, KC_ELASTIC, 6 * fT + (acc ? 2 : 1) * fE);
+  prof_begin(c);
+  ok = ok && launch_colfft<T, +1, 1>(c, T3, T3, 3, (T)1);
+  prof_end(c, KC_YFFT, 6 * fT);
+  prof_begin(c);
+  ok = ok && launch_xpass_drive<T>(c, T1, T3);
+  prof_end(c, KC_DRIVE, 10 * fT);
+  prof_begin(c);
+  ok = ok && launch_colfft<T, -1, 1>(c, T3, T3, 3, (T)1);
+  prof_end(c, KC_YFFT, 6 * fT);
+  if (!ok) return PF_ERR_UNSUPPORTED_SIZE;
+  if (fwd) return run_fwd_ac<T, TE>(c, FE);
   if (hipGetLastError() != hipSuccess) return PF_ERR_HIP;
   return PF_OK;
 }
 
+// f^I and f^E at y_hat, F^E in the precision of the chain.
+template <typename T, typename TE>
+static pf_status run_rhs(pf_ctx* c, const void* y_hat, void* fI_hat, cx<TE>* FE) {
+  StepArgs<TE> sa;
+  std::memset(&sa, 0, sizeof(sa));
+  sa.y = (const cx<double>*)y_hat;
+  sa.FI_out = (cx<double>*)fI_hat;
+  sa.FEc_out = c->mk.fEa != 0.0 ? FE : nullptr;
+  return run_stage<T, TE>(c, sa, 0, FE, true);
+}
+
+// (value, flag) partial pairs are summed by one block up to this many, by 64
+// blocks and then one beyond (at 512^3 one block would take 0.3 ms).
+static constexpr int kReduceOne = 4096;
+static constexpr int kReduceBlocks = 64;
+
 template <typename T, typename TE>
 static pf_status stages_and_finalize(pf_ctx* c, double dt, int* n_rhs) {
   const ArkTable& tb = c->tab;
-  *n_rhs = 0;
-  for (int i = 0; i < tb.s; ++i) {
-    StageArgs<TE> sa;
-    std::memset(&sa, 0, sizeof(sa));
-    sa.y = c->y;
-    for (int j = 0; j < i; ++j) {
-      sa.FE[j] = (const cx<TE>*)c->FE[j];
-      sa.FI[j] = c->FI[j];
-      sa.cE[j] = (c->fe_need[j] ? dt * tb.AE[i][j] : 0.0);
-      sa.cI[j] = (c->fi_need[j] ? dt * tb.AI[i][j] : 0.0);
-    }
-    sa.nprev = i;
-    sa.gdt = dt * tb.AI[i][i];
-    sa.fi0_from_y = c->fi0_derived ? 1 : 0;
-    sa.FI_out = (c->fi_need[i] && !(i == 0 && c->fi0_derived)) ? c->FI[i] : nullptr;
-    if (c->fold_last && i == tb.s - 1) {
-      sa.FI_out = nullptr;  // this stage's F^I enters U and E only
-      sa.U_out = c->FI[i];
-      sa.E_out = c->FI[0];
-      for (int j = 0; j < i; ++j) {  // b^E = b^I here (fold_last); zero weights read nothing
-        sa.ub[j] = tb.bI[j];
-        sa.eb[j] = tb.bI[j] - tb.bt[j];
-      }
-      sa.ubs = tb.bI[i];
-      sa.ebs = tb.bI[i] - tb.bt[i];
-      sa.fdt = dt;
-    }
-    const bool need_rhs = c->fe_need[i];
-    sa.FEc_out = (need_rhs && c->mk.fEa != 0.0) ? (cx<TE>*)c->FE[i] : nullptr;
-    pf_status s = run_stage<T, TE>(c, sa, need_rhs, (cx<TE>*)c->FE[i]);
+  const cx<T>* T3 = (const cx<T>*)c->scratch + 4 * c->g.fs;
+  StepArgs<TE> sa;
+  std::memset(&sa, 0, sizeof(sa));
+  sa.y = c->y;
+  for (int j = 0; j < tb.s; ++j) sa.FE[j] = (cx<TE>*)c->FE[j];
+  fill_tab(tb, dt, c->at);
+  int nf = 0;  // stages with an explicit derivative: all, but the last of IMEX Euler
+  while (nf < tb.s && c->fe_need[nf]) ++nf;
+  *n_rhs = nf;
+  for (int i = 0; i < nf; ++i) {
+    sa.FEc_out = c->mk.fEa != 0.0 ? sa.FE[i] : nullptr;
+    pf_status s = run_stage<T, TE>(c, sa, i, sa.FE[i], !fresh_fe<T>);
     if (s != PF_OK) return s;
-    if (need_rhs) ++*n_rhs;
   }
-  FinArgs<TE> fa;
-  std::memset(&fa, 0, sizeof(fa));
-  fa.y = c->y;
-  fa.ynew = c->ynew;
-  for (int j = 0; j < tb.s; ++j) {
-    fa.FE[j] = (const cx<TE>*)c->FE[j];
-    fa.FI[j] = c->FI[j];
-    fa.bE[j] = c->fe_need[j] ? dt * tb.bE[j] : 0.0;
-    fa.bI[j] = c->fi_need[j] ? dt * tb.bI[j] : 0.0;
-    fa.dE[j] = (tb.has_emb && c->fe_need[j]) ? dt * (tb.bE[j] - tb.bt[j]) : 0.0;
-    fa.dI[j] = (tb.has_emb && c->fi_need[j]) ? dt * (tb.bI[j] - tb.bt[j]) : 0.0;
-  }
-  fa.s = tb.s;
-  fa.want_err = tb.has_emb;
-  fa.fi0_from_y = c->fi0_derived ? 1 : 0;
-  if (c->fold_last) {  // everything but the last stage's F^E is in U and E
-    const int l = tb.s - 1;
-    for (int j = 0; j < tb.s; ++j) fa.bE[j] = fa.bI[j] = fa.dE[j] = fa.dI[j] = 0.0;
-    fa.bE[l] = dt * tb.bE[l];
-    fa.dE[l] = dt * (tb.bE[l] - tb.bt[l]);
-    fa.fi0_from_y = 0;
-    fa.U = c->FI[l];
-    fa.E = c->FI[0];
-  }
-  fa.rtol = c->p.rtol;
-  fa.atol = c->p.atol;
-  fa.sc = 1.0 / std::sqrt((double)c->g.nx * c->g.ny * c->g.nz);
-  fa.partial = c->partial;
-  fa.err_out = (c->norm_real && tb.has_emb) ? c->FI[0] : nullptr;
-  // y read + ynew write (4 complex FP64 fields each)
-  double b_fin = 2.0 * 4 * c->g.nz * (double)c->g.ny * c->g.nxh * sizeof(cx<double>);
-  if (fa.U) b_fin += 2.0 * 4 * c->g.nz * (double)c->g.ny * c->g.nxh * sizeof(cx<double>);  // U and E
-  for (int j = 0; j < tb.s; ++j) {
-    const double nv = 4.0 * c->g.nz * (double)c->g.ny * c->g.nxh;
-    if ((fa.bI[j] != 0.0 || fa.dI[j] != 0.0) && !(j == 0 && fa.fi0_from_y)) b_fin += nv * sizeof(cx<double>);
-    if (fa.bE[j] != 0.0 || fa.dE[j] != 0.0) b_fin += nv * sizeof(cx<TE>);
-  }
+  sa.ynew = c->ynew;
+  sa.err_out = (c->norm_real && tb.has_emb) ? c->err : nullptr;
+  sa.rtol = c->p.rtol;
+  sa.atol = c->p.atol;
+  sa.sc = 1.0 / std::sqrt((double)c->g.nx * c->g.ny * c->g.nz);
+  const double nv = (double)c->g.nz * c->g.ny * c->g.nxh;
+  const double fT = nv * sizeof(cx<T>), fE = nv * sizeof(cx<TE>), f64 = nv * sizeof(cx<double>);
   prof_begin(c);
-  k_finalize<TE><<<dim3(c->nblk_red), dim3(256), 0, c->stream>>>(fa, c->g, c->mk);
-  k_reduce_pairs<<<dim3(1), dim3(256), 0, c->stream>>>(c->partial, c->nblk_red, c->red);
-  prof_end(c, KC_FINAL, b_fin);
+  const int nb = launch_final<T, TE>(c, sa, T3);
+  if (nb == 0) return PF_ERR_UNSUPPORTED_SIZE;
+  const double* part = c->partial;
+  int np = nb;
+  if (nb > kReduceOne) {
+    double* second = c->partial + 2 * (size_t)final_blocks_max(c->g);
+    k_reduce_pairs<<<dim3(kReduceBlocks), dim3(256), 0, c->stream>>>(part, np, second);
+    part = second;
+    np = kReduceBlocks;
+  }
+  k_reduce_pairs<<<dim3(1), dim3(256), 0, c->stream>>>(part, np, c->red);
+  // y and F^E read (the newest's order parameters from T3, in T), y_new written
+  prof_end(c, KC_FINAL, 8 * f64 + (4 * nf - 3) * fE + 3 * (fresh_fe<T> ? fT : fE) + (sa.err_out ? 4 * f64 : 0.0));
   if (hipGetLastError() != hipSuccess) return PF_ERR_HIP;
   return PF_OK;
 }
@@ -797,15 +638,6 @@ void ctx_setup(pf_ctx* c, const pf_params* p, hipStream_t stream) {
   c->tab = table_for(p->method);
   for (int i = 0; i < c->tab.s; ++i) {
     c->fe_need[i] = fe_needed(c->tab, i);
-    c->fi_need[i] = fi_needed(c->tab, i);
-  }
-  // explicit first stage: its value is the state, F^I_1 = L y is formed where used
-  c->fi0_derived = c->tab.AI[0][0] == 0.0 && c->fi_need[0];
-  {
-    const int l = c->tab.s - 1;
-    bool same_b = true;  // one weight set for the explicit and implicit parts
-    for (int j = 0; j < c->tab.s; ++j) same_b = same_b && c->tab.bE[j] == c->tab.bI[j];
-    c->fold_last = c->tab.has_emb && same_b && c->fi0_derived && l >= 1 && c->fe_need[l] && c->fi_need[l];
   }
   std::memset(&c->st, 0, sizeof(c->st));
   c->dt_next = p->dt0;
@@ -940,13 +772,13 @@ void pf_finalize(pf_ctx* c) {
   hipFree(c->y);
   hipFree(c->ynew);
   hipFree(c->ycopy);
+  hipFree(c->err);
   hipFree(c->E6);
   hipFree(c->R6);
   hipFree(c->LC6);
   hipFree(c->elmax);
   hipFree(c->el_part);
   for (int i = 0; i < 6; ++i) {
-    hipFree(c->FI[i]);
     hipFree(c->FE[i]);
   }
   hipFree(c->scratch);
@@ -1004,17 +836,17 @@ pf_status pf_init(const pf_params* p, void* stream, pf_ctx** out) {
   s = dalloc(c, (void**)&c->y, kbytes64);
   if (s == PF_OK) s = dalloc(c, (void**)&c->ynew, kbytes64);
   if (s == PF_OK && c->norm_real) s = dalloc(c, (void**)&c->ycopy, kbytes64);
+  if (s == PF_OK && c->norm_real) s = dalloc(c, (void**)&c->err, kbytes64);
   if (s == PF_OK && c->inhom) s = dalloc(c, (void**)&c->E6, sizeof(cx<double>) * 6 * (size_t)g.fs);
   if (s == PF_OK && c->inhom) s = dalloc(c, (void**)&c->R6, sizeof(double) * 6 * (size_t)g.nx * g.ny * g.nz);
   if (s == PF_OK && c->inhom) s = dalloc(c, (void**)&c->LC6, sizeof(double) * 6 * (size_t)g.nx * g.ny * g.nz);
   if (s == PF_OK && c->inhom) s = dalloc(c, (void**)&c->elmax, sizeof(double));
   if (s == PF_OK && c->inhom) s = dalloc(c, (void**)&c->el_part, sizeof(double) * (size_t)el_row_blocks(c));
-  for (int i = 0; i < c->tab.s && s == PF_OK; ++i) {
-    if (c->fi_need[i] || i == 0) s = dalloc(c, (void**)&c->FI[i], kbytes64);
-    if (s == PF_OK && (c->fe_need[i] || i == 0)) s = dalloc(c, &c->FE[i], fe_bytes);
-  }
+  for (int i = 0; i < c->tab.s && s == PF_OK; ++i)
+    if (c->fe_need[i] || i == 0) s = dalloc(c, &c->FE[i], fe_bytes);
   if (s == PF_OK) s = dalloc(c, &c->scratch, c->scratch_bytes);
-  if (s == PF_OK) s = dalloc(c, (void**)&c->partial, sizeof(double) * 4 * c->nblk_red);
+  if (s == PF_OK) s = dalloc(c, (void**)&c->partial, sizeof(double) * (size_t)std::max(
+                                       4 * c->nblk_red, 2 * (final_blocks_max(g) + kReduceBlocks)));
   if (s == PF_OK) s = dalloc(c, (void**)&c->red, sizeof(double) * 8);
   if (s == PF_OK && hipHostMalloc((void**)&c->host_red, sizeof(double) * 8, 0) != hipSuccess) s = PF_ERR_OOM;
   if (s == PF_OK) s = upload_twiddles(c, 0, g.nz);
@@ -1132,20 +964,10 @@ pf_status pf_rhs(pf_ctx* c, double t, const void* y_hat, void* fI_hat, void* fE_
   if (!c || !y_hat || !fI_hat || !fE_hat) return PF_ERR_ARG;
   pf_status s;
   if (!c->mixed) {
-    StageArgs<double> sa;
-    std::memset(&sa, 0, sizeof(sa));
-    sa.y = (const cx<double>*)y_hat;
-    sa.FI_out = (cx<double>*)fI_hat;
-    sa.FEc_out = c->mk.fEa != 0.0 ? (cx<double>*)fE_hat : nullptr;
-    s = run_stage<double, double>(c, sa, true, (cx<double>*)fE_hat);
+    s = run_rhs<double, double>(c, y_hat, fI_hat, (cx<double>*)fE_hat);
   } else {
-    StageArgs<float> sa;
-    std::memset(&sa, 0, sizeof(sa));
-    sa.y = (const cx<double>*)y_hat;
-    sa.FI_out = (cx<double>*)fI_hat;
     cx<float>* fe = (cx<float>*)c->FE[0];
-    sa.FEc_out = c->mk.fEa != 0.0 ? fe : nullptr;
-    s = run_stage<float, float>(c, sa, true, fe);
+    s = run_rhs<float, float>(c, y_hat, fI_hat, fe);
     if (s == PF_OK) {
       k_convert<float, double><<<dim3(1024), dim3(256), 0, c->stream>>>(fe, (cx<double>*)fE_hat, c->g, 4);
       if (hipGetLastError() != hipSuccess) s = PF_ERR_HIP;
@@ -1158,14 +980,14 @@ pf_status pf_rhs(pf_ctx* c, double t, const void* y_hat, void* fI_hat, void* fE_
 }
 
 // Real-space WRMS of the step's error estimate (norm_space = 1): the error
-// (stored by the finalize in FI[0]) and the previous state are transformed
+// (stored by the finalize) and the previous state are transformed
 // back to real space and weighted point by point; the sum of squares goes to
 // red[2].
 static pf_status wrms_real_space(pf_ctx* c) {
   const long long n = (long long)c->g.nx * c->g.ny * c->g.nz;
   double* re = (double*)c->scratch;
   double* ry = re + 4 * n;
-  pf_status s = inverse3d_fp64(c, c->FI[0], re, 4);
+  pf_status s = inverse3d_fp64(c, c->err, re, 4);
   if (s != PF_OK) return s;
   PF_HIP(hipMemcpyAsync(c->ycopy, c->y, sizeof(cx<double>) * 4 * c->g.fs, hipMemcpyDeviceToDevice, c->stream));
   s = inverse3d_fp64(c, c->ycopy, ry, 4);
@@ -1426,20 +1248,13 @@ template <typename T, typename TE>
 static pf_status autotune_impl(pf_ctx* c, int reps) {
   cx<T>* T1 = (cx<T>*)c->scratch;
   cx<T>* T3 = T1 + 4 * c->g.fs;
-  int npairs = 0;
-  while (npairs < 3 && c->FI[npairs] && c->FE[npairs]) ++npairs;
-  StageArgs<TE> sa;
+  int np = 0;  // the stage pass is timed over up to three previous stages
+  while (np < 3 && np < c->tab.s - 1 && c->FE[np]) ++np;
+  StepArgs<TE> sa;
   std::memset(&sa, 0, sizeof(sa));
   sa.y = c->y;
-  for (int j = 0; j < npairs; ++j) {
-    sa.FE[j] = (const cx<TE>*)c->FE[j];
-    sa.FI[j] = c->FI[j];
-    sa.cE[j] = 1e-3;
-    sa.cI[j] = 1e-3;
-  }
-  sa.nprev = npairs;
-  sa.gdt = 1e-3;
-  sa.FI_out = c->FI[0];
+  for (int j = 0; j < np; ++j) sa.FE[j] = (cx<TE>*)c->FE[j];
+  fill_tab(c->tab, 1e-3, c->at);
   hipEvent_t e0, e1;
   PF_HIP(hipEventCreate(&e0));
   PF_HIP(hipEventCreate(&e1));
@@ -1453,7 +1268,7 @@ static pf_status autotune_impl(pf_ctx* c, int reps) {
       auto run = [&]() {
         switch (k) {
           case CK_FFT: launch_colfft<T, -1, 1>(c, T1, T1, 4, (T)1); break;
-          case CK_STAGE: launch_stage_invz<T, TE>(c, sa, T1, 1); break;
+          case CK_STAGE: launch_stage<T, TE>(c, sa, np, T3, T1); break;
           case CK_ELASTIC: launch_zpass_elastic<T, TE>(c, T3, (cx<TE>*)c->FE[0], 0); break;
           default: launch_zpass_fwd_ac<T, TE>(c, T3, (cx<TE>*)c->FE[0]); break;
         }
