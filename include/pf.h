@@ -419,7 +419,8 @@ pf_status pf_fno_apply(pf_fno* f, const double* state, double* next);
  * its storage width: BF16 activations and weights, FP32 outputs, gradients
  * and spectra, FP64 states) and flops (2 per multiply-add) to its kind.
  * Kinds, in this order (PF_FNO_KINDS): 0 truncated-DFT GEMMs (k_lm_gemm),
- * 1 channel-mixing GEMMs (k_cm_gemm), 2 weight-gradient reductions
+ * 1 channel-mixing GEMMs (k_cm_gemm; the fused
+ * projection k_proj as its products), 2 weight-gradient reductions
  * (k_wgrad_mfma), 3 their partial sums (k_sum_partials), 4 per-mode mixing
  * (k_mix_*), 5 GELU backward (k_gelu_bwd), 6 elementwise (input packing,
  * loss, Adam, surrogate update, mass reset).  bytes / flops / launches
@@ -434,7 +435,7 @@ pf_status pf_fno_work(pf_fno* f, int32_t enable, double* bytes, double* flops, i
  * [batch][cin][n^3]; nexts may equal states): one network pass whose GEMMs
  * run over every sample's points and lines together, so each sample's result
  * is bit-identical to pf_fno_apply's.  The batched activations (about
- * 0.93 GB per 128^3 sample at width 32, hidden 128) are allocated on the
+ * 0.4 GB per 128^3 sample at width 32) are allocated on the
  * first call and grown when a larger batch comes.  Errors: PF_ERR_ARG (batch
  * < 1, NULL, cin != cout), PF_ERR_OOM, PF_ERR_HIP. */
 pf_status pf_fno_apply_batch(pf_fno* f, const double* states, double* nexts, int32_t batch);

@@ -25,6 +25,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/pf.h"
@@ -36,7 +37,11 @@ typedef unsigned short u16;
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 // gfx950's 32 x 32 x 16 BF16 MFMA (FP32 accumulate).  Lane l holds row l % 32
 // of A and column l % 32 of B at k = 8 (l / 32) .. 8 (l / 32) + 7; the
@@ -47,6 +52,62 @@ __device__ inline f32x16 mfma16(bf16x4 a_lo, bf16x4 a_hi, bf16x4 b_lo, bf16x4 b_
   const s16x8 b = {b_lo[0], b_lo[1], b_lo[2], b_lo[3], b_hi[0], b_hi[1], b_hi[2], b_hi[3]};
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc,
                                                  0, 0, 0);
+}
+__device__ inline f32x16 mfma32(u32x4 a, u32x4 b, f32x16 acc) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc,
+                                                 0, 0, 0);
+}
+// 16 x 16 x 32: lane l holds row / column l % 16 at k = 8 (l / 16) ..; element
+// i of the accumulator: row 4 (l / 16) + i, column l % 16.
+__device__ inline f32x4 mfma16x16(u32x4 a, u32x4 b, f32x4 acc) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc,
+                                                 0, 0, 0);
+}
+__device__ inline f32x16 zero16() {
+  f32x16 z;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) z[i] = 0.0f;
+  return z;
+}
+
+// two values to BF16, round to nearest even (v_cvt_pk_bf16_f32)
+__device__ inline unsigned pack2(float a, float b) {
+  const bf16x2 v = {(__bf16)a, (__bf16)b};
+  return __builtin_bit_cast(unsigned, v);
+}
+
+// A 32 x 32 accumulator tile as BF16 operands of the next MFMA: lane l keeps
+// its column l % 32, with the tile's rows as that operand's k (op[s]: rows
+// 16 s .. 16 s + 15).  The two half-waves exchange the row groups they hold.
+__device__ inline void to_operand(const f32x16& v, u32x4 (&op)[2]) {
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const unsigned d0 = pack2(v[8 * s], v[8 * s + 1]), d1 = pack2(v[8 * s + 2], v[8 * s + 3]);
+    const unsigned e0 = pack2(v[8 * s + 4], v[8 * s + 5]), e1 = pack2(v[8 * s + 6], v[8 * s + 7]);
+    const auto p = __builtin_amdgcn_permlane32_swap(d0, e0, false, false);
+    const auto q = __builtin_amdgcn_permlane32_swap(d1, e1, false, false);
+    op[s] = u32x4{p[0], q[0], p[1], q[1]};
+  }
+}
+
+// The identity's rows k = 16 s .. 16 s + 15 as a B operand: op x identity puts
+// an operand (lane = row) into the accumulator with lane = k, i.e. transposes
+// it, exactly (BF16 values times one).
+__device__ inline u32x4 identity_operand(int s, int lr, int lg) {
+  u32x4 w;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int k = 16 * s + 8 * lg + 2 * j;
+    w[j] = (k == lr ? 0x3F80u : 0u) | (k + 1 == lr ? 0x3F800000u : 0u);
+  }
+  return w;
+}
+// op (lane = row, k) -> operands with lane = k and k = row; t: the same in FP32
+__device__ inline f32x16 transpose_operand(const u32x4 (&op)[2], const u32x4 (&id)[2], u32x4 (&out)[2]) {
+  f32x16 t = mfma32(op[0], id[0], zero16());
+  t = mfma32(op[1], id[1], t);
+  to_operand(t, out);
+  return t;
 }
 
 __host__ __device__ inline u16 f2bf(float f) {
@@ -82,82 +143,405 @@ struct LineTerm {
   int ldx = 0;
 };
 
+// Eight values of a row at k = kb .. kb + 7, zero beyond K (K % 4 == 0); v16:
+// the row is 16-byte aligned and K % 8 == 0.
+__device__ inline u32x4 ld8(const u16* row, int kb, int K, bool v16) {
+  u32x4 r = {0, 0, 0, 0};
+  if (v16) {
+    if (kb < K) r = *reinterpret_cast<const u32x4*>(row + kb);
+  } else {
+    if (kb < K) {
+      const u32x2 a = *reinterpret_cast<const u32x2*>(row + kb);
+      r[0] = a[0], r[1] = a[1];
+    }
+    if (kb + 4 < K) {
+      const u32x2 a = *reinterpret_cast<const u32x2*>(row + kb + 4);
+      r[2] = a[0], r[3] = a[1];
+    }
+  }
+  return r;
+}
+// the same for a store of n values starting at column c of the row
+__device__ inline void st8(u16* row, int c, int N, bool v16, u32x4 v) {
+  if (v16) {
+    if (c < N) *reinterpret_cast<u32x4*>(row + c) = v;
+  } else {
+    if (c < N) *reinterpret_cast<u32x2*>(row + c) = u32x2{v[0], v[1]};
+    if (c + 4 < N) *reinterpret_cast<u32x2*>(row + c + 4) = u32x2{v[2], v[3]};
+  }
+}
+
 // ---- channel-mixing GEMM: Out[p][n] = epi(sum_k In[p][k] Bt[n][k] [+ line term]) ----
 // K % 4 == 0 (zero beyond K), P % 128 == 0, N <= 32 * NT.  Epilogue: + bias[n] + resid[p][n],
-// times GELU'(gpre[p][n]) (a data gradient through the activation), stores any
-// of: f32 result, bf16 pre-activation, bf16 GELU(pre).
+// times GELU'(gpre[p][n]) (a data gradient through the activation; GELU' from a
+// table over the BF16 values), stores any of: f32 result, bf16 pre-activation,
+// bf16 GELU(pre).
+// The weights are the A operand and the points the B operand, so a lane holds
+// one point and reads and writes its channels 16 bytes at a time (with the
+// roles exchanged every store was two bytes wide).
 template <int NT>
 __global__ void __launch_bounds__(256)
 k_cm_gemm(const u16* __restrict__ In, int ldin, int K, const u16* __restrict__ Bt, int N,
           const float* __restrict__ bias, const float* __restrict__ resid, int ldres, float* __restrict__ outf,
           u16* __restrict__ outpre, u16* __restrict__ outact, int ldout, int accumulate, LineTerm lt,
-          const u16* __restrict__ gpre) {
+          const u16* __restrict__ gpre, const float* __restrict__ gtab) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const long long p0 = ((long long)blockIdx.x * 4 + wave) * 32;
   const int lr = lane & 31, lg = lane >> 5;
   f32x16 acc[NT];
 #pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[t][i] = 0.0f;
+  for (int t = 0; t < NT; ++t) acc[t] = zero16();
+  const bool in16 = K % 8 == 0 && ldin % 8 == 0, k16 = K % 8 == 0;
   for (int kk = 0; kk < K; kk += 16) {
-    // K % 4 == 0: each 4-wide half of a lane's 8 values is all in or all out
     const int kb = kk + lg * 8;
-    const bool in0 = kb < K, in1 = kb + 4 < K;
-    bf16x4 a0 = {0, 0, 0, 0}, a1 = {0, 0, 0, 0};
-    if (in0) a0 = ld4(In + (p0 + lr) * ldin + kb);
-    if (in1) a1 = ld4(In + (p0 + lr) * ldin + kb + 4);
+    const u32x4 b = ld8(In + (p0 + lr) * ldin, kb, K, in16);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const int n = t * 32 + lr;
-      bf16x4 b0 = {0, 0, 0, 0}, b1 = {0, 0, 0, 0};
-      if (n < N && in0) b0 = ld4(Bt + (long long)n * K + kb);
-      if (n < N && in1) b1 = ld4(Bt + (long long)n * K + kb + 4);
-      acc[t] = mfma16(a0, a1, b0, b1, acc[t]);
+      u32x4 a = {0, 0, 0, 0};
+      if (n < N) a = ld8(Bt + (long long)n * K, kb, K, k16);
+      acc[t] = mfma32(a, b, acc[t]);
     }
   }
   if (lt.G) {
     const long long line = p0 / lt.R;
     const int x = (int)(p0 % lt.R) + lr;
     const u16* Xb = lt.X + line * lt.xbs;
+    const bool g16 = lt.K % 8 == 0;
     for (int kk = 0; kk < lt.K; kk += 16) {
       const int kb = kk + lg * 8;
-      const bool in0 = kb < lt.K, in1 = kb + 4 < lt.K;
-      bf16x4 a0 = {0, 0, 0, 0}, a1 = {0, 0, 0, 0};
-      if (in0) a0 = ld4(lt.G + (long long)x * lt.K + kb);
-      if (in1) a1 = ld4(lt.G + (long long)x * lt.K + kb + 4);
+      const u32x4 b = ld8(lt.G + (long long)x * lt.K, kb, lt.K, g16);
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         const int n = t * 32 + lr;
-        bf16x4 b0 = {0, 0, 0, 0}, b1 = {0, 0, 0, 0};
-        if (n < N && in0) {
+        u32x4 a = {0, 0, 0, 0};
+        if (n < N) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) b0[j] = (short)Xb[(long long)(kb + j) * lt.ldx + n];
+          for (int j = 0; j < 8; ++j)
+            if (kb + j < lt.K) a[j >> 1] |= (unsigned)Xb[(long long)(kb + j) * lt.ldx + n] << (16 * (j & 1));
         }
-        if (n < N && in1) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) b1[j] = (short)Xb[(long long)(kb + 4 + j) * lt.ldx + n];
-        }
-        acc[t] = mfma16(a0, a1, b0, b1, acc[t]);
+        acc[t] = mfma32(a, b, acc[t]);
       }
     }
   }
+  const long long p = p0 + lr;
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    const int col = t * 32 + lr;
-    if (col >= N) continue;
-    const float bb = bias ? bias[col] : 0.0f;
+    f32x16 v = acc[t];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const long long row = p0 + 8 * (i >> 2) + 4 * lg + (i & 3);
-      float v = acc[t][i] + bb;
-      if (resid) v += resid[row * ldres + col];
-      const long long o = row * ldout + col;
-      if (gpre) v *= gelu_g(bf2f(gpre[o]));
-      if (outf) outf[o] = accumulate ? outf[o] + v : v;
-      if (outpre) outpre[o] = f2bf(v);
-      if (outact) outact[o] = f2bf(gelu_f(v));
+    for (int q = 0; q < 4; ++q) {
+      const int c = t * 32 + 8 * q + 4 * lg;  // this lane's channels c .. c + 3
+      if (c >= N) continue;
+      if (N % 4 == 0) {
+        const f32x4 bb = bias ? *reinterpret_cast<const f32x4*>(bias + c) : f32x4{0.f, 0.f, 0.f, 0.f};
+        f32x4 rr = {0.f, 0.f, 0.f, 0.f};
+        if (resid) rr = *reinterpret_cast<const f32x4*>(resid + p * ldres + c);
+        u32x2 gp = {0, 0};
+        if (gpre) gp = *reinterpret_cast<const u32x2*>(gpre + p * ldout + c);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          float r = v[4 * q + j] + bb[j];
+          if (resid) r += rr[j];
+          if (gpre) r *= gtab[(gp[j >> 1] >> (16 * (j & 1))) & 0xffffu];
+          v[4 * q + j] = r;
+        }
+        if (outf) {
+          f32x4* o = reinterpret_cast<f32x4*>(outf + p * ldout + c);
+          f32x4 r = {v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+          if (accumulate) r = *o + r;
+          *o = r;
+        }
+      } else {  // f32 results of a channel count that 4 does not divide
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (c + j >= N) continue;
+          float r = v[4 * q + j] + (bias ? bias[c + j] : 0.0f);
+          if (resid) r += resid[p * ldres + c + j];
+          const long long o = p * ldout + c + j;
+          if (outf) outf[o] = accumulate ? outf[o] + r : r;
+        }
+      }
     }
+    const bool o16 = N % 8 == 0 && ldout % 8 == 0;
+    u32x4 op[2];
+    if (outpre) {
+      to_operand(v, op);
+#pragma unroll
+      for (int s = 0; s < 2; ++s) st8(outpre + p * ldout, t * 32 + 16 * s + 8 * lg, N, o16, op[s]);
+    }
+    if (outact) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) v[i] = gelu_f(v[i]);
+      to_operand(v, op);
+#pragma unroll
+      for (int s = 0; s < 2; ++s) st8(outact + p * ldout, t * 32 + 16 * s + 8 * lg, N, o16, op[s]);
+    }
+  }
+}
+
+// ---- projection: out = GELU(v P1 + c1) P2 + c2 (w <= 32, h <= 32 HT, co <= 8) ----
+// One pass over the points from v_L to the network's output; the hidden layer
+// stays in registers.  At 128^3, h = 128 the separate GEMMs moved 1.6 GB per
+// sample through the hidden layer (0.92 ms for two samples).  TRAIN goes on to the loss against
+// (y - x) / scale, the data gradient d v_L (dpre) and the gradients of P1, c1, P2
+// and c2 (one partial set per block: part1 rows k = 0 .. w, part2 rows
+// 0 .. h, the last row the bias's): with the hidden layer's activations and
+// gradients in HBM that took 4.6 GB and 3.9 ms per sample.  What bounds it
+// now is the exact GELU's erf: 2.7e8 of them per sample at 128^3.
+// A wave takes 32 points at a time; points are the B operand throughout, so
+// every product's accumulator holds one point per lane, and the next product
+// takes it as an operand (to_operand).  The weight gradients contract over
+// points: their operands are transposed through an identity product.
+// P % 32 == 0.  The sums over channels run in the order of k_cm_gemm's.
+struct ProjArgs {
+  const u16* v;        // [P][w]
+  const u16 *P1T, *P2T, *P1, *P2;  // [h][w], [co][h], [w][h], [h][8]
+  const float *c1, *c2;
+  long long P;
+  int w, h, co;
+  float* outf;         // !TRAIN: [P][co]
+  const float *x, *y;  // TRAIN: planar [..][P]
+  const float* scale;
+  float inv;           // 2 / (P co)
+  const float* gtab;
+  u16* dpre;           // [P][w]
+  float *part1, *part2;
+  double* dpart;
+};
+
+template <bool TRAIN, int HT>
+__global__ void __launch_bounds__(256, 2) k_proj(ProjArgs pa) {
+  constexpr int H = 32 * HT, LH = H + 8;
+  __shared__ __attribute__((aligned(16))) u16 sP1T[H * 40];
+  __shared__ __attribute__((aligned(16))) u16 sP2T[8 * LH];
+  __shared__ __attribute__((aligned(16))) u16 sP1[TRAIN ? 32 * LH : 8];
+  __shared__ __attribute__((aligned(16))) u16 sP2[TRAIN ? H * 8 : 8];
+  __shared__ __attribute__((aligned(16))) float sc1[H];
+  // TRAIN: the hidden activations' operands (each lane's own slots: 32 registers
+  // fewer, which keeps two waves per SIMD), and the block sums at the end
+  __shared__ u32x4 shop[TRAIN ? 2 * HT * 256 : 1];
+  float* red = reinterpret_cast<float*>(shop);
+  const int w = pa.w, h = pa.h, co = pa.co;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lr = lane & 31, lg = lane >> 5;
+  for (int e = tid; e < H * 40; e += 256) {
+    const int r = e / 40, k = e % 40;
+    sP1T[e] = (r < h && k < w) ? pa.P1T[r * w + k] : (u16)0;
+  }
+  for (int e = tid; e < 8 * LH; e += 256) {
+    const int r = e / LH, k = e % LH;
+    sP2T[e] = (r < co && k < h) ? pa.P2T[r * h + k] : (u16)0;
+  }
+  for (int e = tid; e < H; e += 256) sc1[e] = e < h ? pa.c1[e] : 0.0f;
+  if constexpr (TRAIN) {
+    for (int e = tid; e < 32 * LH; e += 256) {
+      const int r = e / LH, k = e % LH;
+      sP1[e] = (r < w && k < h) ? pa.P1[r * h + k] : (u16)0;
+    }
+    for (int e = tid; e < H * 8; e += 256) sP2[e] = e < h * 8 ? pa.P2[e] : (u16)0;
+  }
+  __syncthreads();
+  float c2[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) c2[j] = 4 * lg + j < co ? pa.c2[4 * lg + j] : 0.0f;
+  const bool v16 = w % 8 == 0;
+  const long long ntile = pa.P / 32;
+  u32x4 id[2];
+  f32x16 g1[TRAIN ? HT : 1];
+  f32x4 g2[TRAIN ? 2 * HT : 1];
+  float b1[TRAIN ? HT : 1], b2 = 0.0f, scl[4];
+  double loss = 0.0;
+  if constexpr (TRAIN) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) id[s] = identity_operand(s, lr, lg);
+#pragma unroll
+    for (int t = 0; t < HT; ++t) g1[t] = zero16(), b1[t] = 0.0f;
+#pragma unroll
+    for (int t = 0; t < 2 * HT; ++t) g2[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) scl[j] = 4 * lg + j < co ? pa.scale[4 * lg + j] : 1.0f;
+  }
+  // pre-activations of hidden channels 32 t .. 32 t + 31 at this lane's point
+  auto hidden = [&](int t, const u32x4(&vop)[2]) {
+    f32x16 a = zero16();
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      if (16 * s < w) a = mfma32(*reinterpret_cast<const u32x4*>(sP1T + (32 * t + lr) * 40 + 16 * s + 8 * lg), vop[s], a);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 bb = *reinterpret_cast<const f32x4*>(sc1 + 32 * t + 8 * q + 4 * lg);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a[4 * q + j] = a[4 * q + j] + bb[j];
+    }
+    return a;
+  };
+  for (long long tile = (long long)blockIdx.x * 4 + wave; tile < ntile; tile += (long long)gridDim.x * 4) {
+    const long long p = tile * 32 + lr;
+    u32x4 vop[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) vop[s] = ld8(pa.v + p * w, 16 * s + 8 * lg, w, v16);
+    float xv[4], yv[4];
+    if constexpr (TRAIN) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int c = 4 * lg + j;
+        xv[j] = c < co ? pa.x[c * pa.P + p] : 0.0f;
+        yv[j] = c < co ? pa.y[c * pa.P + p] : 0.0f;
+      }
+    }
+    f32x16 o = zero16();
+#pragma unroll
+    for (int t = 0; t < HT; ++t) {
+      f32x16 a = hidden(t, vop);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        a[i] = gelu_f(a[i]);
+        if (TRAIN && i % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // four erfs in flight: registers
+      }
+      u32x4 hop[2];
+      to_operand(a, hop);
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        if constexpr (TRAIN) shop[(2 * t + s) * 256 + tid] = hop[s];
+        u32x4 q = {0, 0, 0, 0};
+        if (lr < 8) q = *reinterpret_cast<const u32x4*>(sP2T + lr * LH + 32 * t + 16 * s + 8 * lg);
+        o = mfma32(q, hop[s], o);
+      }
+      __builtin_amdgcn_sched_barrier(0);  // one tile at a time: registers
+    }
+    if constexpr (!TRAIN) {
+      float* of = pa.outf + p * co + 4 * lg;
+      if (co % 4 == 0) {
+        if (4 * lg < co)
+          *reinterpret_cast<f32x4*>(of) = f32x4{o[0] + c2[0], o[1] + c2[1], o[2] + c2[2], o[3] + c2[3]};
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (4 * lg + j < co) of[j] = o[j] + c2[j];
+      }
+    } else {
+      float g[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        g[j] = 0.0f;
+        if (4 * lg + j < co) {
+          const float tgt = (yv[j] - xv[j]) / scl[j];
+          const float d = (o[j] + c2[j]) - tgt;
+          loss += (double)d * d;
+          g[j] = d * pa.inv;
+        }
+      }
+      // output gradients as an operand (lane = point, k = output channel < 8)
+      const auto e0 = __builtin_amdgcn_permlane32_swap(pack2(g[0], g[1]), 0u, false, false);
+      const auto e1 = __builtin_amdgcn_permlane32_swap(pack2(g[2], g[3]), 0u, false, false);
+      const u32x4 dop = {e0[0], e1[0], e0[1], e1[1]};
+      u32x4 vT[2], dT[2];
+      transpose_operand(vop, id, vT);
+      u32x4 d16;  // lane % 16 = output channel, k = the 32 points in permlane16 order
+      {
+        const f32x16 t = mfma32(dop, id[0], zero16());
+        to_operand(t, dT);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) b2 += t[i];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) d16[j] = __builtin_amdgcn_permlane16_swap(dT[0][j], dT[1][j], false, false)[0];
+      }
+      f32x16 dv = zero16();
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < HT; ++t) {
+        u32x4 q = {0, 0, 0, 0};
+        if (lg == 0) q = *reinterpret_cast<const u32x4*>(sP2 + (32 * t + lr) * 8);
+        f32x16 dh = mfma32(q, dop, zero16());
+        const f32x16 a = hidden(t, vop);
+#pragma unroll
+        for (int i = 0; i < 16; i += 2) {
+          const unsigned hb = pack2(a[i], a[i + 1]);
+          dh[i] *= pa.gtab[hb & 0xffffu];
+          dh[i + 1] *= pa.gtab[hb >> 16];
+          if (i % 8 == 6) __builtin_amdgcn_sched_barrier(0);
+        }
+        u32x4 dhop[2], tr[2];
+        to_operand(dh, dhop);
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+          dv = mfma32(*reinterpret_cast<const u32x4*>(sP1 + lr * LH + 32 * t + 16 * s + 8 * lg), dhop[s], dv);
+        __builtin_amdgcn_sched_barrier(0);
+        const f32x16 dt = transpose_operand(dhop, id, tr);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) b1[t] += dt[i];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) g1[t] = mfma32(vT[s], tr[s], g1[t]);
+        __builtin_amdgcn_sched_barrier(0);
+        dhop[0] = shop[2 * t * 256 + tid];
+        dhop[1] = shop[(2 * t + 1) * 256 + tid];
+        transpose_operand(dhop, id, tr);
+        u32x4 h0, h1;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const auto z = __builtin_amdgcn_permlane16_swap(tr[0][j], tr[1][j], false, false);
+          h0[j] = z[0];
+          h1[j] = z[1];
+        }
+        g2[2 * t] = mfma16x16(d16, h0, g2[2 * t]);
+        g2[2 * t + 1] = mfma16x16(d16, h1, g2[2 * t + 1]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      u32x4 op[2];
+      to_operand(dv, op);
+#pragma unroll
+      for (int s = 0; s < 2; ++s) st8(pa.dpre + p * w, 16 * s + 8 * lg, w, v16, op[s]);
+    }
+  }
+  if constexpr (TRAIN) {
+    // the four waves' sums, tile by tile, into this block's partial sets
+    float* d1 = pa.part1 + (long long)blockIdx.x * (w + 1) * h;
+    float* d2 = pa.part2 + (long long)blockIdx.x * (h + 1) * co;
+#pragma unroll
+    for (int t = 0; t < HT; ++t) {
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 16; ++i) red[wave * 1024 + (8 * (i >> 2) + 4 * lg + (i & 3)) * 32 + lr] = g1[t][i];
+      __syncthreads();
+      for (int e = tid; e < 1024; e += 256) {
+        const int k = e >> 5, n = 32 * t + (e & 31);
+        if (k < w && n < h) d1[k * h + n] = (red[e] + red[1024 + e]) + (red[2048 + e] + red[3072 + e]);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < 2 * HT; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int c = 4 * (lane >> 4) + i;  // output channel
+        if (c < 8) red[wave * 1024 + c * H + 16 * t + (lane & 15)] = g2[t][i];
+      }
+    __syncthreads();
+    for (int e = tid; e < 8 * H; e += 256) {
+      const int c = e / H, k = e % H;
+      if (c < co && k < h) d2[k * co + c] = (red[e] + red[1024 + e]) + (red[2048 + e] + red[3072 + e]);
+    }
+    __syncthreads();
+    // bias rows: the two half-waves hold different points of a channel
+#pragma unroll
+    for (int t = 0; t < HT; ++t) red[wave * 256 + lg * 128 + 32 * t + lr] = b1[t];
+    red[1024 + wave * 64 + lane] = b2;
+    __syncthreads();
+    for (int e = tid; e < h; e += 256) {
+      float s = 0.0f;
+      for (int k = 0; k < 8; ++k) s += red[128 * k + e];
+      d1[w * h + e] = s;
+    }
+    if (tid < co) {
+      float s = 0.0f;
+      for (int k = 0; k < 8; ++k) s += red[1024 + 32 * k + tid];
+      d2[h * co + tid] = s;
+    }
+    for (int q = 32; q > 0; q >>= 1) loss += __shfl_xor(loss, q, 64);
+    __syncthreads();
+    double* rl = reinterpret_cast<double*>(red);
+    if (lane == 0) rl[wave] = loss;
+    __syncthreads();
+    if (tid == 0) pa.dpart[blockIdx.x] = (rl[0] + rl[1]) + (rl[2] + rl[3]);
   }
 }
 
@@ -289,139 +673,135 @@ k_mix_bwd_w(const float* __restrict__ S, const float* __restrict__ dT, float* __
 }
 
 // ---- weight gradients on MFMA: G[k][n] += sum_p A[p][k] D[p][n], gb[n] += sum_p D[p][n] ----
-// The reduction runs over points, which are the slow index of both operands,
-// so each block stages WG_PTS points of A (bf16) and D (f32, rounded to bf16)
-// transposed into LDS ([channel][point], padded rows) and every wave feeds
-// 32 of those points to the 32 x 32 x 16 MFMA for up to four 32 x 32
-// output tiles [t0, t0 + 4) of the ceil(K/32) x ceil(N/32) tile grid.  The
-// four waves' tiles are summed in LDS and each block writes one partial set
+// The reduction runs over points, the slow index of both operands.  A wave
+// reads 32 points' channels 16 bytes per lane, transposes them in registers
+// (an identity product, transpose_operand) and feeds them to the MFMA as
+// operands over k = points, for the KT x NT output tiles at (k0, n0); the next
+// 32 points are loaded meanwhile.  Each block writes one partial set
 // part[block * KN + k * N + n] (KN = (K + 1) * N; row k = K holds the bias
-// sums, written when t0 == 0); k_sum_partials adds the sets.  Requires lda % 4 == 0, K <= lda,
-// channels K .. 4 ceil(K/4) of A zero, K, N <= 128, chunk % WG_PTS == 0.
-constexpr int WG_PTS = 128;
-constexpr int WG_LD = WG_PTS + 4;  // bf16 row pitch: 264 B rows keep the 8-byte MFMA reads spread over banks
-
+// sums, written with k0 == 0); k_sum_partials adds the sets.  Streaming: at
+// 128^3 a 32 x 32 gradient reads 268 MB.  lda, ldd % 4 == 0 and cover K, N
+// rounded up to 4; P % 32 == 0.
+template <int KT, int NT>
 __global__ void __launch_bounds__(256)
-k_wgrad_mfma(const u16* __restrict__ A, int lda, int K, const float* __restrict__ D, int ldd, int N, long long P,
-             int chunk, int t0, float* __restrict__ part) {
-  // one buffer: the staged operands LA [k][p] and LD [n][p], reused at the end
-  // for the cross-wave sum of the partial tiles (4 waves x 4 tiles x 1024 floats)
-  __shared__ __attribute__((aligned(16))) u16 smem[2 * 128 * WG_LD];
-  u16* LA = smem;
-  u16* LD = smem + 128 * WG_LD;
+k_wgrad_mfma(const u16* __restrict__ A, int lda, int K, const u16* __restrict__ D, int ldd, int N, long long P,
+             int k0, int n0, float* __restrict__ part) {
+  __shared__ float red[4 * 1024];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lr = lane & 31, lg = lane >> 5;
-  const int Nt = (N + 31) / 32;
-  const int ntiles = min(4, ((K + 31) / 32) * Nt - t0);
-  const int KN = (K + 1) * N;
-  const int Kq = (K + 3) / 4;  // 4-channel groups of A staged per point
-  for (int e = tid; e < 128 * WG_LD; e += 256) LA[e] = 0, LD[e] = 0;
-  f32x16 acc[4];
+  const bool a16 = lda % 8 == 0 && K % 8 == 0, d16 = ldd % 8 == 0 && N % 8 == 0;
+  const long long ntile = P / 32, step = (long long)gridDim.x * 4;
+  u32x4 id[2];
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
+  for (int s = 0; s < 2; ++s) id[s] = identity_operand(s, lr, lg);
+  f32x16 acc[KT][NT];
+  float bs[NT];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[t][i] = 0.0f;
-  float bsum = 0.f;  // bias sum of channel n = tid (tid < N)
-  const long long pb = (long long)blockIdx.x * chunk;
-  const long long pe = pb + chunk < P ? pb + chunk : P;
-  for (long long p0 = pb; p0 < pe; p0 += WG_PTS) {
-    __syncthreads();
-    for (int e = tid; e < WG_PTS * Kq; e += 256) {
-      const int pp = e / Kq, kg = e % Kq;
-      const bf16x4 v = ld4(A + (p0 + pp) * lda + 4 * kg);
+  for (int i = 0; i < KT; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) LA[(4 * kg + j) * WG_LD + pp] = (u16)v[j];
+    for (int j = 0; j < NT; ++j) acc[i][j] = zero16();
+#pragma unroll
+  for (int j = 0; j < NT; ++j) bs[j] = 0.0f;
+  u32x4 an[KT][2], dn[NT][2];
+  auto load = [&](long long tile) {
+    const long long p = tile * 32 + lr;
+#pragma unroll
+    for (int i = 0; i < KT; ++i)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) an[i][s] = ld8(A + p * lda, k0 + 32 * i + 16 * s + 8 * lg, K, a16);
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) dn[j][s] = ld8(D + p * ldd, n0 + 32 * j + 16 * s + 8 * lg, N, d16);
+  };
+  long long tile = (long long)blockIdx.x * 4 + wave;
+  if (tile < ntile) load(tile);
+  for (; tile < ntile; tile += step) {
+    u32x4 a[KT][2], d[NT][2], aT[KT][2], dT[2];
+#pragma unroll
+    for (int i = 0; i < KT; ++i) a[i][0] = an[i][0], a[i][1] = an[i][1];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) d[j][0] = dn[j][0], d[j][1] = dn[j][1];
+    if (tile + step < ntile) load(tile + step);
+#pragma unroll
+    for (int i = 0; i < KT; ++i) transpose_operand(a[i], id, aT[i]);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const f32x16 t = transpose_operand(d[j], id, dT);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) bs[j] += t[e];
+#pragma unroll
+      for (int i = 0; i < KT; ++i)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) acc[i][j] = mfma32(aT[i][s], dT[s], acc[i][j]);
     }
-    for (int e = tid; e < WG_PTS * N; e += 256) {
-      const int pp = e / N, nn = e % N;
-      LD[nn * WG_LD + pp] = f2bf(D[(p0 + pp) * ldd + nn]);
-    }
-    __syncthreads();
-    if (tid < N) {
-      float sacc = 0.f;
-      for (int pp = 0; pp < WG_PTS; pp += 4) {
-        const bf16x4 v = *reinterpret_cast<const bf16x4*>(LD + tid * WG_LD + pp);
-        sacc += (bf2f((u16)v[0]) + bf2f((u16)v[1])) + (bf2f((u16)v[2]) + bf2f((u16)v[3]));
+  }
+  float* dst = part + (long long)blockIdx.x * (K + 1) * N;
+#pragma unroll
+  for (int i = 0; i < KT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < 16; ++e) red[wave * 1024 + (8 * (e >> 2) + 4 * lg + (e & 3)) * 32 + lr] = acc[i][j][e];
+      __syncthreads();
+      for (int e = tid; e < 1024; e += 256) {
+        const int k = k0 + 32 * i + (e >> 5), n = n0 + 32 * j + (e & 31);
+        if (k < K && n < N) dst[k * N + n] = (red[e] + red[1024 + e]) + (red[2048 + e] + red[3072 + e]);
       }
-      bsum += sacc;
     }
+  if (k0 == 0) {
+    __syncthreads();
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      if (t >= ntiles) break;
-      const int tile = t0 + t, kt = tile / Nt, nt = tile % Nt;
-      const u16* ra = LA + (kt * 32 + lr) * WG_LD + wave * 32 + lg * 8;
-      const u16* rb = LD + (nt * 32 + lr) * WG_LD + wave * 32 + lg * 8;
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        // 8-byte LDS reads (rows are 8-byte aligned)
-        const bf16x4 a0 = *reinterpret_cast<const bf16x4*>(ra + 16 * j);
-        const bf16x4 a1 = *reinterpret_cast<const bf16x4*>(ra + 16 * j + 4);
-        const bf16x4 b0 = *reinterpret_cast<const bf16x4*>(rb + 16 * j);
-        const bf16x4 b1 = *reinterpret_cast<const bf16x4*>(rb + 16 * j + 4);
-        acc[t] = mfma16(a0, a1, b0, b1, acc[t]);
-      }
+    for (int j = 0; j < NT; ++j) red[(wave * 2 + lg) * 32 * NT + 32 * j + lr] = bs[j];
+    __syncthreads();
+    if (tid < 32 * NT && n0 + tid < N) {
+      float s = 0.0f;
+      for (int k = 0; k < 8; ++k) s += red[k * 32 * NT + tid];
+      dst[K * N + n0 + tid] = s;
     }
   }
-  // sum the four waves' tiles in LDS, then one partial set per block
-  __syncthreads();
-  float* red = reinterpret_cast<float*>(smem);
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    if (t >= ntiles) break;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int row = 8 * (i >> 2) + 4 * lg + (i & 3);
-      red[(wave * 4 + t) * 1024 + row * 32 + lr] = acc[t][i];
-    }
-  }
-  __syncthreads();
-  float* dst = part + (long long)blockIdx.x * KN;
-  for (int e = tid; e < ntiles * 1024; e += 256) {
-    const int t = e >> 10, w = e & 1023;
-    const int tile = t0 + t, kt = tile / Nt, nt = tile % Nt;
-    const int k = kt * 32 + (w >> 5), n = nt * 32 + (w & 31);
-    if (k < K && n < N)
-      dst[k * N + n] = (red[t * 1024 + w] + red[(4 + t) * 1024 + w]) +
-                       (red[(8 + t) * 1024 + w] + red[(12 + t) * 1024 + w]);
-  }
-  if (t0 == 0 && tid < N) dst[K * N + tid] = bsum;  // the bias row
 }
 
-// Adds nsets partial sets into gW / gb, for the entries of tiles [t0, t0 + 4)
-// (and the bias row when t0 == 0).  A block sums 64 consecutive entries: its
-// four groups of 64 threads take every fourth set, then combine in LDS.
+// Adds nsets partial sets into gW / gb.  A block sums 16 consecutive entries:
+// its 16 groups of 16 threads take every sixteenth set, then combine in LDS.
 __global__ void __launch_bounds__(256) k_sum_partials(const float* __restrict__ part, int nsets, int K, int N,
-                                                      int t0, float* __restrict__ gW, float* __restrict__ gb) {
-  __shared__ float sh[4][64];
+                                                      float* __restrict__ gW, float* __restrict__ gb) {
+  __shared__ float sh[16][17];
   const int KN = (K + 1) * N;
-  const int el = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  const int e = blockIdx.x * 64 + el;
+  const int el = threadIdx.x & 15, grp = threadIdx.x >> 4;
+  const int e = blockIdx.x * 16 + el;
   float s = 0.f;
   if (e < KN)
-    for (int b = grp; b < nsets; b += 4) s += part[(long long)b * KN + e];
+    for (int b = grp; b < nsets; b += 16) s += part[(long long)b * KN + e];
   sh[grp][el] = s;
   __syncthreads();
   if (grp != 0 || e >= KN) return;
-  s = (sh[0][el] + sh[1][el]) + (sh[2][el] + sh[3][el]);
+  s = 0.f;
+#pragma unroll
+  for (int g = 0; g < 16; ++g) s += sh[g][el];
   const int k = e / N, n = e % N;
-  if (k < K) {
-    const int tile = (k / 32) * ((N + 31) / 32) + n / 32;
-    if (tile < t0 || tile >= t0 + 4) return;
+  if (k < K)
     gW[k * N + n] += s;
-  } else if (t0 == 0) {
+  else
     gb[n] += s;
-  }
 }
 
 // ---- elementwise ------------------------------------------------------------------
-// dpre = dpost * GELU'(pre) (or dpost when last), f32 and bf16 copies.
+// dpre = dpost * GELU'(pre) (or dpost when linear), in bf16.
 __global__ void __launch_bounds__(256) k_gelu_bwd(const float* __restrict__ dpost, const u16* __restrict__ pre,
-                                                  float* __restrict__ dpre, u16* __restrict__ dpreb, long long n,
-                                                  int linear) {
+                                                  const float* __restrict__ gtab, u16* __restrict__ dpreb,
+                                                  long long n, int linear) {
   const long long i = blockIdx.x * 256LL + threadIdx.x;
   if (i >= n) return;
-  const float g = linear ? dpost[i] : dpost[i] * gelu_g(bf2f(pre[i]));
-  dpre[i] = g;
-  dpreb[i] = f2bf(g);
+  dpreb[i] = f2bf(linear ? dpost[i] : dpost[i] * gtab[pre[i]]);
+}
+
+// GELU' over every bf16 value (65536 entries, 256 KiB): the backward pass takes
+// it at BF16 pre-activations, of which few distinct values occur, so a lookup
+// (from the L1) replaces an erf and an exp.
+__global__ void __launch_bounds__(256) k_gelu_table(float* __restrict__ gtab) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  gtab[i] = gelu_g(bf2f((u16)i));
 }
 
 // per-channel input normalisation (x - shift) * inv, applied before rounding to bf16
@@ -441,11 +821,10 @@ __global__ void __launch_bounds__(256) k_pack_input(const TI* __restrict__ x, lo
 }
 
 // loss: out f32 [P][co] vs target (y - x) / scale (planar f32); writes dout
-// (bf16 [P][ldd] padded, f32 [P][co]) and per-block squared-error partials
+// (bf16 [P][ldd] padded) and per-block squared-error partials
 __global__ void __launch_bounds__(256) k_loss(const float* __restrict__ out, const float* __restrict__ x,
                                               const float* __restrict__ y, const float* __restrict__ scale,
-                                              long long P, int co, int ldd, float* __restrict__ doutf,
-                                              u16* __restrict__ doutb, double* __restrict__ part) {
+                                              long long P, int co, int ldd, u16* __restrict__ doutb, double* __restrict__ part) {
   __shared__ double sh[4];
   const long long p = blockIdx.x * 256LL + threadIdx.x;
   double s = 0.0;
@@ -458,7 +837,6 @@ __global__ void __launch_bounds__(256) k_loss(const float* __restrict__ out, con
         const float d = out[p * co + c] - tgt;
         s += (double)d * d;
         g = d * inv;
-        doutf[p * co + c] = g;
       }
       doutb[p * ldd + c] = f2bf(g);
     }
@@ -569,6 +947,7 @@ struct pf_fno {
   hipStream_t stream = nullptr;
   int acct = 0;  // accounting on
   bool fuse_x = false;  // x stages carried by the channel-mixing GEMMs (n % 32 == 0)
+  bool fuse_proj = false;  // the projection in one pass (width <= 32, one MFMA tile)
   double acct_bytes[FK_COUNT] = {}, acct_flops[FK_COUNT] = {};
   long long acct_n[FK_COUNT] = {};
   long long P = 0;
@@ -595,8 +974,9 @@ struct pf_fno {
   u16 *A1 = nullptr, *A2 = nullptr, *A3 = nullptr, *Tb = nullptr, *B3 = nullptr, *B2 = nullptr;
   float *T = nullptr, *B1 = nullptr, *outf = nullptr;
   // backward buffers
-  float *dvf = nullptr, *dvf2 = nullptr, *dpref = nullptr, *dpref2 = nullptr, *dT = nullptr, *dhf = nullptr;
-  u16 *dvb = nullptr, *dpreb = nullptr, *dpreb2 = nullptr, *douthb = nullptr, *dhb = nullptr, *dSb = nullptr;
+  float *dvf = nullptr, *dT = nullptr;
+  u16 *dpreb = nullptr, *dpreb2 = nullptr, *douthb = nullptr, *dhb = nullptr, *dSb = nullptr;
+  float* gtab = nullptr;  // GELU' over the bf16 values
   float* part = nullptr;
   long long part_elems = 0;
   double* dpart = nullptr;
@@ -736,12 +1116,16 @@ static void cm_launch(pf_fno* F, long long points, const u16* In, int ldin, int 
   }
   if (gpre) bytes += points * N * 2.0;
   account(F, FK_CM, bytes, flops);
+  auto go = [&](auto NC) {
+    k_cm_gemm<decltype(NC)::value><<<grid, 256, 0, F->stream>>>(In, ldin, K, Bt, N, bias, resid, ldres, outf, outpre,
+                                                                outact, ldout, accumulate, lt, gpre, F->gtab);
+  };
   if (N <= 32)
-    k_cm_gemm<1><<<grid, 256, 0, F->stream>>>(In, ldin, K, Bt, N, bias, resid, ldres, outf, outpre, outact, ldout,
-                                               accumulate, lt, gpre);
+    go(std::integral_constant<int, 1>{});
+  else if (N <= 64)
+    go(std::integral_constant<int, 2>{});
   else
-    k_cm_gemm<4><<<grid, 256, 0, F->stream>>>(In, ldin, K, Bt, N, bias, resid, ldres, outf, outpre, outact, ldout,
-                                               accumulate, lt, gpre);
+    go(std::integral_constant<int, 4>{});
 }
 
 static void cm(pf_fno* F, const u16* In, int ldin, int K, const u16* Bt, int N, const float* bias, const float* resid,
@@ -752,35 +1136,96 @@ static void cm(pf_fno* F, const u16* In, int ldin, int K, const u16* Bt, int N, 
 
 constexpr int kWgradBlocks = 512;  // blocks (point chunks) of one weight-gradient reduction
 
-static void wgrad(pf_fno* F, const u16* A, int lda, int K, const float* D, int ldd, int N, float* gW, float* gb) {
-  const long long per = (F->P + kWgradBlocks - 1) / kWgradBlocks;
-  const int chunk = (int)((per + WG_PTS - 1) / WG_PTS * WG_PTS);
-  const int nb = (int)gdiv(F->P, chunk);
-  const int KN = (K + 1) * N;
-  const int tiles = ((K + 31) / 32) * ((N + 31) / 32);
-  const int ntx = (N + 31) / 32;
-  for (int t0 = 0; t0 < tiles; t0 += 4) {
-    // this launch's tiles: the K and N ranges it reads, the outputs it forms
-    const int t1 = std::min(tiles, t0 + 4);
-    double kk = 0.0, nn = 0.0, outs = 0.0;
-    {
-      int kmin = 1 << 30, kmax = 0, nmin = 1 << 30, nmax = 0;
-      for (int t = t0; t < t1; ++t) {
-        const int kt = t / ntx, nt = t % ntx;
-        kmin = std::min(kmin, kt * 32);
-        kmax = std::max(kmax, std::min(K, kt * 32 + 32));
-        nmin = std::min(nmin, nt * 32);
-        nmax = std::max(nmax, std::min(N, nt * 32 + 32));
-        outs += (double)(std::min(K, kt * 32 + 32) - kt * 32) * (std::min(N, nt * 32 + 32) - nt * 32);
-      }
-      kk = kmax - kmin;
-      nn = nmax - nmin;
+static void sum_partials(pf_fno* F, const float* part, int nb, int K, int N, float* gW, float* gb) {
+  const double kn = (double)(K + 1) * N;
+  account(F, FK_WSUM, 4.0 * nb * kn + 8.0 * kn, (double)nb * kn);
+  k_sum_partials<<<gdiv((K + 1) * N, 16), 256, 0, F->stream>>>(part, nb, K, N, gW, gb);
+}
+
+static void wgrad(pf_fno* F, const u16* A, int lda, int K, const u16* D, int ldd, int N, float* gW, float* gb) {
+  const int nb = (int)std::min<long long>(kWgradBlocks, (F->P / 32 + 3) / 4);
+  for (int k0 = 0; k0 < K; k0 += 64)
+    for (int n0 = 0; n0 < N; n0 += 64) {
+      const int kk = std::min(64, K - k0), nn = std::min(64, N - n0);
+      account(F, FK_WGRAD, (double)F->P * 2.0 * (kk + nn) + 4.0 * nb * kk * nn, 2.0 * F->P * kk * nn);
+      auto go = [&](auto KC, auto NC) {
+        k_wgrad_mfma<decltype(KC)::value, decltype(NC)::value>
+            <<<nb, 256, 0, F->stream>>>(A, lda, K, D, ldd, N, F->P, k0, n0, F->part);
+      };
+      using one = std::integral_constant<int, 1>;
+      using two = std::integral_constant<int, 2>;
+      if (kk <= 32)
+        nn <= 32 ? go(one{}, one{}) : go(one{}, two{});
+      else
+        nn <= 32 ? go(two{}, one{}) : go(two{}, two{});
     }
-    account(F, FK_WGRAD, (double)F->P * (2.0 * kk + 4.0 * nn) + 4.0 * nb * KN, 2.0 * F->P * outs);
-    k_wgrad_mfma<<<nb, 256, 0, F->stream>>>(A, lda, K, D, ldd, N, F->P, chunk, t0, F->part);
-    account(F, FK_WSUM, 4.0 * nb * outs + 8.0 * outs, (double)nb * outs);
-    k_sum_partials<<<gdiv(KN, 64), 256, 0, F->stream>>>(F->part, nb, K, N, t0, gW, gb);
-  }
+  sum_partials(F, F->part, nb, K, N, gW, gb);
+}
+
+// The fused projection over `points` points (kProjBlocks: two work-groups per
+// CU, walking the points).
+constexpr int kProjBlocks = 512;
+
+static ProjArgs proj_args(const pf_fno* F, const u16* v, long long points) {
+  ProjArgs a = {};
+  a.v = v;
+  a.P1T = F->bP1T;
+  a.P2T = F->bP2T;
+  a.P1 = F->bP1;
+  a.P2 = F->bP2;
+  a.c1 = F->th + F->o_c1;
+  a.c2 = F->th + F->o_c2;
+  a.P = points;
+  a.w = F->cfg.width;
+  a.h = F->cfg.hidden;
+  a.co = F->cfg.cout;
+  a.gtab = F->gtab;
+  return a;
+}
+
+template <bool TRAIN>
+static int proj_launch(pf_fno* F, const ProjArgs& a) {
+  const int nb = (int)std::min<long long>(kProjBlocks, (a.P / 32 + 3) / 4);
+  if (a.h <= 64)
+    k_proj<TRAIN, 2><<<nb, 256, 0, F->stream>>>(a);
+  else if (a.h <= 96)
+    k_proj<TRAIN, 3><<<nb, 256, 0, F->stream>>>(a);
+  else
+    k_proj<TRAIN, 4><<<nb, 256, 0, F->stream>>>(a);
+  return nb;
+}
+
+// out (f32 [points][cout]) of v_L (bf16 [points][width])
+static void project(pf_fno* F, const u16* v, long long points, float* out) {
+  const pf_fno_config& c = F->cfg;
+  ProjArgs a = proj_args(F, v, points);
+  a.outf = out;
+  // accounted as its two products; the hidden layer moves no bytes
+  account(F, FK_CM, 2.0 * points * c.width + 2.0 * c.hidden * c.width, 2.0 * points * c.hidden * c.width);
+  account(F, FK_CM, 4.0 * points * c.cout + 2.0 * c.hidden * c.cout, 2.0 * points * c.hidden * c.cout);
+  proj_launch<false>(F, a);
+}
+
+// Projection, loss and the projection's backward pass: d v_L into dpre, the
+// gradients of P1, c1, P2, c2 added to the gradient buffer, the summed squared
+// error into F->dsum.
+static void project_train(pf_fno* F, const float* x, const float* y, u16* dpre) {
+  const pf_fno_config& c = F->cfg;
+  const int w = c.width, h = c.hidden, co = c.cout;
+  ProjArgs a = proj_args(F, F->pre[c.layers - 1], F->P);
+  a.x = x;
+  a.y = y;
+  a.scale = F->scale;
+  a.inv = 2.0f / (float)((double)F->P * co);
+  a.dpre = dpre;
+  a.part1 = F->part;
+  a.part2 = F->part + (long long)kProjBlocks * (w + 1) * h;
+  a.dpart = F->dpart;
+  account(F, FK_CM, (double)F->P * (4.0 * w + 8.0 * co) + 4.0 * h * (w + co), 6.0 * F->P * h * (w + co));
+  const int nb = proj_launch<true>(F, a);
+  k_sum_d<<<1, 256, 0, F->stream>>>(F->dpart, nb, F->dsum);
+  sum_partials(F, a.part1, nb, w, h, F->gr + F->o_P1, F->gr + F->o_c1);
+  sum_partials(F, a.part2, nb, h, co, F->gr + F->o_P2, F->gr + F->o_c2);
 }
 
 // refresh the bf16 working weights from the FP32 master vector
@@ -825,11 +1270,10 @@ static LineTerm x_inverse(const pf_fno* F, const u16* B2) {
   return lt;
 }
 
-// forward pass for the packed input F->xin; leaves the result in F->outf
-static void forward(pf_fno* F) {
+// forward pass for the packed input F->xin up to v_L (F->pre[layers - 1])
+static void forward_layers(pf_fno* F) {
   const pf_fno_config& c = F->cfg;
-  const int n = c.n, w = c.width, m = c.modes, m2 = 2 * m, h = c.hidden;
-  const long long P = F->P;
+  const int n = c.n, w = c.width, m = c.modes, m2 = 2 * m;
   const float* th = F->th;
   cm(F, F->xin, F->cinp, F->cinp, F->bWliftT, w, th + F->o_bl, nullptr, 0, nullptr, F->v[0], nullptr, w, 0);
   for (int l = 0; l < c.layers; ++l) {
@@ -860,24 +1304,51 @@ static void forward(pf_fno* F) {
       cm(F, v, w, w, F->bWT[l], w, th + F->o_b[l], F->B1, w, nullptr, F->pre[l], last ? nullptr : F->v[l + 1], w, 0);
     }
   }
-  const u16* vL = F->pre[c.layers - 1];  // v_L = pre_{L-1}
-  cm(F, vL, w, w, F->bP1T, h, th + F->o_c1, nullptr, 0, nullptr, F->hpre, F->hact, h, 0);
-  cm(F, F->hact, h, h, F->bP2T, c.cout, th + F->o_c2, nullptr, 0, F->outf, nullptr, nullptr, c.cout, 0);
-  (void)P;
 }
 
-// backward pass; the loss gradient is in F->douthb (bf16 [P][coutp]) and F->dvf2 (f32 [P][cout])
-static void backward(pf_fno* F) {
+// the projection as GEMMs through the hidden layer (width > 32)
+static void project_gemms(pf_fno* F) {
+  const pf_fno_config& c = F->cfg;
+  const int w = c.width, h = c.hidden;
+  const float* th = F->th;
+  cm(F, F->pre[c.layers - 1], w, w, F->bP1T, h, th + F->o_c1, nullptr, 0, nullptr, F->hpre, F->hact, h, 0);
+  cm(F, F->hact, h, h, F->bP2T, c.cout, th + F->o_c2, nullptr, 0, F->outf, nullptr, nullptr, c.cout, 0);
+}
+
+// forward pass for the packed input F->xin; leaves the result in F->outf
+static void forward(pf_fno* F) {
+  forward_layers(F);
+  if (F->fuse_proj)
+    project(F, F->pre[F->cfg.layers - 1], F->P, F->outf);
+  else
+    project_gemms(F);
+}
+
+// Projection, loss (sum of squares into F->dsum) and backward pass for the
+// state pair x, y.  Every gradient that a weight gradient reads is BF16, as the
+// MFMA takes it.
+static void loss_backward(pf_fno* F, const float* x, const float* y) {
   const pf_fno_config& c = F->cfg;
   const int n = c.n, w = c.width, m = c.modes, m2 = 2 * m, h = c.hidden, co = c.cout;
   const long long P = F->P;
   float* g = F->gr;
-  // projection: out = hact P2 + c2
-  wgrad(F, F->hact, h, h, F->dvf2, co, co, g + F->o_P2, g + F->o_c2);
-  // d hpre = (d out P2^T) GELU'(hpre), formed in the GEMM's epilogue
-  cm(F, F->douthb, F->coutp, F->coutp, F->bP2, h, nullptr, nullptr, 0, F->dhf, F->dhb, nullptr, h, 0, LineTerm(),
-     F->hpre);
-  wgrad(F, F->pre[c.layers - 1], w, w, F->dhf, h, h, g + F->o_P1, g + F->o_c1);
+  u16* db[2] = {F->dpreb, F->dpreb2};  // d pre of the layer, and of the one before
+  if (F->fuse_proj) {
+    project_train(F, x, y, db[0]);
+  } else {
+    project_gemms(F);
+    const unsigned nb = gdiv(P, 256);
+    account(F, FK_ELEM, (double)P * co * (4.0 * 3) + (double)P * F->coutp * 2.0, 0.0);
+    k_loss<<<nb, 256, 0, F->stream>>>(F->outf, x, y, F->scale, P, co, F->coutp, F->douthb, F->dpart);
+    k_sum_d<<<1, 256, 0, F->stream>>>(F->dpart, (int)nb, F->dsum);
+    // out = hact P2 + c2
+    wgrad(F, F->hact, h, h, F->douthb, F->coutp, co, g + F->o_P2, g + F->o_c2);
+    // d hpre = (d out P2^T) GELU'(hpre), formed in the GEMM's epilogue
+    cm(F, F->douthb, F->coutp, F->coutp, F->bP2, h, nullptr, nullptr, 0, nullptr, F->dhb, nullptr, h, 0, LineTerm(),
+       F->hpre);
+    wgrad(F, F->pre[c.layers - 1], w, w, F->dhb, h, h, g + F->o_P1, g + F->o_c1);
+    cm(F, F->dhb, h, h, F->bP1, w, nullptr, nullptr, 0, nullptr, db[0], nullptr, w, 0);
+  }
   const int Nz = m2 * m * w;
   // the spectral path's transposed stages from dpreb (bf16 d pre of the layer) down to A1
   auto spectral_back = [&](int l, const u16* dpreb) {
@@ -899,8 +1370,8 @@ static void backward(pf_fno* F) {
   };
   if (F->fuse_x) {
     // d v_l = d pre_l W^T + (transposed x stage of A1) in one GEMM, whose
-    // epilogue applies GELU'(pre_{l-1}) to give d pre_{l-1} (f32 and bf16),
-    // ping-ponging between two buffers; the last layer is linear
+    // epilogue applies GELU'(pre_{l-1}) to give d pre_{l-1}, ping-ponging
+    // between two buffers; the last layer is linear
     LineTerm lt;
     lt.G = F->GxfT;
     lt.K = 2 * m;
@@ -908,37 +1379,27 @@ static void backward(pf_fno* F) {
     lt.X = F->A1;
     lt.xbs = (long long)2 * m * w;
     lt.ldx = w;
-    float* df[2] = {F->dpref, F->dpref2};
-    u16* db[2] = {F->dpreb, F->dpreb2};
-    int cur = 0;
-    cm(F, F->dhb, h, h, F->bP1, w, nullptr, nullptr, 0, df[cur], db[cur], nullptr, w, 0);
     for (int l = c.layers - 1; l >= 0; --l) {
-      wgrad(F, F->v[l], w, w, df[cur], w, w, g + F->o_W[l], g + F->o_b[l]);
-      spectral_back(l, db[cur]);
-      if (l > 0) {
-        cm(F, db[cur], w, w, F->bW[l], w, nullptr, nullptr, 0, df[1 - cur], db[1 - cur], nullptr, w, 0, lt,
-           F->pre[l - 1]);
-        cur = 1 - cur;
-      } else {
-        cm(F, db[cur], w, w, F->bW[0], w, nullptr, nullptr, 0, F->dvf, nullptr, nullptr, w, 0, lt);
-      }
+      wgrad(F, F->v[l], w, w, db[0], w, w, g + F->o_W[l], g + F->o_b[l]);
+      spectral_back(l, db[0]);
+      cm(F, db[0], w, w, F->bW[l], w, nullptr, nullptr, 0, nullptr, db[1], nullptr, w, 0, lt,
+         l > 0 ? F->pre[l - 1] : nullptr);
+      std::swap(db[0], db[1]);
     }
   } else {
-    cm(F, F->dhb, h, h, F->bP1, w, nullptr, nullptr, 0, F->dvf, nullptr, nullptr, w, 0);
     for (int l = c.layers - 1; l >= 0; --l) {
-      const bool last = l == c.layers - 1;
-      account(F, FK_GELU, (double)P * w * (4.0 + 2.0 + 4.0 + 2.0), 20.0 * P * w);
-      k_gelu_bwd<<<gdiv(P * w, 256), 256, 0, F->stream>>>(F->dvf, F->pre[l], F->dpref, F->dpreb, P * w,
-                                                          last ? 1 : 0);
-      wgrad(F, F->v[l], w, w, F->dpref, w, w, g + F->o_W[l], g + F->o_b[l]);
-      spectral_back(l, F->dpreb);
+      wgrad(F, F->v[l], w, w, db[0], w, w, g + F->o_W[l], g + F->o_b[l]);
+      spectral_back(l, db[0]);
       // pointwise data gradient plus the transposed x stage of the spectral path
-      cm(F, F->dpreb, w, w, F->bW[l], w, nullptr, nullptr, 0, F->dvf, nullptr, nullptr, w, 0);
+      cm(F, db[0], w, w, F->bW[l], w, nullptr, nullptr, 0, F->dvf, nullptr, nullptr, w, 0);
       lm(F, F->GxfT, n, 2 * m, F->A1, (long long)2 * m * w, w, w, n * n, F->dvf, nullptr, (long long)n * w, w, 1);
+      account(F, FK_GELU, (double)P * w * (4.0 + 2.0 + 2.0), 20.0 * P * w);
+      k_gelu_bwd<<<gdiv(P * w, 256), 256, 0, F->stream>>>(F->dvf, l > 0 ? F->pre[l - 1] : nullptr, F->gtab, db[0],
+                                                          P * w, l > 0 ? 0 : 1);
     }
   }
-  // lift: v0 = x W_lift + b_lift
-  wgrad(F, F->xin, F->cinp, c.cin, F->dvf, w, w, g + F->o_Wl, g + F->o_bl);
+  // lift: v0 = x W_lift + b_lift (db[0]: d v0)
+  wgrad(F, F->xin, F->cinp, c.cin, db[0], w, w, g + F->o_Wl, g + F->o_bl);
 }
 
 extern "C" {
@@ -962,6 +1423,7 @@ pf_status pf_fno_create(const pf_fno_config* cfg, void* stream, pf_fno** out) {
   const int w = c.width, m = c.modes, m2 = 2 * m, h = c.hidden, n = c.n;
   F->mode_count = m2 * m2 * m;
   F->fuse_x = n % 32 == 0;
+  F->fuse_proj = w <= 32;
   // parameter layout (same order as the oracle)
   long long off = 0;
   F->o_Wl = off; off += (long long)c.cin * w;
@@ -1012,8 +1474,9 @@ pf_status pf_fno_create(const pf_fno_config* cfg, void* stream, pf_fno** out) {
     A((void**)&F->pre[l], 2 * P * w);
     A((void**)&F->S[l], 4 * spec);
   }
-  A((void**)&F->hpre, 2 * P * h);
-  A((void**)&F->hact, 2 * P * h);
+  if (!F->fuse_proj) A((void**)&F->hpre, 2 * P * h);
+  if (!F->fuse_proj) A((void**)&F->hact, 2 * P * h);
+  A((void**)&F->gtab, 4 * 65536);
   const size_t a1 = (size_t)n * n * 2 * m * w, a2 = (size_t)n * 2 * m2 * m * w, b2 = (size_t)n * 2 * n * m * w;
   A((void**)&F->A1, 2 * std::max(a1, b2));
   A((void**)&F->A2, 2 * std::max(a2, (size_t)2 * n * m2 * m * w));
@@ -1024,16 +1487,12 @@ pf_status pf_fno_create(const pf_fno_config* cfg, void* stream, pf_fno** out) {
   A((void**)&F->B2, 2 * std::max(b2, a1));
   if (!F->fuse_x) A((void**)&F->B1, 4 * P * w);
   A((void**)&F->outf, 4 * P * c.cout);
-  A((void**)&F->dvf, 4 * P * w);
-  A((void**)&F->dvf2, 4 * P * c.cout);
-  A((void**)&F->dpref, 4 * P * w);
+  if (!F->fuse_x) A((void**)&F->dvf, 4 * P * w);
   A((void**)&F->dT, 4 * spec);
-  A((void**)&F->dhf, 4 * P * h);
-  A((void**)&F->dhb, 2 * P * h);
+  if (!F->fuse_proj) A((void**)&F->dhb, 2 * P * h);
   A((void**)&F->dpreb, 2 * P * w);
-  if (F->fuse_x) A((void**)&F->dpref2, 4 * P * w);
   if (F->fuse_x) A((void**)&F->dpreb2, 2 * P * w);
-  A((void**)&F->douthb, 2 * P * F->coutp);
+  if (!F->fuse_proj) A((void**)&F->douthb, 2 * P * F->coutp);
   A((void**)&F->dSb, 2 * spec);
   F->part_elems = (long long)kWgradBlocks * (std::max(std::max(w, h), 8) + 1) * std::max(std::max(w, h), 8);
   A((void**)&F->part, 4 * F->part_elems);
@@ -1058,6 +1517,10 @@ pf_status pf_fno_create(const pf_fno_config* cfg, void* stream, pf_fno** out) {
     if (hipMemset(F->th, 0, 4 * off) != hipSuccess || hipMemset(F->gr, 0, 4 * off) != hipSuccess ||
         hipMemset(F->am, 0, 4 * off) != hipSuccess || hipMemset(F->av, 0, 4 * off) != hipSuccess)
       s = PF_ERR_HIP;
+  }
+  if (s == PF_OK) {
+    k_gelu_table<<<256, 256, 0, F->stream>>>(F->gtab);
+    if (hipGetLastError() != hipSuccess) s = PF_ERR_HIP;
   }
   if (s != PF_OK) {
     pf_fno_destroy(F);
@@ -1174,13 +1637,8 @@ pf_status pf_fno_grad(pf_fno* F, const float* x, const float* y, double* loss) {
   if (!F || !x || !y) return PF_ERR_ARG;
   account(F, FK_ELEM, (double)F->P * (4.0 * F->cfg.cin + 2.0 * F->cinp), 0.0);
   k_pack_input<float><<<gdiv(F->P, 256), 256, 0, F->stream>>>(x, F->P, F->cfg.cin, F->cinp, F->innorm, F->xin);
-  forward(F);
-  const unsigned nb = gdiv(F->P, 256);
-  account(F, FK_ELEM, (double)F->P * F->cfg.cout * (4.0 * 4) + (double)F->P * F->coutp * 2.0, 0.0);
-  k_loss<<<nb, 256, 0, F->stream>>>(F->outf, x, y, F->scale, F->P, F->cfg.cout, F->coutp, F->dvf2, F->douthb,
-                                    F->dpart);
-  k_sum_d<<<1, 256, 0, F->stream>>>(F->dpart, (int)nb, F->dsum);
-  backward(F);
+  forward_layers(F);
+  loss_backward(F, x, y);
   FH(hipMemcpyAsync(F->hsum, F->dsum, 8, hipMemcpyDeviceToHost, F->stream));
   FH(hipGetLastError());
   FH(hipStreamSynchronize(F->stream));
@@ -1324,7 +1782,7 @@ static pf_status ensure_batch(pf_fno* F, int B) {
   A((void**)&F->bB3, Bs * 2 * 2 * n * Nz);
   A((void**)&F->bB2, Bs * 2 * a1);
   if (!F->fuse_x) A((void**)&F->bB1, Bs * 4 * P * w);
-  A((void**)&F->bhact, Bs * 2 * P * h);
+  if (!F->fuse_proj) A((void**)&F->bhact, Bs * 2 * P * h);
   A((void**)&F->boutf, Bs * 4 * P * c.cout);
   A((void**)&F->bdpart, Bs * 8 * gdiv(F->P, 256));
   A((void**)&F->bdsum, Bs * 8);
@@ -1379,6 +1837,10 @@ static void forward_batch(pf_fno* F, int B) {
                 last ? nullptr : vn, w);
     }
     std::swap(v, vn);
+  }
+  if (F->fuse_proj) {
+    project(F, v, PB, F->boutf);
+    return;
   }
   cm_points(F, PB, v, w, w, F->bP1T, h, th + F->o_c1, nullptr, 0, nullptr, nullptr, F->bhact, h);
   cm_points(F, PB, F->bhact, h, h, F->bP2T, c.cout, th + F->o_c2, nullptr, 0, F->boutf, nullptr, nullptr, c.cout);
