@@ -610,6 +610,237 @@ k_lm_gemm(const u16* __restrict__ G, int R, int K, const u16* __restrict__ X, lo
   }
 }
 
+// ---- small-matrix GEMM with the slow index contracted: y and z stages ----------
+// The same product as k_lm_gemm for X whose rows (the contracted index) are
+// long: a wave takes 32 columns and RT * 32 rows of G, reads 32 x 32 tiles of X
+// 16 bytes per lane and transposes them in registers (transpose_operand), where
+// k_lm_gemm gathers eight 2-byte values per lane and operand.  A lane then holds
+// one row of the result and stores eight columns at a time.  blockIdx.z picks
+// the band of RT * 32 rows.  Needs K, Nc, ldx, xbs, ldo, obs % 8 == 0.
+template <int RT>
+__global__ void __launch_bounds__(256)
+k_lm_rows(const u16* __restrict__ G, int R, int K, const u16* __restrict__ X, long long xbs, int ldx, int Nc,
+          float* __restrict__ outf, u16* __restrict__ outb, long long obs, int ldo, long long items) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 31, lg = lane >> 5;
+  const long long item = (long long)blockIdx.x * 4 + wave;  // (batch, 32-column group)
+  if (item >= items) return;  // no block-level synchronisation in this kernel
+  const int groups = (Nc + 31) / 32;
+  const long long b = item / groups;
+  const int n0 = (int)(item % groups) * 32, r0 = blockIdx.z * (32 * RT);
+  const u16* Xb = X + b * xbs;
+  u32x4 id[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) id[s] = identity_operand(s, lr, lg);
+  f32x16 acc[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) acc[t] = zero16();
+  auto load = [&](int k0, u32x4(&x)[2]) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int n = n0 + 16 * s + 8 * lg;
+      x[s] = u32x4{0, 0, 0, 0};
+      if (k0 + lr < K && n < Nc) x[s] = *reinterpret_cast<const u32x4*>(Xb + (long long)(k0 + lr) * ldx + n);
+    }
+  };
+  u32x4 nx[2];
+  load(0, nx);
+  for (int k0 = 0; k0 < K; k0 += 32) {
+    const u32x4 x[2] = {nx[0], nx[1]};
+    u32x4 xt[2];
+    if (k0 + 32 < K) load(k0 + 32, nx);
+    transpose_operand(x, id, xt);
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      const int r = r0 + 32 * t + lr;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        if (k0 + 16 * s >= K) continue;
+        const u32x4 g = r < R ? ld8(G + (long long)r * K, k0 + 16 * s + 8 * lg, K, true) : u32x4{0, 0, 0, 0};
+        acc[t] = mfma32(xt[s], g, acc[t]);
+      }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    const int r = r0 + 32 * t + lr;
+    const long long o = b * obs + (long long)r * ldo + n0;
+    if (outf) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int c = 8 * q + 4 * lg;
+        if (r < R && n0 + c < Nc)
+          *reinterpret_cast<f32x4*>(outf + o + c) = f32x4{acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2],
+                                                          acc[t][4 * q + 3]};
+      }
+    } else {
+      u32x4 op[2];
+      to_operand(acc[t], op);
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+        if (r < R) st8(outb + o - n0, n0 + 16 * s + 8 * lg, Nc, true, op[s]);
+    }
+  }
+}
+
+// ---- one layer along x lines: pointwise product, inverse x stage, activation, next x stage ----
+// A wave takes one x line, 32 points at a time: v W (+ the inverse x stage of
+// the line's spectral block X) + bias, the activation (or, backward, times
+// GELU' of gpre), stored; and, contracted over the line's points with Gd, the
+// x stage the next spectral path starts with - from the registers, so the
+// activations are not read again for it (134 MB per layer at 128^3) nor
+// gathered 2 bytes at a time.  With k_lm_rows it took an advance of two 128^3
+// samples from 3.34 to 2.18 ms, a gradient over four from 21.2 to 16.9 ms.  Bt == nullptr: only the x stage of In.
+// sep: the inverse x stage is summed apart and added last (the order of the
+// unfused path, which grids that 32 does not divide took).
+// K, N <= 32 NT, N % 4 == 0, n % 8 == 0, 2m <= 32.
+struct XLineArgs {
+  const u16* In;       // [point][ldin]
+  int ldin, K, N;
+  const u16* Bt;       // [N][K]
+  const float* bias;
+  const u16 *G, *X;    // [n][2m]; [line][2m][N] (null: no line term)
+  int m2, sep;         // 2m
+  const u16* gpre;     // [point][N]
+  const float* gtab;
+  u16 *outpre, *outact;
+  const u16* Gd;       // [2m][n] (null: no x stage)
+  u16* A1;             // [line][2m][N]
+  int n;
+  long long lines;
+};
+
+template <int NT>
+__global__ void __launch_bounds__(256, NT == 1 ? 4 : 2) k_xline(XLineArgs a) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 31, lg = lane >> 5;
+  const long long line = (long long)blockIdx.x * 4 + wave;
+  if (line >= a.lines) return;  // no block-level synchronisation in this kernel
+  const int n = a.n, K = a.K, N = a.N, m2 = a.m2;
+  const bool in16 = K % 8 == 0 && a.ldin % 8 == 0, k16 = K % 8 == 0, o16 = N % 8 == 0, g16 = m2 % 8 == 0;
+  u32x4 bt[NT][2 * NT], xt[NT][2];
+  f32x16 spec[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int c = 32 * t + lr;
+#pragma unroll
+    for (int s = 0; s < 2 * NT; ++s) {
+      bt[t][s] = u32x4{0, 0, 0, 0};
+      if (a.Bt && c < N) bt[t][s] = ld8(a.Bt + c * K, 16 * s + 8 * lg, K, k16);
+    }
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      u32x4 x = {0, 0, 0, 0};
+      if (a.G && c < N) {
+        const u16* Xb = a.X + line * m2 * N + c;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int k = 16 * s + 8 * lg + j;
+          if (k < m2) x[j >> 1] |= (unsigned)Xb[k * N] << (16 * (j & 1));
+        }
+      }
+      xt[t][s] = x;
+    }
+    spec[t] = zero16();
+  }
+  u32x4 id[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) id[s] = identity_operand(s, lr, lg);
+  for (int x0 = 0; x0 < n; x0 += 32) {
+    const bool in = x0 + lr < n;
+    const long long p = line * n + (in ? x0 + lr : 0);
+    u32x4 src[NT][2];  // what the x stage contracts (lane = point)
+    u32x4 vin[2 * NT];
+#pragma unroll
+    for (int s = 0; s < 2 * NT; ++s) vin[s] = ld8(a.In + p * a.ldin, 16 * s + 8 * lg, K, in16);
+    if (a.Bt) {
+      f32x16 acc[NT], acx[NT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[t] = acx[t] = zero16();
+#pragma unroll
+      for (int s = 0; s < 2 * NT; ++s)
+        if (16 * s < K) {
+#pragma unroll
+          for (int t = 0; t < NT; ++t) acc[t] = mfma32(bt[t][s], vin[s], acc[t]);
+        }
+      if (a.G) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+          if (16 * s < m2) {
+            const u32x4 g = in ? ld8(a.G + (x0 + lr) * m2, 16 * s + 8 * lg, m2, g16) : u32x4{0, 0, 0, 0};
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+              if (a.sep)
+                acx[t] = mfma32(xt[t][s], g, acx[t]);
+              else
+                acc[t] = mfma32(xt[t][s], g, acc[t]);
+            }
+          }
+      }
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        f32x16 v = acc[t];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int c = t * 32 + 8 * q + 4 * lg;
+          if (c >= N) continue;
+          const f32x4 bb = a.bias ? *reinterpret_cast<const f32x4*>(a.bias + c) : f32x4{0.f, 0.f, 0.f, 0.f};
+          u32x2 gp = {0, 0};
+          if (a.gpre) gp = *reinterpret_cast<const u32x2*>(a.gpre + p * N + c);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            float r = v[4 * q + j] + bb[j];
+            if (a.sep) r += acx[t][4 * q + j];
+            if (a.gpre) r *= a.gtab[(gp[j >> 1] >> (16 * (j & 1))) & 0xffffu];
+            v[4 * q + j] = r;
+          }
+        }
+        if (a.outpre || !a.outact) {
+          to_operand(v, src[t]);
+          if (a.outpre && in) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) st8(a.outpre + p * N, 32 * t + 16 * s + 8 * lg, N, o16, src[t][s]);
+          }
+        }
+        if (a.outact) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) v[i] = gelu_f(v[i]);
+          to_operand(v, src[t]);
+          if (in) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) st8(a.outact + p * N, 32 * t + 16 * s + 8 * lg, N, o16, src[t][s]);
+          }
+        }
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) src[t][0] = vin[2 * t], src[t][1] = vin[2 * t + 1];
+    }
+    if (a.Gd) {
+      u32x4 gd[2];
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+        gd[s] = lr < m2 ? ld8(a.Gd + lr * n, x0 + 16 * s + 8 * lg, n, true) : u32x4{0, 0, 0, 0};
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        u32x4 tr[2];
+        transpose_operand(src[t], id, tr);
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+          if (x0 + 16 * s < n) spec[t] = mfma32(tr[s], gd[s], spec[t]);
+      }
+    }
+  }
+  if (a.Gd) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      u32x4 op[2];
+      to_operand(spec[t], op);
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+        if (lr < m2) st8(a.A1 + (line * m2 + lr) * N, 32 * t + 16 * s + 8 * lg, N, o16, op[s]);
+    }
+  }
+}
+
 // ---- per-mode complex mixing (FP32) -------------------------------------------
 // S, T: [2][modes][w] (real block, imaginary block); R: [modes][w][w] (in, out).
 // `batches` spectra one after another (stride 2 modes w), the same weights.
@@ -947,6 +1178,7 @@ struct pf_fno {
   hipStream_t stream = nullptr;
   int acct = 0;  // accounting on
   bool fuse_x = false;  // x stages carried by the channel-mixing GEMMs (n % 32 == 0)
+  bool xlines = false;     // layers as passes along x lines (k_xline: width <= 64, 16 modes at most)
   bool fuse_proj = false;  // the projection in one pass (width <= 32, one MFMA tile)
   double acct_bytes[FK_COUNT] = {}, acct_flops[FK_COUNT] = {};
   long long acct_n[FK_COUNT] = {};
@@ -1102,6 +1334,49 @@ static void lm(pf_fno* F, const u16* G, int R, int K, const u16* X, long long xb
     k_lm_gemm<<<grid, 256, 0, F->stream>>>(G, R, K, X + b0 * xbs, xbs, ldx, Nc, outf ? outf + b0 * obs : nullptr,
                                            outb ? outb + b0 * obs : nullptr, obs, ldo, accumulate, wpb, nb);
   }
+}
+
+// y and z stages of the truncated DFT (G: R x K, K % 8 == 0; columns % 8 == 0)
+static void lm_rows(pf_fno* F, const u16* G, int R, int K, const u16* X, long long xbs, int ldx, int Nc, int batches,
+                    float* outf, u16* outb, long long obs, int ldo) {
+  const double cols = (double)Nc * batches;
+  account(F, FK_LM, 2.0 * R * K + 2.0 * K * cols + (outf ? 4.0 : 2.0) * R * cols, 2.0 * R * K * cols);
+  const long long items = (long long)batches * gdiv(Nc, 32);
+  // 64 rows per wave where that fills the chip (four waves per SIMD), else 32
+  const bool two = R > 32 && items * gdiv(R, 64) >= 4096;
+  dim3 grid(gdiv(items, 4), 1, gdiv(R, two ? 64 : 32));
+  if (two)
+    k_lm_rows<2><<<grid, 256, 0, F->stream>>>(G, R, K, X, xbs, ldx, Nc, outf, outb, obs, ldo, items);
+  else
+    k_lm_rows<1><<<grid, 256, 0, F->stream>>>(G, R, K, X, xbs, ldx, Nc, outf, outb, obs, ldo, items);
+}
+
+// one pass along the x lines of `samples` grids (see k_xline)
+static void xline(pf_fno* F, XLineArgs a, long long samples) {
+  const pf_fno_config& c = F->cfg;
+  a.m2 = 2 * c.modes;
+  a.n = c.n;
+  a.lines = samples * c.n * c.n;
+  a.sep = F->fuse_x ? 0 : 1;
+  a.gtab = F->gtab;
+  const double points = (double)F->P * samples;
+  if (a.Bt) {
+    double bytes = cm_bytes(points, a.K, a.N, a.bias, nullptr, nullptr, a.outpre, a.outact, 0);
+    double flops = 2.0 * points * a.K * a.N;
+    if (a.G) {
+      bytes += 2.0 * a.n * a.m2 + (double)a.lines * a.m2 * a.N * 2.0;
+      flops += 2.0 * points * a.m2 * a.N;
+    }
+    if (a.gpre) bytes += points * a.N * 2.0;
+    account(F, FK_CM, bytes, flops);
+  }
+  if (a.Gd)
+    account(F, FK_LM, 2.0 * a.n * a.m2 + 2.0 * a.lines * a.m2 * a.N + (a.Bt ? 0.0 : 2.0 * points * a.K),
+            2.0 * points * a.m2 * a.N);
+  if (a.N <= 32)
+    k_xline<1><<<gdiv(a.lines, 4), 256, 0, F->stream>>>(a);
+  else
+    k_xline<2><<<gdiv(a.lines, 4), 256, 0, F->stream>>>(a);
 }
 
 static void cm_launch(pf_fno* F, long long points, const u16* In, int ldin, int K, const u16* Bt, int N,
@@ -1270,40 +1545,95 @@ static LineTerm x_inverse(const pf_fno* F, const u16* B2) {
   return lt;
 }
 
-// forward pass for the packed input F->xin up to v_L (F->pre[layers - 1])
-static void forward_layers(pf_fno* F) {
+// Buffers of a forward pass over `B` samples.
+struct FwdBufs {
+  const u16* xin;
+  u16 *A1, *A2, *Tb, *B3, *B2;
+  float *T, *B1;
+};
+
+// One layer's spectral path from the x stage's output (A1) to the inverse y
+// stage's (B2); S: the spectrum before the mixing (f32).
+static void spectral_fwd(pf_fno* F, const FwdBufs& u, int l, int B, float* S) {
   const pf_fno_config& c = F->cfg;
   const int n = c.n, w = c.width, m = c.modes, m2 = 2 * m;
+  const int Nz = m2 * m * w;
+  const long long spec = 2LL * F->mode_count * w;
+  // y (batch sample, z), z (batch sample)
+  lm_rows(F, F->Gyf, 2 * m2, 2 * n, u.A1, (long long)n * 2 * m * w, m * w, m * w, B * n, nullptr, u.A2,
+          (long long)2 * m2 * m * w, m * w);
+  lm_rows(F, F->Gzf, 2 * m2, 2 * n, u.A2, 2LL * n * Nz, Nz, Nz, B, S, nullptr, spec, Nz);
+  account(F, FK_MIX, mix_fwd_bytes(F->mode_count, w, B), 8.0 * F->mode_count * w * w * B);
+  k_mix_fwd<<<gdiv((long long)F->mode_count * w * B, 256), 256, 0, F->stream>>>(S, F->bRr[l], F->bRi[l], u.T,
+                                                                                 F->mode_count, w, u.Tb, B);
+  lm_rows(F, F->Gzi, 2 * n, 2 * m2, u.Tb, spec, Nz, Nz, B, nullptr, u.B3, 2LL * n * Nz, Nz);
+  lm_rows(F, F->Gyi, 2 * n, 2 * m2, u.B3, (long long)2 * m2 * m * w, m * w, m * w, B * n, nullptr, u.B2,
+          (long long)2 * n * m * w, m * w);
+}
+
+// Lift and layers over B samples.  v(l): the layer's input, pre(l): where its
+// pre-activation is kept (null: not kept; the last layer's, v_L, always is),
+// S(l): its spectrum.
+template <class V, class Pre, class Sp>
+static void forward_layers(pf_fno* F, const FwdBufs& u, int B, V v, Pre pre, Sp S) {
+  const pf_fno_config& c = F->cfg;
+  const int n = c.n, w = c.width, m = c.modes;
   const float* th = F->th;
-  cm(F, F->xin, F->cinp, F->cinp, F->bWliftT, w, th + F->o_bl, nullptr, 0, nullptr, F->v[0], nullptr, w, 0);
+  const long long points = F->P * B;
+  if (F->xlines) {
+    XLineArgs a = {};
+    a.In = u.xin;
+    a.ldin = a.K = F->cinp;
+    a.N = w;
+    a.Bt = F->bWliftT;
+    a.bias = th + F->o_bl;
+    a.outpre = v(0);
+    a.Gd = F->Gxf;
+    a.A1 = u.A1;
+    xline(F, a, B);
+  } else {
+    cm_launch(F, points, u.xin, F->cinp, F->cinp, F->bWliftT, w, th + F->o_bl, nullptr, 0, nullptr, v(0), nullptr, w,
+              0, LineTerm());
+  }
   for (int l = 0; l < c.layers; ++l) {
-    const u16* v = F->v[l];
-    // forward truncated DFT: x (batch z,y), y (batch z), z
-    lm(F, F->Gxf, 2 * m, n, v, (long long)n * w, w, w, n * n, nullptr, F->A1, (long long)2 * m * w, w, 0);
-    lm(F, F->Gyf, 2 * m2, 2 * n, F->A1, (long long)n * 2 * m * w, m * w, m * w, n, nullptr, F->A2,
-       (long long)2 * m2 * m * w, m * w, 0);
-    const int Nz = m2 * m * w;
-    lm(F, F->Gzf, 2 * m2, 2 * n, F->A2, 0, Nz, Nz, 1, F->S[l], nullptr, 0, Nz, 0);
-    // per-mode mixing
-    account(F, FK_MIX, mix_fwd_bytes(F->mode_count, w, 1), 8.0 * F->mode_count * w * w);
-    k_mix_fwd<<<gdiv((long long)F->mode_count * w, 256), 256, 0, F->stream>>>(F->S[l], F->bRr[l], F->bRi[l], F->T,
-                                                                               F->mode_count, w, F->Tb, 1);
-    // inverse: z, y (batch z), x (batch z,y)
-    lm(F, F->Gzi, 2 * n, 2 * m2, F->Tb, 0, Nz, Nz, 1, nullptr, F->B3, 0, Nz, 0);
-    lm(F, F->Gyi, 2 * n, 2 * m2, F->B3, (long long)2 * m2 * m * w, m * w, m * w, n, nullptr, F->B2,
-       (long long)2 * n * m * w, m * w, 0);
-    // pointwise path, bias, the spectral part's inverse x stage (carried by the
-    // channel-mixing GEMM when a wave's points lie in one line, else through
-    // B1), activation (the last layer is linear)
-    const bool last = l == c.layers - 1;
-    if (F->fuse_x) {
-      cm(F, v, w, w, F->bWT[l], w, th + F->o_b[l], nullptr, 0, nullptr, F->pre[l], last ? nullptr : F->v[l + 1], w, 0,
-         x_inverse(F, F->B2));
+    const bool last = l == c.layers - 1;  // linear
+    if (!F->xlines)
+      lm(F, F->Gxf, 2 * m, n, v(l), (long long)n * w, w, w, B * n * n, nullptr, u.A1, (long long)2 * m * w, w, 0);
+    spectral_fwd(F, u, l, B, S(l));
+    // pointwise path, bias, the spectral part's inverse x stage, activation, and
+    // the next layer's x stage
+    if (F->xlines) {
+      XLineArgs a = {};
+      a.In = v(l);
+      a.ldin = a.K = a.N = w;
+      a.Bt = F->bWT[l];
+      a.bias = th + F->o_b[l];
+      a.G = F->Gxi;
+      a.X = u.B2;
+      a.outpre = pre(l);
+      a.outact = last ? nullptr : v(l + 1);
+      a.Gd = last ? nullptr : F->Gxf;
+      a.A1 = u.A1;
+      xline(F, a, B);
+    } else if (F->fuse_x) {
+      cm_launch(F, points, v(l), w, w, F->bWT[l], w, th + F->o_b[l], nullptr, 0, nullptr, pre(l),
+                last ? nullptr : v(l + 1), w, 0, x_inverse(F, u.B2));
     } else {
-      lm(F, F->Gxi, n, 2 * m, F->B2, (long long)2 * m * w, w, w, n * n, F->B1, nullptr, (long long)n * w, w, 0);
-      cm(F, v, w, w, F->bWT[l], w, th + F->o_b[l], F->B1, w, nullptr, F->pre[l], last ? nullptr : F->v[l + 1], w, 0);
+      lm(F, F->Gxi, n, 2 * m, u.B2, (long long)2 * m * w, w, w, B * n * n, u.B1, nullptr, (long long)n * w, w, 0);
+      cm_launch(F, points, v(l), w, w, F->bWT[l], w, th + F->o_b[l], u.B1, w, nullptr, pre(l),
+                last ? nullptr : v(l + 1), w, 0, LineTerm());
     }
   }
+}
+
+// forward pass for the packed input F->xin up to v_L (F->pre[layers - 1]);
+// keep: with the other layers' pre-activations, for the backward pass
+static void forward_layers(pf_fno* F, bool keep) {
+  const int L = F->cfg.layers;
+  const FwdBufs u = {F->xin, F->A1, F->A2, F->Tb, F->B3, F->B2, F->T, F->B1};
+  forward_layers(
+      F, u, 1, [&](int l) { return F->v[l]; },
+      [&](int l) { return keep || l == L - 1 ? F->pre[l] : (u16*)nullptr; }, [&](int l) { return F->S[l]; });
 }
 
 // the projection as GEMMs through the hidden layer (width > 32)
@@ -1317,7 +1647,7 @@ static void project_gemms(pf_fno* F) {
 
 // forward pass for the packed input F->xin; leaves the result in F->outf
 static void forward(pf_fno* F) {
-  forward_layers(F);
+  forward_layers(F, false);
   if (F->fuse_proj)
     project(F, F->pre[F->cfg.layers - 1], F->P, F->outf);
   else
@@ -1350,12 +1680,11 @@ static void loss_backward(pf_fno* F, const float* x, const float* y) {
     cm(F, F->dhb, h, h, F->bP1, w, nullptr, nullptr, 0, nullptr, db[0], nullptr, w, 0);
   }
   const int Nz = m2 * m * w;
-  // the spectral path's transposed stages from dpreb (bf16 d pre of the layer) down to A1
-  auto spectral_back = [&](int l, const u16* dpreb) {
-    lm(F, F->GxiT, 2 * m, n, dpreb, (long long)n * w, w, w, n * n, nullptr, F->B2, (long long)2 * m * w, w, 0);
-    lm(F, F->GyiT, 2 * m2, 2 * n, F->B2, (long long)2 * n * m * w, m * w, m * w, n, nullptr, F->B3,
-       (long long)2 * m2 * m * w, m * w, 0);
-    lm(F, F->GziT, 2 * m2, 2 * n, F->B3, 0, Nz, Nz, 1, F->dT, nullptr, 0, Nz, 0);
+  // the spectral path's transposed stages from the x stage's output (B2) down to A1
+  auto spectral_back = [&](int l) {
+    lm_rows(F, F->GyiT, 2 * m2, 2 * n, F->B2, (long long)2 * n * m * w, m * w, m * w, n, nullptr, F->B3,
+            (long long)2 * m2 * m * w, m * w);
+    lm_rows(F, F->GziT, 2 * m2, 2 * n, F->B3, 0, Nz, Nz, 1, F->dT, nullptr, 0, Nz);
     account(F, FK_MIX, 2.0 * F->mode_count * w * 4.0 * 2 + 2.0 * F->mode_count * (double)w * w * 8.0,
             8.0 * F->mode_count * w * w);
     account(F, FK_MIX, 2.0 * F->mode_count * w * (4.0 + 2.0) + 2.0 * F->mode_count * (double)w * w * 2.0,
@@ -1364,38 +1693,54 @@ static void loss_backward(pf_fno* F, const float* x, const float* y) {
         F->S[l], F->dT, g + F->o_Rr[l], g + F->o_Ri[l], F->mode_count, w);
     k_mix_bwd_data<<<gdiv((long long)F->mode_count * w, 256), 256, 0, F->stream>>>(F->dT, F->bRr[l], F->bRi[l],
                                                                                    F->dSb, F->mode_count, w);
-    lm(F, F->GzfT, 2 * n, 2 * m2, F->dSb, 0, Nz, Nz, 1, nullptr, F->A2, 0, Nz, 0);
-    lm(F, F->GyfT, 2 * n, 2 * m2, F->A2, (long long)2 * m2 * m * w, m * w, m * w, n, nullptr, F->A1,
-       (long long)2 * n * m * w, m * w, 0);
+    lm_rows(F, F->GzfT, 2 * n, 2 * m2, F->dSb, 0, Nz, Nz, 1, nullptr, F->A2, 0, Nz);
+    lm_rows(F, F->GyfT, 2 * n, 2 * m2, F->A2, (long long)2 * m2 * m * w, m * w, m * w, n, nullptr, F->A1,
+            (long long)2 * n * m * w, m * w);
   };
-  if (F->fuse_x) {
-    // d v_l = d pre_l W^T + (transposed x stage of A1) in one GEMM, whose
-    // epilogue applies GELU'(pre_{l-1}) to give d pre_{l-1}, ping-ponging
-    // between two buffers; the last layer is linear
-    LineTerm lt;
-    lt.G = F->GxfT;
-    lt.K = 2 * m;
-    lt.R = n;
-    lt.X = F->A1;
-    lt.xbs = (long long)2 * m * w;
-    lt.ldx = w;
-    for (int l = c.layers - 1; l >= 0; --l) {
-      wgrad(F, F->v[l], w, w, db[0], w, w, g + F->o_W[l], g + F->o_b[l]);
-      spectral_back(l, db[0]);
-      cm(F, db[0], w, w, F->bW[l], w, nullptr, nullptr, 0, nullptr, db[1], nullptr, w, 0, lt,
-         l > 0 ? F->pre[l - 1] : nullptr);
+  if (F->xlines) {
+    XLineArgs a = {};
+    a.In = db[0];
+    a.ldin = a.K = a.N = w;
+    a.Gd = F->GxiT;
+    a.A1 = F->B2;
+    xline(F, a, 1);
+  }
+  for (int l = c.layers - 1; l >= 0; --l) {
+    wgrad(F, F->v[l], w, w, db[0], w, w, g + F->o_W[l], g + F->o_b[l]);
+    if (!F->xlines)
+      lm(F, F->GxiT, 2 * m, n, db[0], (long long)n * w, w, w, n * n, nullptr, F->B2, (long long)2 * m * w, w, 0);
+    spectral_back(l);
+    // d v_l = d pre_l W^T + (transposed x stage of A1), times GELU'(pre_{l-1}) to
+    // give d pre_{l-1} (d v_0 for l = 0)
+    const u16* gp = l > 0 ? F->pre[l - 1] : nullptr;
+    if (F->xlines) {
+      XLineArgs a = {};
+      a.In = db[0];
+      a.ldin = a.K = a.N = w;
+      a.Bt = F->bW[l];
+      a.G = F->GxfT;
+      a.X = F->A1;
+      a.gpre = gp;
+      a.outpre = db[1];
+      a.Gd = l > 0 ? F->GxiT : nullptr;  // and the next spectral path's x stage
+      a.A1 = F->B2;
+      xline(F, a, 1);
       std::swap(db[0], db[1]);
-    }
-  } else {
-    for (int l = c.layers - 1; l >= 0; --l) {
-      wgrad(F, F->v[l], w, w, db[0], w, w, g + F->o_W[l], g + F->o_b[l]);
-      spectral_back(l, db[0]);
-      // pointwise data gradient plus the transposed x stage of the spectral path
+    } else if (F->fuse_x) {
+      LineTerm lt;
+      lt.G = F->GxfT;
+      lt.K = 2 * m;
+      lt.R = n;
+      lt.X = F->A1;
+      lt.xbs = (long long)2 * m * w;
+      lt.ldx = w;
+      cm(F, db[0], w, w, F->bW[l], w, nullptr, nullptr, 0, nullptr, db[1], nullptr, w, 0, lt, gp);
+      std::swap(db[0], db[1]);
+    } else {
       cm(F, db[0], w, w, F->bW[l], w, nullptr, nullptr, 0, F->dvf, nullptr, nullptr, w, 0);
       lm(F, F->GxfT, n, 2 * m, F->A1, (long long)2 * m * w, w, w, n * n, F->dvf, nullptr, (long long)n * w, w, 1);
       account(F, FK_GELU, (double)P * w * (4.0 + 2.0 + 2.0), 20.0 * P * w);
-      k_gelu_bwd<<<gdiv(P * w, 256), 256, 0, F->stream>>>(F->dvf, l > 0 ? F->pre[l - 1] : nullptr, F->gtab, db[0],
-                                                          P * w, l > 0 ? 0 : 1);
+      k_gelu_bwd<<<gdiv(P * w, 256), 256, 0, F->stream>>>(F->dvf, gp, F->gtab, db[0], P * w, l > 0 ? 0 : 1);
     }
   }
   // lift: v0 = x W_lift + b_lift (db[0]: d v0)
@@ -1424,6 +1769,7 @@ pf_status pf_fno_create(const pf_fno_config* cfg, void* stream, pf_fno** out) {
   F->mode_count = m2 * m2 * m;
   F->fuse_x = n % 32 == 0;
   F->fuse_proj = w <= 32;
+  F->xlines = w <= 64 && m <= 16;
   // parameter layout (same order as the oracle)
   long long off = 0;
   F->o_Wl = off; off += (long long)c.cin * w;
@@ -1485,13 +1831,13 @@ pf_status pf_fno_create(const pf_fno_config* cfg, void* stream, pf_fno** out) {
   A((void**)&F->T, 4 * spec);
   A((void**)&F->B3, 2 * std::max((size_t)2 * n * m2 * m * w, a2));
   A((void**)&F->B2, 2 * std::max(b2, a1));
-  if (!F->fuse_x) A((void**)&F->B1, 4 * P * w);
+  if (!F->fuse_x && !F->xlines) A((void**)&F->B1, 4 * P * w);
   A((void**)&F->outf, 4 * P * c.cout);
-  if (!F->fuse_x) A((void**)&F->dvf, 4 * P * w);
+  if (!F->fuse_x && !F->xlines) A((void**)&F->dvf, 4 * P * w);
   A((void**)&F->dT, 4 * spec);
   if (!F->fuse_proj) A((void**)&F->dhb, 2 * P * h);
   A((void**)&F->dpreb, 2 * P * w);
-  if (F->fuse_x) A((void**)&F->dpreb2, 2 * P * w);
+  if (F->fuse_x || F->xlines) A((void**)&F->dpreb2, 2 * P * w);
   if (!F->fuse_proj) A((void**)&F->douthb, 2 * P * F->coutp);
   A((void**)&F->dSb, 2 * spec);
   F->part_elems = (long long)kWgradBlocks * (std::max(std::max(w, h), 8) + 1) * std::max(std::max(w, h), 8);
@@ -1637,7 +1983,7 @@ pf_status pf_fno_grad(pf_fno* F, const float* x, const float* y, double* loss) {
   if (!F || !x || !y) return PF_ERR_ARG;
   account(F, FK_ELEM, (double)F->P * (4.0 * F->cfg.cin + 2.0 * F->cinp), 0.0);
   k_pack_input<float><<<gdiv(F->P, 256), 256, 0, F->stream>>>(x, F->P, F->cfg.cin, F->cinp, F->innorm, F->xin);
-  forward_layers(F);
+  forward_layers(F, true);
   loss_backward(F, x, y);
   FH(hipMemcpyAsync(F->hsum, F->dsum, 8, hipMemcpyDeviceToHost, F->stream));
   FH(hipGetLastError());
@@ -1781,7 +2127,7 @@ static pf_status ensure_batch(pf_fno* F, int B) {
   A((void**)&F->bTb, Bs * 2 * spec);
   A((void**)&F->bB3, Bs * 2 * 2 * n * Nz);
   A((void**)&F->bB2, Bs * 2 * a1);
-  if (!F->fuse_x) A((void**)&F->bB1, Bs * 4 * P * w);
+  if (!F->fuse_x && !F->xlines) A((void**)&F->bB1, Bs * 4 * P * w);
   if (!F->fuse_proj) A((void**)&F->bhact, Bs * 2 * P * h);
   A((void**)&F->boutf, Bs * 4 * P * c.cout);
   A((void**)&F->bdpart, Bs * 8 * gdiv(F->P, 256));
@@ -1807,37 +2153,15 @@ static void cm_points(pf_fno* F, long long points, const u16* In, int ldin, int 
 // same small GEMM, so the sums are those of the one-sample pass.
 static void forward_batch(pf_fno* F, int B) {
   const pf_fno_config& c = F->cfg;
-  const int n = c.n, w = c.width, m = c.modes, m2 = 2 * m, h = c.hidden;
+  const int w = c.width, h = c.hidden, L = c.layers;
   const long long PB = F->P * B;
-  const long long Nz = (long long)m2 * m * w, spec = 2LL * F->mode_count * w;
   const float* th = F->th;
-  cm_points(F, PB, F->bxin, F->cinp, F->cinp, F->bWliftT, w, th + F->o_bl, nullptr, 0, nullptr, F->bv0, nullptr, w);
-  u16* v = F->bv0;
-  u16* vn = F->bv1;
-  for (int l = 0; l < c.layers; ++l) {
-    lm(F, F->Gxf, 2 * m, n, v, (long long)n * w, w, w, B * n * n, nullptr, F->bA1, (long long)2 * m * w, w, 0);
-    lm(F, F->Gyf, 2 * m2, 2 * n, F->bA1, (long long)n * 2 * m * w, m * w, m * w, B * n, nullptr, F->bA2,
-       (long long)2 * m2 * m * w, m * w, 0);
-    lm(F, F->Gzf, 2 * m2, 2 * n, F->bA2, 2LL * n * Nz, (int)Nz, (int)Nz, B, F->bS, nullptr, spec, (int)Nz, 0);
-    account(F, FK_MIX, mix_fwd_bytes(F->mode_count, w, B), 8.0 * F->mode_count * w * w * B);
-    k_mix_fwd<<<gdiv((long long)F->mode_count * w * B, 256), 256, 0, F->stream>>>(F->bS, F->bRr[l], F->bRi[l],
-                                                                                   F->bT, F->mode_count, w,
-                                                                                   F->bTb, B);
-    lm(F, F->Gzi, 2 * n, 2 * m2, F->bTb, spec, (int)Nz, (int)Nz, B, nullptr, F->bB3, 2LL * n * Nz, (int)Nz, 0);
-    lm(F, F->Gyi, 2 * n, 2 * m2, F->bB3, (long long)2 * m2 * m * w, m * w, m * w, B * n, nullptr, F->bB2,
-       (long long)2 * n * m * w, m * w, 0);
-    const bool last = l == c.layers - 1;
-    if (F->fuse_x) {
-      cm_points(F, PB, v, w, w, F->bWT[l], w, th + F->o_b[l], nullptr, 0, nullptr, last ? vn : nullptr,
-                last ? nullptr : vn, w, x_inverse(F, F->bB2));
-    } else {
-      lm(F, F->Gxi, n, 2 * m, F->bB2, (long long)2 * m * w, w, w, B * n * n, F->bB1, nullptr, (long long)n * w, w,
-         0);
-      cm_points(F, PB, v, w, w, F->bWT[l], w, th + F->o_b[l], F->bB1, w, nullptr, last ? vn : nullptr,
-                last ? nullptr : vn, w);
-    }
-    std::swap(v, vn);
-  }
+  const FwdBufs u = {F->bxin, F->bA1, F->bA2, F->bTb, F->bB3, F->bB2, F->bT, F->bB1};
+  u16* vb[2] = {F->bv0, F->bv1};
+  forward_layers(
+      F, u, B, [&](int l) { return vb[l & 1]; }, [&](int l) { return l == L - 1 ? vb[(l + 1) & 1] : (u16*)nullptr; },
+      [&](int) { return F->bS; });
+  const u16* v = vb[L & 1];
   if (F->fuse_proj) {
     project(F, v, PB, F->boutf);
     return;
