@@ -544,16 +544,21 @@ __device__ inline void colfft_pipelined(int nf, int bf, bool valid, const cx<T>*
 
 template <typename T, int N, int TX, int RE, int S, int AXIS>
 __global__ void __launch_bounds__((ColGeo<N, TX, RE>::THREADS))
-k_colfft(const cx<T>* in, cx<T>* out, Geo g, int nf, const cx<T>* tw, T scale) {
+k_colfft(const cx<T>* in, cx<T>* out, Geo g, int nf, int ntile, const cx<T>* tw, T scale) {
   using CG = ColGeo<N, TX, RE>;
   __shared__ cx<T> lds[N * CG::LD];
+  int tile = xcd_tile(blockIdx.x, gridDim.x);
+  if (ntile) {  // one field per work-group
+    in += (tile / ntile) * g.fs;
+    out += (tile / ntile) * g.fs;
+    tile %= ntile;
+    nf = 1;
+  }
   if constexpr (sizeof(T) == 8) {
-    body_colfft<T, N, TX, RE, S, AXIS>(in, out, g, nf, tw, scale, xcd_tile(blockIdx.x, gridDim.x), threadIdx.x,
-                                       lds);
+    body_colfft<T, N, TX, RE, S, AXIS>(in, out, g, nf, tw, scale, tile, threadIdx.x, lds);
   } else {
     __shared__ cx<T> twl[N];
     for (int j = threadIdx.x; j < N; j += CG::THREADS) twl[j] = tw[j];
-    const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int nbx = (g.nxh + TX - 1) / TX;
     const int xb = tile % nbx;
     const int o = tile / nbx;

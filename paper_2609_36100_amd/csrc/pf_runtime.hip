@@ -165,8 +165,18 @@ static bool launch_colfft(pf_ctx* c, const cx<T>* in, cx<T>* out, int nf, T scal
           return;
         }
       }
-      k_colfft<T, N, TX, RE, S, AXIS><<<dim3(nbx * other), dim3(ColGeo<N, TX, RE>::THREADS), 0, c->stream>>>(
-          in, out, g, nf, tw<T>(c, AXIS == 1 ? 1 : 0), scale);
+      // One field per work-group where the tiles alone are few (under four work-groups
+      // per CU: 64^3 0.50 -> 0.47 ms and 32^3 0.32 -> 0.29 ms an ARK4 step) and, in
+      // FP64, where a work-group is half a CU (512^3: 111.8 -> 107.5 ms); between them
+      // a group keeps its fields (128^3: 1.82 against 1.85 ms).  FP32 lines of 128 and
+      // more keep them too: there the fields are pipelined, and the tuner's choice
+      // between this pass and the persistent one, which rounds differently, stays.
+      const int ntile = nbx * other;
+      const bool split = nf > 1 && (sizeof(T) == 8 ? ntile < 1024 || ColGeo<N, TX, RE>::THREADS >= 512
+                                                   : ntile < 1024 && N < 128);
+      k_colfft<T, N, TX, RE, S, AXIS>
+          <<<dim3(split ? ntile * nf : ntile), dim3(ColGeo<N, TX, RE>::THREADS), 0, c->stream>>>(
+              in, out, g, nf, split ? ntile : 0, tw<T>(c, AXIS == 1 ? 1 : 0), scale);
     });
   });
 }
