@@ -16,8 +16,8 @@ import time
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SRCS = [os.path.join(HERE, "csrc", f) for f in ("pf_runtime.hip", "pf_stage_fp64.hip", "pf_stage_mixed.hip", "pf_ensemble.hip",
-                                                 "pf_fno.hip")]
+SRCS = [os.path.join(HERE, "csrc", f) for f in ("pf_runtime.hip", "pf_stage_fp64.hip", "pf_stage_mixed.hip", "pf_plane.hip",
+                                                 "pf_ensemble.hip", "pf_fno.hip")]
 OUT = os.path.join(HERE, "libpf.so")
 OBJDIR = os.path.join(HERE, "_build")
 

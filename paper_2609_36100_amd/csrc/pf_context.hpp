@@ -261,6 +261,11 @@ void make_twiddles32(int n, cx<float>* host);
 // mass, volume fraction, threshold fraction and (want_F) total free energy of
 // the context's current state; F is NaN without want_F
 pf_status ctx_diagnostics(pf_ctx* c, bool want_F, double out[4]);
+// plane passes (defined in pf_plane.hip): whether a grid's planes fit in LDS; the
+// theta and driving-force passes from and to z-transformed planes
+bool plane_supported(const Geo& g);
+bool launch_plane_theta(pf_ctx* c, const cx<double>* T1, cx<double>* T3);
+bool launch_plane_drive(pf_ctx* c, const cx<double>* T1, cx<double>* T3);
 // ensemble member access (defined in pf_ensemble.hip)
 int ens_members(const pf_ens* E);
 int ens_member_n(const pf_ens* E, int m);

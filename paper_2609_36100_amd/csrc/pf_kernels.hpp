@@ -17,6 +17,9 @@
 //  ypass<-1>     forward y-FFT of the driving force                    (y pass)
 //  zpass_fwd_ac  mixed form and pf_rhs: forward z-FFT, F^E_eta = -L g~ (z pass)
 //
+// (small FP64 grids with nx == ny take the y and x passes between two z passes as
+// one, pf_plane.hpp)
+//
 // followed once per step by `finalize` (FP64: the last forward z-FFT; update,
 // embedded error, WRMS partial sums).  z and y passes give each work-group TX consecutive kx columns of one
 // plane so every global access is TX contiguous complex values; x passes give

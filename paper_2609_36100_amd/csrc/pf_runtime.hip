@@ -480,16 +480,36 @@ static pf_status run_stage(pf_ctx* c, const StepArgs<TE>& sa, int np, cx<TE>* FE
   prof_end(c, KC_STAGE, b_stage);
   const int acc = (sa.FEc_out != nullptr) ? 1 : 0;
   bool ok = true;
-  prof_begin(c);
-  ok = ok && launch_colfft<T, +1, 1>(c, T1, T1, 4, (T)1);
-  prof_end(c, KC_YFFT, 8 * fT);
   if constexpr (std::is_same<T, double>::value && std::is_same<TE, double>::value) {
     if (c->inhom) {
+      prof_begin(c);
+      ok = ok && launch_colfft<T, +1, 1>(c, T1, T1, 4, (T)1);
+      prof_end(c, KC_YFFT, 8 * fT);
       if (!ok) return PF_ERR_UNSUPPORTED_SIZE;
       pf_status s = run_rhs_inhom(c, T1, FE, acc);
       return s == PF_OK && fwd ? run_fwd_ac<T, TE>(c, FE) : s;
     }
   }
+  if constexpr (std::is_same<T, double>::value && std::is_same<TE, double>::value) {
+    if (plane_supported(c->g)) {
+      // y and x transforms of a plane together
+      prof_begin(c);
+      ok = ok && launch_plane_theta(c, T1, T3);
+      prof_end(c, KC_THETA, 6 * fT);
+      prof_begin(c);
+      ok = ok && launch_zpass_elastic<T, TE>(c, T3, FE, acc);
+      prof_end(c, KC_ELASTIC, 6 * fT + (acc ? 2 : 1) * fE);
+      prof_begin(c);
+      ok = ok && launch_plane_drive(c, T1, T3);
+      prof_end(c, KC_DRIVE, 10 * fT);
+      if (!ok) return PF_ERR_UNSUPPORTED_SIZE;
+      if (fwd) return run_fwd_ac<T, TE>(c, FE);
+      return hipGetLastError() == hipSuccess ? PF_OK : PF_ERR_HIP;
+    }
+  }
+  prof_begin(c);
+  ok = ok && launch_colfft<T, +1, 1>(c, T1, T1, 4, (T)1);
+  prof_end(c, KC_YFFT, 8 * fT);
   prof_begin(c);
   ok = ok && launch_xpass_theta<T>(c, T1, T3);
   prof_end(c, KC_THETA, 6 * fT);
