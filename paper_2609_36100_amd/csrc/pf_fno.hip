@@ -842,34 +842,58 @@ __global__ void __launch_bounds__(256, NT == 1 ? 4 : 2) k_xline(XLineArgs a) {
 }
 
 // ---- per-mode complex mixing (FP32) -------------------------------------------
-// S, T: [2][modes][w] (real block, imaginary block); R: [modes][w][w] (in, out).
-// `batches` spectra one after another (stride 2 modes w), the same weights.
-__global__ void __launch_bounds__(256)
-k_mix_fwd(const float* __restrict__ S, const u16* __restrict__ Rr, const u16* __restrict__ Ri, float* __restrict__ T,
-          int modes, int w, u16* __restrict__ Tb, int batches) {
-  const long long gid = blockIdx.x * 256LL + threadIdx.x;
-  const long long mo = (long long)modes * w;
-  if (gid >= mo * batches) return;
-  const long long bo = (gid / mo) * 2 * mo;  // this spectrum's offset
-  S += bo;
-  T += bo;
-  Tb += bo;
-  const long long id = gid % mo;
-  const long long md = id / w;
-  const int o = (int)(id % w);
-  float tr = 0.f, ti = 0.f;
-  for (int i = 0; i < w; ++i) {
-    const float sr = S[md * w + i], si = S[mo + md * w + i];
-    const float rr = bf2f(Rr[(md * w + i) * w + o]), ri = bf2f(Ri[(md * w + i) * w + o]);
-    tr += rr * sr - ri * si;
-    ti += rr * si + ri * sr;
+// S: [2][modes][w] (real block, imaginary block); R: [modes][w][w] (in, out),
+// BF16.  `batches` spectra one after another (stride 2 modes w), the same
+// weights.  Bound by reading R (28 MB a layer at width 32, 12 modes): V weights
+// per load (V = 8: 16 bytes, where w % 8 == 0).
+template <int V>
+__device__ inline void ldw(const u16* p, float (&r)[V]) {
+  if constexpr (V == 8) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(p);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r[e] = bf2f((u16)(v[e >> 1] >> (16 * (e & 1))));
+  } else {
+    r[0] = bf2f(p[0]);
   }
-  T[md * w + o] = tr;
-  T[mo + md * w + o] = ti;
-  Tb[md * w + o] = f2bf(tr);
-  Tb[mo + md * w + o] = f2bf(ti);
 }
 
+// T = R S: V outputs per thread
+template <int V>
+__global__ void __launch_bounds__(256)
+k_mix_fwd(const float* __restrict__ S, const u16* __restrict__ Rr, const u16* __restrict__ Ri, int modes, int w,
+          u16* __restrict__ Tb, int batches) {
+  const long long gid = blockIdx.x * 256LL + threadIdx.x;
+  const long long mo = (long long)modes * w, per = mo / V;
+  if (gid >= per * batches) return;
+  const long long bo = (gid / per) * 2 * mo;  // this spectrum's offset
+  S += bo;
+  Tb += bo;
+  const long long id = gid % per;
+  const long long md = id / (w / V);
+  const int o = V * (int)(id % (w / V));
+  float tr[V], ti[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) tr[e] = ti[e] = 0.f;
+  for (int i = 0; i < w; ++i) {
+    const float sr = S[md * w + i], si = S[mo + md * w + i];
+    float rr[V], ri[V];
+    ldw<V>(Rr + (md * w + i) * w + o, rr);
+    ldw<V>(Ri + (md * w + i) * w + o, ri);
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      tr[e] += rr[e] * sr - ri[e] * si;
+      ti[e] += rr[e] * si + ri[e] * sr;
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < V; ++e) {
+    Tb[md * w + o + e] = f2bf(tr[e]);
+    Tb[mo + md * w + o + e] = f2bf(ti[e]);
+  }
+}
+
+// dS = R^H dT: V weights per load
+template <int V>
 __global__ void __launch_bounds__(256)
 k_mix_bwd_data(const float* __restrict__ dT, const u16* __restrict__ Rr, const u16* __restrict__ Ri,
                u16* __restrict__ dSb, int modes, int w) {
@@ -879,11 +903,16 @@ k_mix_bwd_data(const float* __restrict__ dT, const u16* __restrict__ Rr, const u
   const int i = (int)(id % w);
   const long long mo = (long long)modes * w;
   float sr = 0.f, si = 0.f;
-  for (int o = 0; o < w; ++o) {
-    const float tr = dT[md * w + o], ti = dT[mo + md * w + o];
-    const float rr = bf2f(Rr[(md * w + i) * w + o]), ri = bf2f(Ri[(md * w + i) * w + o]);
-    sr += rr * tr + ri * ti;
-    si += rr * ti - ri * tr;
+  for (int o = 0; o < w; o += V) {
+    float rr[V], ri[V];
+    ldw<V>(Rr + (md * w + i) * w + o, rr);
+    ldw<V>(Ri + (md * w + i) * w + o, ri);
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      const float tr = dT[md * w + o + e], ti = dT[mo + md * w + o + e];
+      sr += rr[e] * tr + ri[e] * ti;
+      si += rr[e] * ti - ri[e] * tr;
+    }
   }
   dSb[md * w + i] = f2bf(sr);
   dSb[mo + md * w + i] = f2bf(si);
@@ -1203,8 +1232,8 @@ struct pf_fno {
   std::vector<u16*> v, pre;
   std::vector<float*> S;
   u16 *hpre = nullptr, *hact = nullptr;
-  u16 *A1 = nullptr, *A2 = nullptr, *A3 = nullptr, *Tb = nullptr, *B3 = nullptr, *B2 = nullptr;
-  float *T = nullptr, *B1 = nullptr, *outf = nullptr;
+  u16 *A1 = nullptr, *A2 = nullptr, *Tb = nullptr, *B3 = nullptr, *B2 = nullptr;
+  float *B1 = nullptr, *outf = nullptr;
   // backward buffers
   float *dvf = nullptr, *dT = nullptr;
   u16 *dpreb = nullptr, *dpreb2 = nullptr, *douthb = nullptr, *dhb = nullptr, *dSb = nullptr;
@@ -1219,7 +1248,7 @@ struct pf_fno {
   std::vector<void*> ballocs;
   u16 *bxin = nullptr, *bv0 = nullptr, *bv1 = nullptr, *bA1 = nullptr, *bA2 = nullptr, *bTb = nullptr, *bB3 = nullptr,
       *bB2 = nullptr, *bhact = nullptr;
-  float *bS = nullptr, *bT = nullptr, *bB1 = nullptr, *boutf = nullptr;
+  float *bS = nullptr, *bB1 = nullptr, *boutf = nullptr;
   double *bdpart = nullptr, *bdsum = nullptr;
   // ensemble surrogate advance: current, network and plain states of `ecap` members
   int ecap = 0;
@@ -1526,10 +1555,10 @@ static void refresh(pf_fno* F) {
   cvt(F->o_P2, h, c.cout, F->coutp, c.cout, 1, F->bP2);  // P2 [h][coutp]
 }
 
-// per-mode mixing of `batches` spectra: S (f32) and R (bf16) in, T (f32) and Tb (bf16) out
+// per-mode mixing of `batches` spectra: S (f32) and R (bf16) in, T (bf16) out
 static double mix_fwd_bytes(int modes, int w, int batches) {
   const double mo = (double)modes * w;
-  return batches * (2.0 * mo * 4.0 + 2.0 * mo * (4.0 + 2.0)) + 2.0 * modes * (double)w * w * 2.0;
+  return batches * (2.0 * mo * 4.0 + 2.0 * mo * 2.0) + 2.0 * modes * (double)w * w * 2.0;
 }
 
 // the inverse x stage of a layer's spectral path as a line term (B2: the
@@ -1549,7 +1578,7 @@ static LineTerm x_inverse(const pf_fno* F, const u16* B2) {
 struct FwdBufs {
   const u16* xin;
   u16 *A1, *A2, *Tb, *B3, *B2;
-  float *T, *B1;
+  float* B1;
 };
 
 // One layer's spectral path from the x stage's output (A1) to the inverse y
@@ -1564,8 +1593,12 @@ static void spectral_fwd(pf_fno* F, const FwdBufs& u, int l, int B, float* S) {
           (long long)2 * m2 * m * w, m * w);
   lm_rows(F, F->Gzf, 2 * m2, 2 * n, u.A2, 2LL * n * Nz, Nz, Nz, B, S, nullptr, spec, Nz);
   account(F, FK_MIX, mix_fwd_bytes(F->mode_count, w, B), 8.0 * F->mode_count * w * w * B);
-  k_mix_fwd<<<gdiv((long long)F->mode_count * w * B, 256), 256, 0, F->stream>>>(S, F->bRr[l], F->bRi[l], u.T,
-                                                                                 F->mode_count, w, u.Tb, B);
+  auto mix = [&](auto VC) {
+    constexpr int V = decltype(VC)::value;
+    k_mix_fwd<V><<<gdiv((long long)F->mode_count * w / V * B, 256), 256, 0, F->stream>>>(S, F->bRr[l], F->bRi[l],
+                                                                                         F->mode_count, w, u.Tb, B);
+  };
+  w % 8 == 0 ? mix(std::integral_constant<int, 8>{}) : mix(std::integral_constant<int, 1>{});
   lm_rows(F, F->Gzi, 2 * n, 2 * m2, u.Tb, spec, Nz, Nz, B, nullptr, u.B3, 2LL * n * Nz, Nz);
   lm_rows(F, F->Gyi, 2 * n, 2 * m2, u.B3, (long long)2 * m2 * m * w, m * w, m * w, B * n, nullptr, u.B2,
           (long long)2 * n * m * w, m * w);
@@ -1630,7 +1663,7 @@ static void forward_layers(pf_fno* F, const FwdBufs& u, int B, V v, Pre pre, Sp 
 // keep: with the other layers' pre-activations, for the backward pass
 static void forward_layers(pf_fno* F, bool keep) {
   const int L = F->cfg.layers;
-  const FwdBufs u = {F->xin, F->A1, F->A2, F->Tb, F->B3, F->B2, F->T, F->B1};
+  const FwdBufs u = {F->xin, F->A1, F->A2, F->Tb, F->B3, F->B2, F->B1};
   forward_layers(
       F, u, 1, [&](int l) { return F->v[l]; },
       [&](int l) { return keep || l == L - 1 ? F->pre[l] : (u16*)nullptr; }, [&](int l) { return F->S[l]; });
@@ -1691,8 +1724,11 @@ static void loss_backward(pf_fno* F, const float* x, const float* y) {
             8.0 * F->mode_count * w * w);
     k_mix_bwd_w<<<gdiv((long long)F->mode_count * w * w, 256), 256, 0, F->stream>>>(
         F->S[l], F->dT, g + F->o_Rr[l], g + F->o_Ri[l], F->mode_count, w);
-    k_mix_bwd_data<<<gdiv((long long)F->mode_count * w, 256), 256, 0, F->stream>>>(F->dT, F->bRr[l], F->bRi[l],
-                                                                                   F->dSb, F->mode_count, w);
+    auto mix = [&](auto VC) {
+      k_mix_bwd_data<decltype(VC)::value><<<gdiv((long long)F->mode_count * w, 256), 256, 0, F->stream>>>(
+          F->dT, F->bRr[l], F->bRi[l], F->dSb, F->mode_count, w);
+    };
+    w % 8 == 0 ? mix(std::integral_constant<int, 8>{}) : mix(std::integral_constant<int, 1>{});
     lm_rows(F, F->GzfT, 2 * n, 2 * m2, F->dSb, 0, Nz, Nz, 1, nullptr, F->A2, 0, Nz);
     lm_rows(F, F->GyfT, 2 * n, 2 * m2, F->A2, (long long)2 * m2 * m * w, m * w, m * w, n, nullptr, F->A1,
             (long long)2 * n * m * w, m * w);
@@ -1826,9 +1862,7 @@ pf_status pf_fno_create(const pf_fno_config* cfg, void* stream, pf_fno** out) {
   const size_t a1 = (size_t)n * n * 2 * m * w, a2 = (size_t)n * 2 * m2 * m * w, b2 = (size_t)n * 2 * n * m * w;
   A((void**)&F->A1, 2 * std::max(a1, b2));
   A((void**)&F->A2, 2 * std::max(a2, (size_t)2 * n * m2 * m * w));
-  A((void**)&F->A3, 2 * spec);
   A((void**)&F->Tb, 2 * spec);
-  A((void**)&F->T, 4 * spec);
   A((void**)&F->B3, 2 * std::max((size_t)2 * n * m2 * m * w, a2));
   A((void**)&F->B2, 2 * std::max(b2, a1));
   if (!F->fuse_x && !F->xlines) A((void**)&F->B1, 4 * P * w);
@@ -2123,7 +2157,6 @@ static pf_status ensure_batch(pf_fno* F, int B) {
   A((void**)&F->bA1, Bs * 2 * a1);
   A((void**)&F->bA2, Bs * 2 * 2 * n * Nz);
   A((void**)&F->bS, Bs * 4 * spec);
-  A((void**)&F->bT, Bs * 4 * spec);
   A((void**)&F->bTb, Bs * 2 * spec);
   A((void**)&F->bB3, Bs * 2 * 2 * n * Nz);
   A((void**)&F->bB2, Bs * 2 * a1);
@@ -2156,7 +2189,7 @@ static void forward_batch(pf_fno* F, int B) {
   const int w = c.width, h = c.hidden, L = c.layers;
   const long long PB = F->P * B;
   const float* th = F->th;
-  const FwdBufs u = {F->bxin, F->bA1, F->bA2, F->bTb, F->bB3, F->bB2, F->bT, F->bB1};
+  const FwdBufs u = {F->bxin, F->bA1, F->bA2, F->bTb, F->bB3, F->bB2, F->bB1};
   u16* vb[2] = {F->bv0, F->bv1};
   forward_layers(
       F, u, B, [&](int l) { return vb[l & 1]; }, [&](int l) { return l == L - 1 ? vb[(l + 1) & 1] : (u16*)nullptr; },
