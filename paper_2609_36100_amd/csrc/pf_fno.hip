@@ -690,7 +690,7 @@ k_lm_rows(const u16* __restrict__ G, int R, int K, const u16* __restrict__ X, lo
 // activations are not read again for it (134 MB per layer at 128^3) nor
 // gathered 2 bytes at a time.  With k_lm_rows it took an advance of two 128^3
 // samples from 3.34 to 2.18 ms, a gradient over four from 21.2 to 16.9 ms.  Bt == nullptr: only the x stage of In.
-// sep: the inverse x stage is summed apart and added last (the order of the
+// SEP: the inverse x stage is summed apart and added last (the order of the
 // unfused path, which grids that 32 does not divide took).
 // K, N <= 32 NT, N % 4 == 0, n % 8 == 0, 2m <= 32.
 struct XLineArgs {
@@ -699,7 +699,7 @@ struct XLineArgs {
   const u16* Bt;       // [N][K]
   const float* bias;
   const u16 *G, *X;    // [n][2m]; [line][2m][N] (null: no line term)
-  int m2, sep;         // 2m
+  int m2;              // 2m
   const u16* gpre;     // [point][N]
   const float* gtab;
   u16 *outpre, *outact;
@@ -709,8 +709,8 @@ struct XLineArgs {
   long long lines;
 };
 
-template <int NT>
-__global__ void __launch_bounds__(256, NT == 1 ? 4 : 2) k_xline(XLineArgs a) {
+template <int NT, bool SEP>
+__global__ void __launch_bounds__(256, NT == 1 ? (SEP ? 3 : 4) : 2) k_xline(XLineArgs a) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 31, lg = lane >> 5;
   const long long line = (long long)blockIdx.x * 4 + wave;
   if (line >= a.lines) return;  // no block-level synchronisation in this kernel
@@ -744,17 +744,38 @@ __global__ void __launch_bounds__(256, NT == 1 ? 4 : 2) k_xline(XLineArgs a) {
   u32x4 id[2];
 #pragma unroll
   for (int s = 0; s < 2; ++s) id[s] = identity_operand(s, lr, lg);
+  // the next 32 points' channels are loaded while these are worked on
+  auto point = [&](int x0) { return line * n + (x0 + lr < n ? x0 + lr : 0); };
+  u32x4 vn[2 * NT];
+#pragma unroll
+  for (int s = 0; s < 2 * NT; ++s) vn[s] = ld8(a.In + point(0) * a.ldin, 16 * s + 8 * lg, K, in16);
   for (int x0 = 0; x0 < n; x0 += 32) {
     const bool in = x0 + lr < n;
-    const long long p = line * n + (in ? x0 + lr : 0);
+    const long long p = point(x0);
     u32x4 src[NT][2];  // what the x stage contracts (lane = point)
     u32x4 vin[2 * NT];
 #pragma unroll
-    for (int s = 0; s < 2 * NT; ++s) vin[s] = ld8(a.In + p * a.ldin, 16 * s + 8 * lg, K, in16);
-    if (a.Bt) {
-      f32x16 acc[NT], acx[NT];
+    for (int s = 0; s < 2 * NT; ++s) vin[s] = vn[s];
+    if (x0 + 32 < n) {
 #pragma unroll
-      for (int t = 0; t < NT; ++t) acc[t] = acx[t] = zero16();
+      for (int s = 0; s < 2 * NT; ++s) vn[s] = ld8(a.In + point(x0 + 32) * a.ldin, 16 * s + 8 * lg, K, in16);
+    }
+    if (a.Bt) {
+      u32x2 gp[NT][4];
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int c = t * 32 + 8 * q + 4 * lg;
+          gp[t][q] = u32x2{0, 0};
+          if (a.gpre && c < N) gp[t][q] = *reinterpret_cast<const u32x2*>(a.gpre + p * N + c);
+        }
+      f32x16 acc[NT], acx[SEP ? NT : 1];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        acc[t] = zero16();
+        if constexpr (SEP) acx[t] = zero16();
+      }
 #pragma unroll
       for (int s = 0; s < 2 * NT; ++s)
         if (16 * s < K) {
@@ -768,7 +789,7 @@ __global__ void __launch_bounds__(256, NT == 1 ? 4 : 2) k_xline(XLineArgs a) {
             const u32x4 g = in ? ld8(a.G + (x0 + lr) * m2, 16 * s + 8 * lg, m2, g16) : u32x4{0, 0, 0, 0};
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-              if (a.sep)
+              if constexpr (SEP)
                 acx[t] = mfma32(xt[t][s], g, acx[t]);
               else
                 acc[t] = mfma32(xt[t][s], g, acc[t]);
@@ -783,13 +804,11 @@ __global__ void __launch_bounds__(256, NT == 1 ? 4 : 2) k_xline(XLineArgs a) {
           const int c = t * 32 + 8 * q + 4 * lg;
           if (c >= N) continue;
           const f32x4 bb = a.bias ? *reinterpret_cast<const f32x4*>(a.bias + c) : f32x4{0.f, 0.f, 0.f, 0.f};
-          u32x2 gp = {0, 0};
-          if (a.gpre) gp = *reinterpret_cast<const u32x2*>(a.gpre + p * N + c);
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             float r = v[4 * q + j] + bb[j];
-            if (a.sep) r += acx[t][4 * q + j];
-            if (a.gpre) r *= a.gtab[(gp[j >> 1] >> (16 * (j & 1))) & 0xffffu];
+            if constexpr (SEP) r += acx[t][4 * q + j];
+            if (a.gpre) r *= a.gtab[(gp[t][q][j >> 1] >> (16 * (j & 1))) & 0xffffu];
             v[4 * q + j] = r;
           }
         }
@@ -802,7 +821,10 @@ __global__ void __launch_bounds__(256, NT == 1 ? 4 : 2) k_xline(XLineArgs a) {
         }
         if (a.outact) {
 #pragma unroll
-          for (int i = 0; i < 16; ++i) v[i] = gelu_f(v[i]);
+          for (int i = 0; i < 16; ++i) {
+            v[i] = gelu_f(v[i]);
+            if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // four erfs in flight: registers
+          }
           to_operand(v, src[t]);
           if (in) {
 #pragma unroll
@@ -1386,7 +1408,6 @@ static void xline(pf_fno* F, XLineArgs a, long long samples) {
   a.m2 = 2 * c.modes;
   a.n = c.n;
   a.lines = samples * c.n * c.n;
-  a.sep = F->fuse_x ? 0 : 1;
   a.gtab = F->gtab;
   const double points = (double)F->P * samples;
   if (a.Bt) {
@@ -1402,10 +1423,11 @@ static void xline(pf_fno* F, XLineArgs a, long long samples) {
   if (a.Gd)
     account(F, FK_LM, 2.0 * a.n * a.m2 + 2.0 * a.lines * a.m2 * a.N + (a.Bt ? 0.0 : 2.0 * points * a.K),
             2.0 * points * a.m2 * a.N);
+  const unsigned grid = gdiv(a.lines, 4);
   if (a.N <= 32)
-    k_xline<1><<<gdiv(a.lines, 4), 256, 0, F->stream>>>(a);
+    F->fuse_x ? k_xline<1, false><<<grid, 256, 0, F->stream>>>(a) : k_xline<1, true><<<grid, 256, 0, F->stream>>>(a);
   else
-    k_xline<2><<<gdiv(a.lines, 4), 256, 0, F->stream>>>(a);
+    F->fuse_x ? k_xline<2, false><<<grid, 256, 0, F->stream>>>(a) : k_xline<2, true><<<grid, 256, 0, F->stream>>>(a);
 }
 
 static void cm_launch(pf_fno* F, long long points, const u16* In, int ldin, int K, const u16* Bt, int N,
