@@ -207,8 +207,8 @@ __global__ void __launch_bounds__(EB) kb_drive(const EMemb<T, TE>* mem, const ES
   switch (e.g.nz) {
 #define PF_C(N)                                                                                        \
   case N:                                                                                              \
-    body_xpass_drive<T, N / 2, ens_rb(EB, N / 2), true>(e.T1, e.T3, e.g, e.mk, e.twN, e.twM, tile,    \
-                                                         threadIdx.x, lds);                            \
+    body_xpass_drive<T, N / 2, ens_rb(EB, N / 2), true, RowGeo<N / 2, ens_rb(EB, N / 2)>::SYNC_PLAIN>( \
+        e.T1, e.T3, e.g, e.mk, e.twN, e.twM, tile, threadIdx.x, lds);                                  \
     break;
     PF_ENS_SIZES(PF_C)
 #undef PF_C

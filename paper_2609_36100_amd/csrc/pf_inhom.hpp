@@ -272,7 +272,7 @@ k_el_strain(const cx<double>* __restrict__ e6, double* __restrict__ r6, Geo g, c
   double dmax = 0.0;
   for (int f = 0; f < 6; ++f) {
     cx<double> a[RG::R0];
-    row_c2r<double, M, RB>(e6 + f * g.fs + rr * g.P, rvalid, a, bf, rbuf, twN, twM);
+    row_c2r<double, M, RB, RG::SYNC_PLAIN>(e6 + f * g.fs + rr * g.P, rvalid, a, bf, rbuf, twN, twM);
     if (rvalid) {
       cx<double>* dst = reinterpret_cast<cx<double>*>(r6 + ((long long)f * nrows + rr) * (2 * M));
 #pragma unroll
@@ -314,7 +314,7 @@ __device__ inline void row_eta3(const cx<double>* st, long long rb, bool rvalid,
   // memory), one transform at a time
 #pragma unroll
   for (int v = 0; v < 3; ++v) {
-    row_c2r<double, M, RB>(st + (1 + v) * g.fs + rb, rvalid, et[v], bf, rbuf, twN, twM);
+    row_c2r<double, M, RB, RowGeo<M, RB>::SYNC_PLAIN>(st + (1 + v) * g.fs + rb, rvalid, et[v], bf, rbuf, twN, twM);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -345,7 +345,7 @@ k_el_local(const cx<double>* __restrict__ st, double* __restrict__ lc6, Geo g, M
   cx<double> th[3][RG::R0];
 #pragma unroll
   for (int v = 0; v < 3; ++v) {
-    row_c2r<double, M, RB>(st + (1 + v) * g.fs + rr * g.P, rvalid, th[v], bf, rbuf, twN, twM);
+    row_c2r<double, M, RB, RG::SYNC_PLAIN>(st + (1 + v) * g.fs + rr * g.P, rvalid, th[v], bf, rbuf, twN, twM);
     __builtin_amdgcn_sched_barrier(0);
   }
   if (!rvalid) return;
@@ -412,7 +412,7 @@ k_el_tau(const double* __restrict__ lc6, const double* __restrict__ r6, cx<doubl
       a[t] = mk(A.re - d11.re * uj.re - d12.re * (uk.re + ul.re), A.im - d11.im * uj.im - d12.im * (uk.im + ul.im));
       if (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // four points' loads in flight at a time
     }
-    row_r2c<double, M, RB>(a, e6 + c * g.fs + rb, rvalid, bf, rbuf, twN, twM);
+    row_r2c<double, M, RB, RG::SYNC_PLAIN>(a, e6 + c * g.fs + rb, rvalid, bf, rbuf, twN, twM);
   }
 #pragma unroll 1
   for (int c = 3; c < 6; ++c) {
@@ -423,7 +423,7 @@ k_el_tau(const double* __restrict__ lc6, const double* __restrict__ r6, cx<doubl
       const cx<double> d44 = ld(lc + 5 * npair, q), u = ld(s6 + c * npair, q);
       a[t] = mk(-2.0 * d44.re * u.re, -2.0 * d44.im * u.im);
     }
-    row_r2c<double, M, RB>(a, e6 + c * g.fs + rb, rvalid, bf, rbuf, twN, twM);
+    row_r2c<double, M, RB, RG::SYNC_PLAIN>(a, e6 + c * g.fs + rb, rvalid, bf, rbuf, twN, twM);
   }
 }
 
@@ -473,7 +473,7 @@ k_el_drive(const cx<double>* __restrict__ st, const double* __restrict__ r6, cx<
   cx<double> chi[RG::R0];
   {
     cx<double> a[RG::R0];
-    row_c2r<double, M, RB>(st + rb, rvalid, a, bf, rbuf, twN, twM);
+    row_c2r<double, M, RB, RG::SYNC_PLAIN>(st + rb, rvalid, a, bf, rbuf, twN, twM);
 #pragma unroll
     for (int t = 0; t < RG::R0; ++t) {
       const double c0 = a[t].re, c1 = a[t].im;
@@ -515,7 +515,7 @@ k_el_drive(const cx<double>* __restrict__ st, const double* __restrict__ r6, cx<
   }
 #pragma unroll
   for (int v = 0; v < 3; ++v) {
-    row_r2c<double, M, RB>(et[v], el + v * g.fs + rb, rvalid, bf, rbuf, twN, twM);
+    row_r2c<double, M, RB, RG::SYNC_PLAIN>(et[v], el + v * g.fs + rb, rvalid, bf, rbuf, twN, twM);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
