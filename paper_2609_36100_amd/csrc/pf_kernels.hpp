@@ -1001,10 +1001,10 @@ __device__ inline void body_xpass_theta(const cx<T>* st, cx<T>* th, const Geo& g
   const long long rb = (long long)(rvalid ? row : 0) * g.P;
   for (int v = 0; v < 3; ++v) {
     cx<T> a[RG::R0];
-    row_c2r<T, M, RB, RG::SYNC_PLAIN>(st + (1 + v) * g.fs + rb, rvalid, a, bf, rbuf, twN, twM, act);
+    row_c2r<T, M, RB, RG::SYNC>(st + (1 + v) * g.fs + rb, rvalid, a, bf, rbuf, twN, twM, act);
 #pragma unroll
     for (int t = 0; t < RG::R0; ++t) a[t] = mk<T>(hfun(a[t].re), hfun(a[t].im));
-    row_r2c<T, M, RB, RG::SYNC_PLAIN>(a, th + v * g.fs + rb, rvalid, bf, rbuf, twN, twM, act);
+    row_r2c<T, M, RB, RG::SYNC>(a, th + v * g.fs + rb, rvalid, bf, rbuf, twN, twM, act);
   }
 }
 
