@@ -22,10 +22,9 @@
 //   x theta -> y, z forward (3)            theta~
 //   k_el_start        theta~ -> Gamma0 C0 eps*(theta~) into E6, F^E_c
 //   x_el_local        T1 eta -> LC6 (the polarisation's per-point coefficients)
-//   z, y inverse (6) -> x_el_strain        R6 = eps_u
-//   repeat:  x_el_tau (LC6, R6 -> E6), y forward (6), k_el_zgamma (z forward,
-//            Gamma0, z inverse), y inverse (6), x_el_strain (E6 -> R6, largest
-//            change)
+//   z, y inverse (6) -> k_el_strain        R6 = eps_u, and tau~ rows (R6, LC6 -> E6)
+//   repeat:  y forward (6), k_el_zgamma (z forward, Gamma0, z inverse), y inverse
+//            (6), k_el_strain (E6 -> R6, largest change; tau~ rows of the next)
 //   x_el_drive (T1, R6 -> T3 g) -> y forward, z forward to F^E_eta
 #pragma once
 
@@ -155,8 +154,6 @@ __device__ inline void atomic_max_nonneg(double* mx, double v) {
   atomicMax(reinterpret_cast<unsigned long long*>(mx), (unsigned long long)__double_as_longlong(v));
 }
 
-__global__ void k_el_zero(double* p) { *p = 0.0; }
-
 }  // namespace
 
 // One update's Green-operator step fused with its z transforms, per column
@@ -167,8 +164,9 @@ __global__ void k_el_zero(double* p) { *p = 0.0; }
 // field and thread); columns past nxh transform zeros and store nothing.
 template <int N, int TX, int RE>
 __global__ void __launch_bounds__((ColGeo<N, TX, RE>::THREADS))
-k_el_zgamma(cx<double>* __restrict__ e6, Geo g, ModelK m, const cx<double>* twz, double scale) {
+k_el_zgamma(cx<double>* __restrict__ e6, Geo g, ModelK m, const cx<double>* twz, double scale, double* mx) {
   using CG = ColGeo<N, TX, RE>;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *mx = 0.0;  // for this update's strain
   __shared__ cx<double> lds[N * CG::LD];
   __shared__ cx<double> twl[N];
   for (int j = threadIdx.x; j < N; j += CG::THREADS) twl[j] = twz[j];
@@ -254,35 +252,93 @@ k_el_zgamma(cx<double>* __restrict__ e6, Geo g, ModelK m, const cx<double>* twz,
 // Real strain rows from the six inverse-transformed spectra (c2r of each row),
 // written to r6 (pitch nx per row, field stride nx ny nz); with mx, the
 // largest change of any component against the values r6 held before is
-// merged into *mx.
-template <int M, int RB>
+// merged into *mx.  With TAU also the next update's polarisation rows: from the
+// strain while it is in registers and the per-point coefficients lc6
+// (k_el_local), r2c of each of the six tensor components into e6, row for row
+// over the spectra just read.  Every update but the last one needs them, and
+// the last is known only after its strain, so they are made with each strain:
+// a row's strain is not read back for them (600 -> 500 MB per update at 128^3,
+// where a strain and a polarisation pass took 54.8 + 71.8 us and this one takes
+// 99 us, 5.0 TB/s).  The three normal components are held together (each tau_j
+// needs all three); the shear ones pass one at a time.
+template <int M, int RB, bool TAU>
 __global__ void __launch_bounds__((RowGeo<M, RB>::THREADS))
-k_el_strain(const cx<double>* __restrict__ e6, double* __restrict__ r6, Geo g, const cx<double>* twN,
-            const cx<double>* twM, double* mx) {
+k_el_strain(cx<double>* __restrict__ e6, double* __restrict__ r6, const double* __restrict__ lc6, Geo g,
+            const cx<double>* twN, const cx<double>* twM, double* mx) {
   using RG = RowGeo<M, RB>;
   __shared__ cx<double> lds[RB * RG::LD];
+  __shared__ cx<double> tM[M], tN[M];
   __shared__ double wmax[RG::THREADS / 64 + 1];
+  for (int j = threadIdx.x; j < M; j += RG::THREADS) {
+    tM[j] = twM[j];
+    tN[j] = twN[j];
+  }
   const int rl = threadIdx.x / RG::TL;
   const int bf = threadIdx.x % RG::TL;
   const int row = blockIdx.x * RB + rl;
   const int nrows = g.nz * g.ny;
   const bool rvalid = row < nrows;
   cx<double>* rbuf = lds + rl * RG::LD;
-  const long long rr = rvalid ? row : 0;
+  const long long rr = rvalid ? row : 0;  // rows past the end read row 0 and store nothing
+  const long long rb = rr * g.P;
+  const long long npair = (long long)nrows * M;
+  cx<double>* s6 = reinterpret_cast<cx<double>*>(r6);
+  const cx<double>* lc = reinterpret_cast<const cx<double>*>(lc6);
+  const uint32_t q0 = (uint32_t)(rr * M) + bf;
   double dmax = 0.0;
-  for (int f = 0; f < 6; ++f) {
-    cx<double> a[RG::R0];
-    row_c2r<double, M, RB, RG::SYNC_PLAIN>(e6 + f * g.fs + rr * g.P, rvalid, a, bf, rbuf, twN, twM);
+  __syncthreads();  // the tables
+  auto strain = [&](int f, cx<double>* a) {
+    cx<double>* dst = s6 + f * npair;
+    row_c2r<double, M, RB, RG::SYNC>(e6 + f * g.fs + rb, rvalid, a, bf, rbuf, tN, tM);
     if (rvalid) {
-      cx<double>* dst = reinterpret_cast<cx<double>*>(r6 + ((long long)f * nrows + rr) * (2 * M));
 #pragma unroll
       for (int t = 0; t < RG::R0; ++t) {
+        cx<double>& d = at32(dst, q0 + t * RG::TL);
         if (mx) {
-          const cx<double> old = dst[bf + t * RG::TL];
+          const cx<double> old = d;
           dmax = fmax(dmax, fmax(fabs(a[t].re - old.re), fabs(a[t].im - old.im)));
         }
-        dst[bf + t * RG::TL] = a[t];
+        d = a[t];
       }
+    }
+  };
+  if constexpr (TAU) {
+    cx<double> u[3][RG::R0];
+#pragma unroll
+    for (int f = 0; f < 3; ++f) {
+      strain(f, u[f]);
+      __builtin_amdgcn_sched_barrier(0);  // one transform at a time
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const int k = (c + 1) % 3, l = (c + 2) % 3;
+      cx<double> a[RG::R0];
+#pragma unroll
+      for (int t = 0; t < RG::R0; ++t) {
+        const uint32_t q = q0 + t * RG::TL;
+        const cx<double> A = at32(lc + c * npair, q), d11 = at32(lc + 3 * npair, q), d12 = at32(lc + 4 * npair, q);
+        a[t] = mk(A.re - d11.re * u[c][t].re - d12.re * (u[k][t].re + u[l][t].re),
+                  A.im - d11.im * u[c][t].im - d12.im * (u[k][t].im + u[l][t].im));
+        if (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // four points' loads in flight at a time
+      }
+      row_r2c<double, M, RB, RG::SYNC>(a, e6 + c * g.fs + rb, rvalid, bf, rbuf, tN, tM);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll 1
+    for (int f = 3; f < 6; ++f) {
+      cx<double> a[RG::R0];
+      strain(f, a);
+#pragma unroll
+      for (int t = 0; t < RG::R0; ++t) {
+        const cx<double> d44 = at32(lc + 5 * npair, q0 + t * RG::TL);
+        a[t] = mk(-2.0 * d44.re * a[t].re, -2.0 * d44.im * a[t].im);
+      }
+      row_r2c<double, M, RB, RG::SYNC>(a, e6 + f * g.fs + rb, rvalid, bf, rbuf, tN, tM);
+    }
+  } else {
+    for (int f = 0; f < 6; ++f) {
+      cx<double> a[RG::R0];
+      strain(f, a);
     }
   }
   if (mx) {
@@ -374,56 +430,6 @@ k_el_local(const cx<double>* __restrict__ st, double* __restrict__ lc6, Geo g, M
     }
 #pragma unroll
     for (int f = 0; f < 6; ++f) out[f * npair + bf + t * RG::TL] = mk(o[0][f], o[1][f]);
-  }
-}
-
-// Polarisation rows from the real strain r6 and the per-point coefficients
-// lc6 (k_el_local), r2c of each of the six tensor components into e6.  Fields
-// are addressed as a uniform base plus a 32-bit pair index.
-template <int M, int RB>
-__global__ void __launch_bounds__((RowGeo<M, RB>::THREADS))
-k_el_tau(const double* __restrict__ lc6, const double* __restrict__ r6, cx<double>* __restrict__ e6, Geo g,
-         const cx<double>* twN, const cx<double>* twM) {
-  using RG = RowGeo<M, RB>;
-  __shared__ cx<double> lds[RB * RG::LD];
-  const int rl = threadIdx.x / RG::TL;
-  const int bf = threadIdx.x % RG::TL;
-  const int row = blockIdx.x * RB + rl;
-  const int nrows = g.nz * g.ny;
-  const bool rvalid = row < nrows;
-  cx<double>* rbuf = lds + rl * RG::LD;
-  const long long rr = rvalid ? row : 0;
-  const long long rb = rr * g.P;
-  const long long npair = (long long)nrows * M;
-  const cx<double>* s6 = reinterpret_cast<const cx<double>*>(r6);
-  const cx<double>* lc = reinterpret_cast<const cx<double>*>(lc6);
-  const uint32_t q0 = (uint32_t)(rr * M) + bf;
-  // rows past the end read row 0 (rr = 0; in bounds) and store nothing
-  auto ld = [&](const cx<double>* f, uint32_t q) { return at32(f, q); };
-#pragma unroll 1
-  for (int c = 0; c < 3; ++c) {
-    const int k = c == 2 ? 0 : c + 1, l = c == 0 ? 2 : c - 1;
-    cx<double> a[RG::R0];
-#pragma unroll
-    for (int t = 0; t < RG::R0; ++t) {
-      const uint32_t q = q0 + t * RG::TL;
-      const cx<double> A = ld(lc + c * npair, q), d11 = ld(lc + 3 * npair, q), d12 = ld(lc + 4 * npair, q);
-      const cx<double> uj = ld(s6 + c * npair, q), uk = ld(s6 + k * npair, q), ul = ld(s6 + l * npair, q);
-      a[t] = mk(A.re - d11.re * uj.re - d12.re * (uk.re + ul.re), A.im - d11.im * uj.im - d12.im * (uk.im + ul.im));
-      if (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // four points' loads in flight at a time
-    }
-    row_r2c<double, M, RB, RG::SYNC_PLAIN>(a, e6 + c * g.fs + rb, rvalid, bf, rbuf, twN, twM);
-  }
-#pragma unroll 1
-  for (int c = 3; c < 6; ++c) {
-    cx<double> a[RG::R0];
-#pragma unroll
-    for (int t = 0; t < RG::R0; ++t) {
-      const uint32_t q = q0 + t * RG::TL;
-      const cx<double> d44 = ld(lc + 5 * npair, q), u = ld(s6 + c * npair, q);
-      a[t] = mk(-2.0 * d44.re * u.re, -2.0 * d44.im * u.im);
-    }
-    row_r2c<double, M, RB, RG::SYNC_PLAIN>(a, e6 + c * g.fs + rb, rvalid, bf, rbuf, twN, twM);
   }
 }
 

@@ -310,16 +310,14 @@ static bool launch_el_rows(pf_ctx* c, const cx<double>* T1, cx<double>* out, dou
     constexpr int M = decltype(MC)::value;
     // 128-thread groups for the drive and local-coefficient kernels (0.64 ->
     // 0.58 ms and 0.27 -> 0.26 ms at 256^3), 256-thread ones for the strain
-    // kernel (5 % slower at 128), the update and the energy sums
+    // (5 % slower with 128) and the energy sums
     constexpr int RB = (K == 2 || K == 4) ? rb_x(M) : rb_of(M);
     const int nb = (g.nz * g.ny + RB - 1) / RB;
     const dim3 blk(RowGeo<M, RB>::THREADS);
     const cx<double>* twN = tw<double>(c, 3);
     const cx<double>* twM = tw<double>(c, 2);
-    if constexpr (K == 0)
-      k_el_strain<M, RB><<<nb, blk, 0, c->stream>>>(c->E6, c->R6, g, twN, twM, mx);
-    else if constexpr (K == 1)
-      k_el_tau<M, RB><<<nb, blk, 0, c->stream>>>(c->LC6, c->R6, c->E6, g, twN, twM);
+    if constexpr (K == 0 || K == 1)  // the strain; with the next update's polarisation
+      k_el_strain<M, RB, K == 1><<<nb, blk, 0, c->stream>>>(c->E6, c->R6, c->LC6, g, twN, twM, mx);
     else if constexpr (K == 4)
       k_el_local<M, RB><<<nb, blk, 0, c->stream>>>(T1, c->LC6, g, c->mk, twN, twM);
     else if constexpr (K == 2)
@@ -343,7 +341,7 @@ static bool launch_el_zgamma(pf_ctx* c, double scale) {
     constexpr int TX = el_ztx(N);
     const int nbx = (g.nxh + TX - 1) / TX;
     k_el_zgamma<N, TX, 4><<<dim3(nbx * g.ny), dim3(ColGeo<N, TX, 4>::THREADS), 0, c->stream>>>(
-        c->E6, g, c->mk, tw<double>(c, 0), scale);
+        c->E6, g, c->mk, tw<double>(c, 0), scale, c->elmax);
   });
 }
 
@@ -371,8 +369,9 @@ static pf_status el_solve(pf_ctx* c, cx<double>* T1, cx<double>* FE0, int accumu
   const int kgrid = (int)std::min<long long>((modes + 255) / 256, 16384);
   const double s = c->mk.inv_n3;
   bool ok = true;
-  // E6 spectra -> R6 real strain (the z inverse only with `zinv`)
-  auto back = [&](double* mx, bool zinv) {
+  // E6 spectra -> R6 real strain (the z inverse only with `zinv`); with `tau`
+  // also the next update's polarisation rows in E6
+  auto back = [&](double* mx, bool zinv, bool tau) {
     if (zinv) {
       prof_begin(c);
       ok = ok && launch_colfft<double, +1, 2>(c, c->E6, c->E6, 6, s);
@@ -382,8 +381,13 @@ static pf_status el_solve(pf_ctx* c, cx<double>* T1, cx<double>* FE0, int accumu
     ok = ok && launch_colfft<double, +1, 1>(c, c->E6, c->E6, 6, 1.0);
     prof_end(c, KC_YFFT, 12 * fk);
     prof_begin(c);
-    ok = ok && launch_el_rows<0>(c, nullptr, nullptr, mx);
-    prof_end(c, KC_EL_STRAIN, 6 * fk + (mx ? 12 : 6) * fr);
+    if (tau) {
+      ok = ok && launch_el_rows<1>(c, nullptr, nullptr, mx);
+      prof_end(c, KC_EL_TAU, 12 * fk + (mx ? 18 : 12) * fr);
+    } else {
+      ok = ok && launch_el_rows<0>(c, nullptr, nullptr, mx);
+      prof_end(c, KC_EL_STRAIN, 6 * fk + (mx ? 12 : 6) * fr);
+    }
   };
   prof_begin(c);
   ok = ok && launch_xpass_theta<double>(c, T1, T3);
@@ -400,12 +404,9 @@ static pf_status el_solve(pf_ctx* c, cx<double>* T1, cx<double>* FE0, int accumu
   prof_begin(c);
   ok = ok && launch_el_rows<4>(c, T1, nullptr, nullptr);
   prof_end(c, KC_EL_LOCAL, 3 * fk + 6 * fr);
-  back(nullptr, true);
+  back(nullptr, true, c->p.el_max_iter > 0);
   int it = 0;
   while (ok && it < c->p.el_max_iter) {
-    prof_begin(c);
-    ok = ok && launch_el_rows<1>(c, T1, nullptr, nullptr);
-    prof_end(c, KC_EL_TAU, 6 * fk + 12 * fr);  // coefficients and strain read, six spectra written
     prof_begin(c);
     ok = ok && launch_colfft<double, -1, 1>(c, c->E6, c->E6, 6, 1.0);
     prof_end(c, KC_YFFT, 12 * fk);
@@ -413,9 +414,8 @@ static pf_status el_solve(pf_ctx* c, cx<double>* T1, cx<double>* FE0, int accumu
     prof_begin(c);
     ok = ok && launch_el_zgamma(c, s);
     prof_end(c, KC_EL_ZGAMMA, 12 * fk);
-    k_el_zero<<<1, 1, 0, c->stream>>>(c->elmax);
-    back(c->elmax, false);
     ++it;
+    back(c->elmax, false, it < c->p.el_max_iter);
     if (!ok) break;
     PF_HIP(hipMemcpyAsync(&c->host_red[6], c->elmax, sizeof(double), hipMemcpyDeviceToHost, c->stream));
     PF_HIP(hipStreamSynchronize(c->stream));
