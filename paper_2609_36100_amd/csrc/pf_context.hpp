@@ -211,6 +211,7 @@ struct pf_ctx {
   double* R6 = nullptr;          // inhom: six real strain fields
   double* LC6 = nullptr;         // inhom: the polarisation's per-point coefficients (six real fields)
   double* elmax = nullptr;       // inhom: largest strain change of the last update
+  hipEvent_t el_ev = nullptr;    // inhom: that change has reached the host
   double* el_part = nullptr;     // inhom: per-block elastic energy sums
 
   bool owns = true;  // false for views whose buffers belong to an ensemble

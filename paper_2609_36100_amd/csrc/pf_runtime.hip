@@ -405,11 +405,15 @@ static pf_status el_solve(pf_ctx* c, cx<double>* T1, cx<double>* FE0, int accumu
   ok = ok && launch_el_rows<4>(c, T1, nullptr, nullptr);
   prof_end(c, KC_EL_LOCAL, 3 * fk + 6 * fr);
   back(nullptr, true, c->p.el_max_iter > 0);
-  int it = 0;
-  while (ok && it < c->p.el_max_iter) {
+  auto yfwd = [&] {  // the first pass of an update
     prof_begin(c);
     ok = ok && launch_colfft<double, -1, 1>(c, c->E6, c->E6, 6, 1.0);
     prof_end(c, KC_YFFT, 12 * fk);
+  };
+  int it = 0;
+  bool ahead = false;  // the next update's first pass is under way
+  while (ok && it < c->p.el_max_iter) {
+    if (!ahead) yfwd();
     // forward z, Gamma0 and the scaled inverse z in one pass
     prof_begin(c);
     ok = ok && launch_el_zgamma(c, s);
@@ -418,7 +422,13 @@ static pf_status el_solve(pf_ctx* c, cx<double>* T1, cx<double>* FE0, int accumu
     back(c->elmax, false, it < c->p.el_max_iter);
     if (!ok) break;
     PF_HIP(hipMemcpyAsync(&c->host_red[6], c->elmax, sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    PF_HIP(hipStreamSynchronize(c->stream));
+    PF_HIP(hipEventRecord(c->el_ev, c->stream));
+    // Solves of neighbouring stages take about as many updates: where the last
+    // one took more, the next update's first pass is launched before the change
+    // is known, so that it runs while the host waits (E6 is free either way).
+    ahead = it < c->p.el_max_iter && it < c->st.el_last;
+    if (ahead) yfwd();
+    PF_HIP(hipEventSynchronize(c->el_ev));
     if (c->host_red[6] <= c->p.el_tol) break;  // a NaN change never stops early
   }
   if (!ok) return PF_ERR_UNSUPPORTED_SIZE;
@@ -807,6 +817,7 @@ void pf_finalize(pf_ctx* c) {
   hipFree(c->R6);
   hipFree(c->LC6);
   hipFree(c->elmax);
+  if (c->el_ev) hipEventDestroy(c->el_ev);
   hipFree(c->el_part);
   for (int i = 0; i < 6; ++i) {
     hipFree(c->FE[i]);
@@ -871,6 +882,7 @@ pf_status pf_init(const pf_params* p, void* stream, pf_ctx** out) {
   if (s == PF_OK && c->inhom) s = dalloc(c, (void**)&c->R6, sizeof(double) * 6 * (size_t)g.nx * g.ny * g.nz);
   if (s == PF_OK && c->inhom) s = dalloc(c, (void**)&c->LC6, sizeof(double) * 6 * (size_t)g.nx * g.ny * g.nz);
   if (s == PF_OK && c->inhom) s = dalloc(c, (void**)&c->elmax, sizeof(double));
+  if (s == PF_OK && c->inhom && hipEventCreateWithFlags(&c->el_ev, hipEventDisableTiming) != hipSuccess) s = PF_ERR_HIP;
   if (s == PF_OK && c->inhom) s = dalloc(c, (void**)&c->el_part, sizeof(double) * (size_t)el_row_blocks(c));
   for (int i = 0; i < c->tab.s && s == PF_OK; ++i)
     if (c->fe_need[i] || i == 0) s = dalloc(c, &c->FE[i], fe_bytes);
