@@ -289,7 +289,7 @@ k_el_strain(cx<double>* __restrict__ e6, double* __restrict__ r6, const double* 
   __syncthreads();  // the tables
   auto strain = [&](int f, cx<double>* a) {
     cx<double>* dst = s6 + f * npair;
-    row_c2r<double, M, RB, RG::SYNC>(e6 + f * g.fs + rb, rvalid, a, bf, rbuf, tN, tM);
+    row_c2r<double, M, RB, RG::SYNC_OWN>(e6 + f * g.fs + rb, rvalid, a, bf, rbuf, tN, tM);
     if (rvalid) {
 #pragma unroll
       for (int t = 0; t < RG::R0; ++t) {
@@ -321,7 +321,7 @@ k_el_strain(cx<double>* __restrict__ e6, double* __restrict__ r6, const double* 
                   A.im - d11.im * u[c][t].im - d12.im * (u[k][t].im + u[l][t].im));
         if (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // four points' loads in flight at a time
       }
-      row_r2c<double, M, RB, RG::SYNC>(a, e6 + c * g.fs + rb, rvalid, bf, rbuf, tN, tM);
+      row_r2c<double, M, RB, RG::SYNC_OWN>(a, e6 + c * g.fs + rb, rvalid, bf, rbuf, tN, tM);
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll 1
@@ -333,7 +333,7 @@ k_el_strain(cx<double>* __restrict__ e6, double* __restrict__ r6, const double* 
         const cx<double> d44 = at32(lc + 5 * npair, q0 + t * RG::TL);
         a[t] = mk(-2.0 * d44.re * a[t].re, -2.0 * d44.im * a[t].im);
       }
-      row_r2c<double, M, RB, RG::SYNC>(a, e6 + f * g.fs + rb, rvalid, bf, rbuf, tN, tM);
+      row_r2c<double, M, RB, RG::SYNC_OWN>(a, e6 + f * g.fs + rb, rvalid, bf, rbuf, tN, tM);
     }
   } else {
     for (int f = 0; f < 6; ++f) {
@@ -362,7 +362,7 @@ __device__ inline void eigen_diag(const ModelK& m, double t0, double t1, double 
 
 // The c2r of the three order parameters of one row of T1 into et[3][R0]
 // (pairs of consecutive x).
-template <int M, int RB>
+template <int M, int RB, int LB>
 __device__ inline void row_eta3(const cx<double>* st, long long rb, bool rvalid, cx<double> (*et)[RowGeo<M, RB>::R0],
                                 int bf, cx<double>* rbuf, const cx<double>* twN, const cx<double>* twM,
                                 const Geo& g) {
@@ -370,7 +370,7 @@ __device__ inline void row_eta3(const cx<double>* st, long long rb, bool rvalid,
   // memory), one transform at a time
 #pragma unroll
   for (int v = 0; v < 3; ++v) {
-    row_c2r<double, M, RB, RowGeo<M, RB>::SYNC_PLAIN>(st + (1 + v) * g.fs + rb, rvalid, et[v], bf, rbuf, twN, twM);
+    row_c2r<double, M, RB, LB>(st + (1 + v) * g.fs + rb, rvalid, et[v], bf, rbuf, twN, twM);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -490,7 +490,7 @@ k_el_drive(const cx<double>* __restrict__ st, const double* __restrict__ r6, cx<
   cx<double> chi[RG::R0];
   {
     cx<double> a[RG::R0];
-    row_c2r<double, M, RB, RG::SYNC>(st + rb, rvalid, a, bf, rbuf, tN, tM);
+    row_c2r<double, M, RB, RG::SYNC_OWN>(st + rb, rvalid, a, bf, rbuf, tN, tM);
 #pragma unroll
     for (int t = 0; t < RG::R0; ++t) {
       const double c0 = a[t].re, c1 = a[t].im;
@@ -500,7 +500,7 @@ k_el_drive(const cx<double>* __restrict__ st, const double* __restrict__ r6, cx<
     }
   }
   cx<double> et[3][RG::R0];
-  row_eta3<M, RB>(st, rb, rvalid, et, bf, rbuf, tN, tM, g);
+  row_eta3<M, RB, RG::SYNC_OWN>(st, rb, rvalid, et, bf, rbuf, tN, tM, g);
 #pragma unroll
   for (int t = 0; t < RG::R0; ++t) {
     cx<double> uu[6];
@@ -536,7 +536,7 @@ k_el_drive(const cx<double>* __restrict__ st, const double* __restrict__ r6, cx<
   }
 #pragma unroll
   for (int v = 0; v < 3; ++v) {
-    row_r2c<double, M, RB, RG::SYNC>(et[v], el + v * g.fs + rb, rvalid, bf, rbuf, tN, tM);
+    row_r2c<double, M, RB, RG::SYNC_OWN>(et[v], el + v * g.fs + rb, rvalid, bf, rbuf, tN, tM);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -560,7 +560,7 @@ k_el_energy(const cx<double>* __restrict__ st, const double* __restrict__ r6, Ge
   const long long npair = (long long)nrows * M;
   const cx<double>* s6 = reinterpret_cast<const cx<double>*>(r6) + rr * M;
   cx<double> et[3][RG::R0];
-  row_eta3<M, RB>(st, rr * g.P, rvalid, et, bf, rbuf, twN, twM, g);
+  row_eta3<M, RB, RG::SYNC_PLAIN>(st, rr * g.P, rvalid, et, bf, rbuf, twN, twM, g);
   double acc = 0.0;
   if (rvalid) {
 #pragma unroll

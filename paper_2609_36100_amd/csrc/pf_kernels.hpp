@@ -164,7 +164,7 @@ __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_b
 // in one wavefront, whose LDS accesses the hardware executes in order.
 template <int LB>
 __device__ inline void xbar() {
-  if constexpr (LB == 2)
+  if constexpr (LB >= 2)
     asm volatile("" ::: "memory");
   else if constexpr (LB == 1)
     lds_barrier();
@@ -900,6 +900,10 @@ struct RowGeo {
   static constexpr int SYNC = 64 % TL == 0 ? 2 : 1;
   // the same where the twiddles are read from memory between the exchanges
   static constexpr int SYNC_PLAIN = 64 % TL == 0 ? 2 : 0;
+  // SYNC as instantiations of its own: sharing them with kernels that read their
+  // twiddles from memory changes those kernels' rounding (the boundary transforms
+  // of a state, and with them a mixed step at 4e-8)
+  static constexpr int SYNC_OWN = 64 % TL == 0 ? 3 : 1;
 };
 
 // The HBM reads of row_c2r on their own: raw[t] = src[bf + t TL], raw[R0] =
