@@ -372,7 +372,7 @@ struct ZItem {
 
 // Forward z-transform of the driving force g of order parameter f - 1 and
 // F^E = -L g~, left in LDS at the thread's own positions (rounded to TE).
-template <typename T, typename TE, int N, int TX, int RE, bool GUARD, class Buf>
+template <typename T, typename TE, int N, int TX, int RE, bool GUARD, int LB = 0, class Buf>
 __device__ inline void fresh_explicit(const cx<T>* gk, const ZItem<N, TX, RE, GUARD>& q, const Geo& g, const ModelK& m,
                                       const cx<T>* twz, Buf buf) {
   using CG = ColGeo<N, TX, RE>;
@@ -381,7 +381,7 @@ __device__ inline void fresh_explicit(const cx<T>* gk, const ZItem<N, TX, RE, GU
 #pragma unroll
   for (int t = 0; t < CG::R0; ++t)
     a[t] = q.valid ? at32(src, q.base + (uint32_t)(q.bf + t * CG::TL) * q.lstride) : mk<T>(0, 0);
-  line_fft<T, N, -1, RE>(a, q.bf, twz, buf, q.act);
+  line_fft<T, N, -1, RE, LB>(a, q.bf, twz, buf, q.act);
   const T nl = (T)(-m.L);
   if (q.act) {
 #pragma unroll
@@ -423,14 +423,14 @@ struct StageRow {
 // ARK4 step at 512^3 took 114 ms with this pass and the update as below (130
 // with F^I stored and four fields per work-group), the mixed step at 256^3 8.8
 // (10.8), an adaptive one at 64^3 0.40 (0.53).
-template <typename T, typename TE, int N, int TX, int RE, int NP, bool GUARD = false, class TabP>
+template <typename T, typename TE, int N, int TX, int RE, int NP, bool GUARD = false, int LB = 0, class TabP>
 __device__ inline void body_stage(const StepArgs<TE>& sa, TabP tb, const Geo& g, const ModelK& m,
                                   const cx<T>* gk, const cx<T>* twz, cx<T>* out, int item, int tid, cx<T>* lds) {
   using CG = ColGeo<N, TX, RE>;
   const ZItem<N, TX, RE, GUARD> q(g, item, tid);
   auto buf = [&](int pos) -> cx<T>& { return lds[pos * CG::LD + q.col]; };
   if constexpr (NP > 0 && fresh_fe<T>) {
-    if (q.f > 0) fresh_explicit<T, TE, N, TX, RE, GUARD>(gk, q, g, m, twz, buf);
+    if (q.f > 0) fresh_explicit<T, TE, N, TX, RE, GUARD, LB>(gk, q, g, m, twz, buf);
   }
   const double kx = q.x * g.kfx, ky = mode_of(q.y, g.ny) * g.kfy;
     const long long fo = q.f * g.fs;
@@ -470,7 +470,7 @@ __device__ inline void body_stage(const StepArgs<TE>& sa, TabP tb, const Geo& g,
   cx<T> a[CG::R0];
 #pragma unroll
   for (int t = 0; t < CG::R0; ++t) a[t] = q.act ? buf(q.bf + t * CG::TL) : mk<T>(0, 0);
-  line_fft<T, N, +1, RE>(a, q.bf, twz, buf, q.act);
+  line_fft<T, N, +1, RE, LB>(a, q.bf, twz, buf, q.act);
   if (q.valid) {
     cx<T>* of = out + fo;
 #pragma unroll
@@ -487,7 +487,7 @@ k_stage_invz(StepArgs<TE> sa, ArkTab tb, Geo g, ModelK m, const cx<T>* gk, const
 
 // ---- generic column FFT along y or z (in or out of place) -----------------
 // axis 1 = y (lines at fixed z), axis 2 = z (lines at fixed y).
-template <typename T, int N, int TX, int RE, int S, int AXIS, bool GUARD = false>
+template <typename T, int N, int TX, int RE, int S, int AXIS, bool GUARD = false, int LB = 0>
 __device__ inline void body_colfft(const cx<T>* in, cx<T>* out, const Geo& g, int nf, const cx<T>* tw, T scale,
                                    int tile, int tid, cx<T>* lds) {
   using CG = ColGeo<N, TX, RE>;
@@ -510,7 +510,7 @@ __device__ inline void body_colfft(const cx<T>* in, cx<T>* out, const Geo& g, in
       const int q = bf + t * CG::TL;
       a[t] = valid ? in[fb + q * lstride] : mk<T>(0, 0);
     }
-    line_fft<T, N, S, RE>(a, bf, tw, buf, act);
+    line_fft<T, N, S, RE, LB>(a, bf, tw, buf, act);
     if (valid) {
 #pragma unroll
       for (int t = 0; t < CG::R0; ++t) {
@@ -1245,7 +1245,7 @@ __device__ inline double block_sum(double v, double* sh) {
 // F^E comes straight from the forward z-transform of its driving force and is
 // never stored.  S == 2 is IMEX Euler, whose last stage has no explicit derivative.
 // acc and bad receive the thread's error terms and count of non-finite values.
-template <typename T, typename TE, int N, int TX, int RE, int S, bool GUARD = false, class TabP>
+template <typename T, typename TE, int N, int TX, int RE, int S, bool GUARD = false, int LB = 0, class TabP>
 __device__ inline void body_final(const StepArgs<TE>& sa, TabP tb, const Geo& g, const ModelK& m,
                                   const cx<T>* gk, const cx<T>* twz, int item, int tid, cx<T>* lds, double& acc,
                                   double& bad) {
@@ -1254,7 +1254,7 @@ __device__ inline void body_final(const StepArgs<TE>& sa, TabP tb, const Geo& g,
   const ZItem<N, TX, RE, GUARD> q(g, item, tid);
   auto buf = [&](int pos) -> cx<T>& { return lds[pos * CG::LD + q.col]; };
   if constexpr (fresh_fe<T>) {
-    if (q.f > 0) fresh_explicit<T, TE, N, TX, RE, GUARD>(gk, q, g, m, twz, buf);
+    if (q.f > 0) fresh_explicit<T, TE, N, TX, RE, GUARD, LB>(gk, q, g, m, twz, buf);
   }
   acc = bad = 0.0;
   if (!q.valid) return;
