@@ -30,6 +30,7 @@
 
 #include "../../include/pf.h"
 #include "pf_context.hpp"
+#include "pf_fno_sizes.hpp"
 
 namespace {
 
@@ -1261,7 +1262,6 @@ struct pf_fno {
   u16 *dpreb = nullptr, *dpreb2 = nullptr, *douthb = nullptr, *dhb = nullptr, *dSb = nullptr;
   float* gtab = nullptr;  // GELU' over the bf16 values
   float* part = nullptr;
-  long long part_elems = 0;
   double* dpart = nullptr;
   double* dsum = nullptr;
   double* hsum = nullptr;  // pinned
@@ -1460,8 +1460,6 @@ static void cm(pf_fno* F, const u16* In, int ldin, int K, const u16* Bt, int N, 
   cm_launch(F, F->P, In, ldin, K, Bt, N, bias, resid, ldres, outf, outpre, outact, ldout, accumulate, lt, gpre);
 }
 
-constexpr int kWgradBlocks = 512;  // blocks (point chunks) of one weight-gradient reduction
-
 static void sum_partials(pf_fno* F, const float* part, int nb, int K, int N, float* gW, float* gb) {
   const double kn = (double)(K + 1) * N;
   account(F, FK_WSUM, 4.0 * nb * kn + 8.0 * kn, (double)nb * kn);
@@ -1469,7 +1467,7 @@ static void sum_partials(pf_fno* F, const float* part, int nb, int K, int N, flo
 }
 
 static void wgrad(pf_fno* F, const u16* A, int lda, int K, const u16* D, int ldd, int N, float* gW, float* gb) {
-  const int nb = (int)std::min<long long>(kWgradBlocks, (F->P / 32 + 3) / 4);
+  const int nb = pf::wgrad_blocks(F->P);
   for (int k0 = 0; k0 < K; k0 += 64)
     for (int n0 = 0; n0 < N; n0 += 64) {
       const int kk = std::min(64, K - k0), nn = std::min(64, N - n0);
@@ -1488,10 +1486,7 @@ static void wgrad(pf_fno* F, const u16* A, int lda, int K, const u16* D, int ldd
   sum_partials(F, F->part, nb, K, N, gW, gb);
 }
 
-// The fused projection over `points` points (kProjBlocks: two work-groups per
-// CU, walking the points).
-constexpr int kProjBlocks = 512;
-
+// The fused projection over `points` points.
 static ProjArgs proj_args(const pf_fno* F, const u16* v, long long points) {
   ProjArgs a = {};
   a.v = v;
@@ -1511,7 +1506,7 @@ static ProjArgs proj_args(const pf_fno* F, const u16* v, long long points) {
 
 template <bool TRAIN>
 static int proj_launch(pf_fno* F, const ProjArgs& a) {
-  const int nb = (int)std::min<long long>(kProjBlocks, (a.P / 32 + 3) / 4);
+  const int nb = pf::proj_blocks(a.P);
   if (a.h <= 64)
     k_proj<TRAIN, 2><<<nb, 256, 0, F->stream>>>(a);
   else if (a.h <= 96)
@@ -1545,7 +1540,7 @@ static void project_train(pf_fno* F, const float* x, const float* y, u16* dpre) 
   a.inv = 2.0f / (float)((double)F->P * co);
   a.dpre = dpre;
   a.part1 = F->part;
-  a.part2 = F->part + (long long)kProjBlocks * (w + 1) * h;
+  a.part2 = F->part + pf::proj_parts(F->P, w, h, co).second;
   a.dpart = F->dpart;
   account(F, FK_CM, (double)F->P * (4.0 * w + 8.0 * co) + 4.0 * h * (w + co), 6.0 * F->P * h * (w + co));
   const int nb = proj_launch<true>(F, a);
@@ -1896,8 +1891,7 @@ pf_status pf_fno_create(const pf_fno_config* cfg, void* stream, pf_fno** out) {
   if (F->fuse_x || F->xlines) A((void**)&F->dpreb2, 2 * P * w);
   if (!F->fuse_proj) A((void**)&F->douthb, 2 * P * F->coutp);
   A((void**)&F->dSb, 2 * spec);
-  F->part_elems = (long long)kWgradBlocks * (std::max(std::max(w, h), 8) + 1) * std::max(std::max(w, h), 8);
-  A((void**)&F->part, 4 * F->part_elems);
+  A((void**)&F->part, 4 * pf::part_elems(P, w, h, c.cin, c.cout, F->fuse_proj));
   A((void**)&F->dpart, 8 * (size_t)gdiv(P, 256));
   A((void**)&F->dsum, 8);
   if (s == PF_OK && hipHostMalloc((void**)&F->hsum, 8, 0) != hipSuccess) s = PF_ERR_OOM;

@@ -1,0 +1,58 @@
+"""Surrogate gradients at the hidden sizes closest to the width, where the fused
+projection's two partial sets need the most scratch for their width: forward
+output, loss and every gradient against the FP64 oracle at 3e-2 relative L2 (the
+BF16 network's stated bound), and the forward pass after the gradient equal to
+the one before it (the DFT matrices lie behind the scratch)."""
+import numpy as np
+import pytest
+
+from oracle import fno as of
+
+pytestmark = pytest.mark.gpu
+BOUND = 3e-2
+
+
+def check_gradient(n, w, m, L, h, cin, cout):
+    import torch
+    from paper_2609_36100_amd import FNO
+    print("[case] fno scratch", n, w, m, L, h, cin, cout, flush=True)
+    net = of.FNO(n, width=w, modes=m, layers=L, cin=cin, cout=cout, hidden=h)
+    rng = np.random.default_rng(9)
+    p = net.init_params(seed=3)
+    for k in p:
+        if k[0] in "bc":
+            p[k] = 0.1 * rng.standard_normal(p[k].shape)
+    to_bf = lambda a: torch.from_numpy(np.asarray(a, np.float32)).to(torch.bfloat16).to(torch.float64).numpy()
+    p = {k: to_bf(v) for k, v in p.items()}
+    x = rng.uniform(-1, 1, (n, n, n, cin))
+    x = to_bf(x - x.mean(axis=(0, 1, 2)))
+    tgt = rng.standard_normal((n, n, n, cout)) * 0.5
+    out, tape = net.forward(p, x, keep=True)
+    loss, dout = of.mse_loss(out, tgt)
+    g = net.backward(p, tape, dout)
+    xt = torch.from_numpy(np.ascontiguousarray(np.moveaxis(x, -1, 0))).float().cuda()
+    yt = torch.zeros((max(cin, cout),) + xt.shape[1:], device="cuda")
+    yt[:cin] = xt
+    yt = yt[:cout] + torch.from_numpy(np.ascontiguousarray(np.moveaxis(tgt, -1, 0))).float().cuda()
+    with FNO(n, width=w, modes=m, layers=L, hidden=h, cin=cin, cout=cout) as f:
+        f.set_params(np.concatenate([p[k].ravel() for k in net.param_shapes()]).astype(np.float32))
+        before = f.forward(xt).cpu().numpy()
+        f.zero_grad()
+        gl = f.grad(xt, yt)
+        flat = f.get_grad().astype(np.float64)
+        after = f.forward(xt).cpu().numpy()
+    assert np.array_equal(before, after)
+    gout = before.reshape(n, n, n, cout)
+    assert np.linalg.norm(gout - out) < BOUND * np.linalg.norm(out)
+    assert abs(gl - loss) < BOUND * loss
+    at = 0
+    for k, s in net.param_shapes().items():
+        a = flat[at:at + int(np.prod(s))].reshape(s)
+        at += a.size
+        assert np.linalg.norm(a - g[k]) < BOUND * np.linalg.norm(g[k]) + 1e-30, k
+
+
+@pytest.mark.parametrize("w,h", [(8, 8), (16, 16), (32, 32), (28, 32)])
+@pytest.mark.parametrize("cout", [1, 4, 8])
+def test_gradient_with_two_partial_sets(w, h, cout):
+    check_gradient(56, w, 2, 1, h, 8 if cout == 8 else 4, cout)
