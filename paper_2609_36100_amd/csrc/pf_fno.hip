@@ -1717,7 +1717,7 @@ static void loss_backward(pf_fno* F, const float* x, const float* y) {
     project_train(F, x, y, db[0]);
   } else {
     project_gemms(F);
-    const unsigned nb = gdiv(P, 256);
+    const unsigned nb = pf::pointwise_blocks(P);
     account(F, FK_ELEM, (double)P * co * (4.0 * 3) + (double)P * F->coutp * 2.0, 0.0);
     k_loss<<<nb, 256, 0, F->stream>>>(F->outf, x, y, F->scale, P, co, F->coutp, F->douthb, F->dpart);
     k_sum_d<<<1, 256, 0, F->stream>>>(F->dpart, (int)nb, F->dsum);
@@ -1892,7 +1892,7 @@ pf_status pf_fno_create(const pf_fno_config* cfg, void* stream, pf_fno** out) {
   if (!F->fuse_proj) A((void**)&F->douthb, 2 * P * F->coutp);
   A((void**)&F->dSb, 2 * spec);
   A((void**)&F->part, 4 * pf::part_elems(P, w, h, c.cin, c.cout, F->fuse_proj));
-  A((void**)&F->dpart, 8 * (size_t)gdiv(P, 256));
+  A((void**)&F->dpart, 8 * pf::dpart_elems(P, F->fuse_proj));
   A((void**)&F->dsum, 8);
   if (s == PF_OK && hipHostMalloc((void**)&F->hsum, 8, 0) != hipSuccess) s = PF_ERR_OOM;
   if (s == PF_OK) {
@@ -2179,7 +2179,7 @@ static pf_status ensure_batch(pf_fno* F, int B) {
   if (!F->fuse_x && !F->xlines) A((void**)&F->bB1, Bs * 4 * P * w);
   if (!F->fuse_proj) A((void**)&F->bhact, Bs * 2 * P * h);
   A((void**)&F->boutf, Bs * 4 * P * c.cout);
-  A((void**)&F->bdpart, Bs * 8 * gdiv(F->P, 256));
+  A((void**)&F->bdpart, Bs * 8 * pf::pointwise_blocks(F->P));
   A((void**)&F->bdsum, Bs * 8);
   if (s != PF_OK) {
     for (void* p : F->ballocs) hipFree(p);
@@ -2226,7 +2226,7 @@ static pf_status apply_batch(pf_fno* F, const double* states, double* nexts, int
   if (s != PF_OK) return s;
   const long long P = F->P;
   const int ci = F->cfg.cin, co = F->cfg.cout;
-  const unsigned nb = gdiv(P, 256);
+  const unsigned nb = pf::pointwise_blocks(P);
   for (int b = 0; b < B; ++b) {
     account(F, FK_ELEM, (double)P * (8.0 * ci + 2.0 * F->cinp), 0.0);
     k_pack_input<double><<<nb, 256, 0, F->stream>>>(states + (long long)b * ci * P, P, ci, F->cinp, F->innorm,
@@ -2280,7 +2280,7 @@ pf_status pf_fno_apply(pf_fno* F, const double* state, double* next) {
   account(F, FK_ELEM, (double)F->P * (8.0 * F->cfg.cin + 2.0 * F->cinp), 0.0);
   k_pack_input<double><<<gdiv(F->P, 256), 256, 0, F->stream>>>(state, F->P, F->cfg.cin, F->cinp, F->innorm, F->xin);
   forward(F);
-  const unsigned nb = gdiv(F->P, 256);
+  const unsigned nb = pf::pointwise_blocks(F->P);
   account(F, FK_ELEM, (double)F->P * F->cfg.cout * (8.0 + 4.0 + 8.0), 0.0);
   k_apply<<<nb, 256, 0, F->stream>>>(state, F->outf, F->scale, F->P, F->cfg.cout, next, F->dpart);
   k_sum_d<<<1, 256, 0, F->stream>>>(F->dpart, (int)nb, F->dsum);

@@ -35,4 +35,13 @@ inline long long part_elems(long long P, int w, int h, int ci, int co, bool fuse
                                     : std::max(wgrad_elems(P, w, h), wgrad_elems(P, h, co)));
 }
 
+// Blocks of the kernels with one point per thread.
+inline int pointwise_blocks(long long P) { return (int)((P + 255) / 256); }
+
+// Elements of the per-block FP64 sums: the squared error (k_loss, or the fused
+// projection's blocks) and the mass of an advance (k_apply).
+inline long long dpart_elems(long long P, bool fuse_proj) {
+  return std::max(pointwise_blocks(P), fuse_proj ? proj_blocks(P) : 0);
+}
+
 }  // namespace pf

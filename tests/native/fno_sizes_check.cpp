@@ -1,5 +1,5 @@
 // Walks every surrogate shape that pf_fno_create accepts (host only) and checks
-// that each block's partial sums lie inside the scratch allocated for them and
+// that each block's partial sums and scalar sums lie inside the scratch allocated for them and
 // apart from the others'.  Prints "ok <shapes>" or the first shape that fails.
 #include <cstdio>
 
@@ -31,8 +31,10 @@ int main() {
               sets(w, h);
               sets(h, co);
             }
-            if (!ok) {
-              std::printf("part n %d w %d h %d cin %d cout %d\n", n, w, h, ci, co);
+            const long long sums = pf::dpart_elems(P, fuse);
+            const bool dok = pf::pointwise_blocks(P) <= sums && (!fuse || pf::proj_blocks(P) <= sums);
+            if (!ok || !dok) {
+              std::printf("%s n %d w %d h %d cin %d cout %d\n", ok ? "sums" : "part", n, w, h, ci, co);
               return 1;
             }
             ++shapes;

@@ -56,3 +56,10 @@ def check_gradient(n, w, m, L, h, cin, cout):
 @pytest.mark.parametrize("cout", [1, 4, 8])
 def test_gradient_with_two_partial_sets(w, h, cout):
     check_gradient(56, w, 2, 1, h, 8 if cout == 8 else 4, cout)
+
+
+@pytest.mark.parametrize("n,w,h", [(8, 8, 16), (16, 32, 32), (40, 16, 64), (48, 32, 128)])
+def test_gradient_on_few_points(n, w, h):
+    """Grids on which the fused projection has more blocks than the pointwise
+    kernels: one squared-error sum per block."""
+    check_gradient(n, w, 2, 1, h, 4, 4)
