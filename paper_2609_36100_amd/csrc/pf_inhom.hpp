@@ -148,10 +148,10 @@ __global__ void __launch_bounds__(256) k_el_start(const cx<double>* th, cx<doubl
   }
 }
 
-// Non-negative doubles order like their bit patterns: a block's largest change
-// is merged into *mx with an integer atomic max.
-__device__ inline void atomic_max_nonneg(double* mx, double v) {
-  atomicMax(reinterpret_cast<unsigned long long*>(mx), (unsigned long long)__double_as_longlong(v));
+// |v| as an integer: magnitudes order like their bit patterns, and a NaN comes
+// after every number, so that a maximum over them keeps it (fmax drops it).
+__device__ inline unsigned long long mag_bits(double v) {
+  return (unsigned long long)__double_as_longlong(v) & 0x7fffffffffffffffull;
 }
 
 }  // namespace
@@ -268,7 +268,7 @@ k_el_strain(cx<double>* __restrict__ e6, double* __restrict__ r6, const double* 
   using RG = RowGeo<M, RB>;
   __shared__ cx<double> lds[RB * RG::LD];
   __shared__ cx<double> tM[M], tN[M];
-  __shared__ double wmax[RG::THREADS / 64 + 1];
+  __shared__ unsigned long long wmax[RG::THREADS / 64 + 1];
   for (int j = threadIdx.x; j < M; j += RG::THREADS) {
     tM[j] = twM[j];
     tN[j] = twN[j];
@@ -285,7 +285,7 @@ k_el_strain(cx<double>* __restrict__ e6, double* __restrict__ r6, const double* 
   cx<double>* s6 = reinterpret_cast<cx<double>*>(r6);
   const cx<double>* lc = reinterpret_cast<const cx<double>*>(lc6);
   const uint32_t q0 = (uint32_t)(rr * M) + bf;
-  double dmax = 0.0;
+  unsigned long long dmax = 0;  // the largest change, as mag_bits
   __syncthreads();  // the tables
   auto strain = [&](int f, cx<double>* a) {
     cx<double>* dst = s6 + f * npair;
@@ -296,7 +296,7 @@ k_el_strain(cx<double>* __restrict__ e6, double* __restrict__ r6, const double* 
         cx<double>& d = at32(dst, q0 + t * RG::TL);
         if (mx) {
           const cx<double> old = d;
-          dmax = fmax(dmax, fmax(fabs(a[t].re - old.re), fabs(a[t].im - old.im)));
+          dmax = max(dmax, max(mag_bits(a[t].re - old.re), mag_bits(a[t].im - old.im)));
         }
         d = a[t];
       }
@@ -343,13 +343,13 @@ k_el_strain(cx<double>* __restrict__ e6, double* __restrict__ r6, const double* 
   }
   if (mx) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) dmax = fmax(dmax, __shfl_xor(dmax, o, 64));
+    for (int o = 32; o > 0; o >>= 1) dmax = max(dmax, (unsigned long long)__shfl_xor(dmax, o, 64));
     if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = dmax;
     __syncthreads();
     if (threadIdx.x == 0) {
-      double b = 0.0;
-      for (int w = 0; w < (RG::THREADS + 63) / 64; ++w) b = fmax(b, wmax[w]);
-      atomic_max_nonneg(mx, b);
+      unsigned long long b = 0;
+      for (int w = 0; w < (RG::THREADS + 63) / 64; ++w) b = max(b, wmax[w]);
+      atomicMax(reinterpret_cast<unsigned long long*>(mx), b);
     }
   }
 }
