@@ -300,13 +300,17 @@ __global__ void __launch_bounds__(EB) kb_fwd_ac(const EMemb<T, TE>* mem, const E
   }
 }
 
-// Update + embedded error + WRMS partial sums, one pair per work-group.
+// Columns per partial pair of the update's sums: the narrower tile's, for both
+// work-group sizes (tile_sums), so `pairs` is that tile's work list.
+constexpr int ens_pair_cols(int n) { return ens_tx(128, n, 8); }
+
+// Update + embedded error + WRMS partial sums.
 template <typename T, typename TE, int EB, int S>
 __global__ void __launch_bounds__(EB) kb_final(const EMemb<T, TE>* mem, const EState* st, const int* start, int M,
-                                               const ArkTab* tabs, double* partial) {
+                                               const ArkTab* tabs, const int* pairs, double* partial) {
   __shared__ cx<T> lds[ens_lds(EB)];
+  static_assert(sizeof(lds) >= 16 * EB, "the sums");
   __shared__ ColTable<T> table;
-  __shared__ double sh[16];
   const int m = find_member(start, M, blockIdx.x);
   if (st[m].done) return;  // uniform per block: the partials of done members are never read
   const EMemb<T, TE>& e = mem[m];
@@ -314,21 +318,18 @@ __global__ void __launch_bounds__(EB) kb_final(const EMemb<T, TE>* mem, const ES
   const StepArgs<TE> sa = member_step(e, st[m]);
   const TabK tb = member_tab(tabs, m);
   const cx<T>* twl = col_table<EB>(e, table);
-  double acc = 0.0, bad = 0.0;
+  double acc, bad;
   switch (e.g.nz) {
 #define PF_C(N)                                                                                               \
   case N:                                                                                                     \
     body_final<T, TE, N, ens_tx(EB, N, 8), 8, S, true, ens_lb<T>>(sa, tb, e.g, e.mk, e.T3, twl, item,         \
                                                                   threadIdx.x, lds, acc, bad);               \
+    tile_sums<N, ens_tx(EB, N, 8), 8, ens_pair_cols(N), EB>(acc, bad, e.g, item, threadIdx.x,                 \
+                                                            reinterpret_cast<double*>(lds),                  \
+                                                            partial + 2 * pairs[m]);                         \
     break;
     PF_ENS_SIZES(PF_C)
 #undef PF_C
-  }
-  const double s0 = block_sum(acc, sh);
-  const double s1 = block_sum(bad, sh);
-  if (threadIdx.x == 0) {
-    partial[2 * blockIdx.x] = s0;
-    partial[2 * blockIdx.x + 1] = s1;
   }
 }
 
@@ -388,7 +389,7 @@ __device__ inline double control_member(const Geo& g, EState& st, double a, doub
 // One work-group per member: sum its partials in a fixed order, then the
 // accept / reject decision and the next step size (thread 0).
 template <typename T, typename TE>
-__global__ void __launch_bounds__(256) kb_control(const EMemb<T, TE>* mem, EState* st, const int* fstart,
+__global__ void __launch_bounds__(256) kb_control(const EMemb<T, TE>* mem, EState* st, const int* pairs,
                                                   const double* partial, int q, int has_emb, int nrhs,
                                                   ArkTab unit, ArkTab* tabs) {
   __shared__ double sh[16];
@@ -396,7 +397,7 @@ __global__ void __launch_bounds__(256) kb_control(const EMemb<T, TE>* mem, EStat
   const int m = blockIdx.x;
   if (st[m].done) return;
   double a = 0.0, b = 0.0;
-  for (int i = fstart[m] + threadIdx.x; i < fstart[m + 1]; i += blockDim.x) {
+  for (int i = pairs[m] + threadIdx.x; i < pairs[m + 1]; i += blockDim.x) {
     a += partial[2 * i];
     b += partial[2 * i + 1];
   }
@@ -436,7 +437,8 @@ struct pf_ens {
   EState* st_host = nullptr;  // pinned
   int* start[EK_COUNT][2] = {{nullptr}};
   int ntiles[EK_COUNT][2] = {{0}};
-  double* partial = nullptr;
+  double* partial = nullptr;  // the update's sums, by `pairs`
+  const int* pairs() const { return start[EK_STAGE][0]; }
   int var[EK_COUNT] = {1, 1, 1, 1, 1, 1, 1};
   double tune_ms[EK_COUNT][2] = {{0}};
   ArkTable tab;
@@ -500,8 +502,7 @@ static pf_status build_lists(pf_ens* E) {
       PF_HIP(hipMemcpy(E->start[k][v], st.data(), sizeof(int) * (E->M + 1), hipMemcpyHostToDevice));
       E->ntiles[k][v] = st[E->M];
     }
-  return ens_alloc(E, (void**)&E->partial,
-                   sizeof(double) * 2 * std::max(E->ntiles[EK_STAGE][0], E->ntiles[EK_STAGE][1]));
+  return ens_alloc(E, (void**)&E->partial, sizeof(double) * 2 * E->ntiles[EK_STAGE][0]);
 }
 
 template <typename T, typename TE>
@@ -517,9 +518,9 @@ static void launch_kind(pf_ens* E, int kind, int stage) {
       case EK_STAGE:
         if (stage == E->tab.s) {  // the step's update; embedded pairs only
           switch (E->tab.s) {
-            case 3: kb_final<T, TE, EB, 3><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, E->tab_dev, E->partial); break;
-            case 4: kb_final<T, TE, EB, 4><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, E->tab_dev, E->partial); break;
-            default: kb_final<T, TE, EB, 6><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, E->tab_dev, E->partial); break;
+            case 3: kb_final<T, TE, EB, 3><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, E->tab_dev, E->pairs(), E->partial); break;
+            case 4: kb_final<T, TE, EB, 4><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, E->tab_dev, E->pairs(), E->partial); break;
+            default: kb_final<T, TE, EB, 6><<<nb, EB, 0, s>>>(mem, E->st_dev, st, E->M, E->tab_dev, E->pairs(), E->partial); break;
           }
           break;
         }
@@ -573,8 +574,8 @@ static void enqueue_step(pf_ens* E) {
   }
   launch_kind<T, TE>(E, EK_STAGE, tb.s);
   const EMemb<T, TE>* mem = (const EMemb<T, TE>*)E->mem_dev;
-  kb_control<T, TE><<<E->M, 256, 0, E->stream>>>(mem, E->st_dev, E->start[EK_STAGE][E->var[EK_STAGE]], E->partial,
-                                                  tb.emb_order, tb.has_emb, tb.s, E->unit, E->tab_dev);
+  kb_control<T, TE><<<E->M, 256, 0, E->stream>>>(mem, E->st_dev, E->pairs(), E->partial, tb.emb_order, tb.has_emb,
+                                                  tb.s, E->unit, E->tab_dev);
 }
 
 // Members' states and coefficients (for the dt of their next attempt) to the device.

@@ -433,7 +433,7 @@ __device__ inline void body_stage(const StepArgs<TE>& sa, TabP tb, const Geo& g,
     if (q.f > 0) fresh_explicit<T, TE, N, TX, RE, GUARD, LB>(gk, q, g, m, twz, buf);
   }
   const double kx = q.x * g.kfx, ky = mode_of(q.y, g.ny) * g.kfy;
-    const long long fo = q.f * g.fs;
+  const long long fo = q.f * g.fs;
   StageRow<TE, NP, fresh_fe<T>> nxt;
   if (q.valid) nxt.load(sa, g, q.f, q.base + (uint32_t)q.bf * q.lstride);
 #pragma unroll 1
@@ -1259,7 +1259,7 @@ __device__ inline void body_final(const StepArgs<TE>& sa, TabP tb, const Geo& g,
   acc = bad = 0.0;
   if (!q.valid) return;
   const double kx = q.x * g.kfx, ky = mode_of(q.y, g.ny) * g.kfy;
-    const double mult = (q.x == 0 || 2 * q.x == g.nx) ? 1.0 : 2.0;
+  const double mult = (q.x == 0 || 2 * q.x == g.nx) ? 1.0 : 2.0;
   const long long fo = q.f * g.fs;
   StageRow<TE, NF, fresh_fe<T>> nxt;
   nxt.load(sa, g, q.f, q.base + (uint32_t)q.bf * q.lstride);
@@ -1316,28 +1316,61 @@ __device__ inline void body_final(const StepArgs<TE>& sa, TabP tb, const Geo& g,
   }
 }
 
-// Threads of an update block: its columns' threads, filled up to whole
-// wavefronts for the block sums.
-template <int N, int TX, int RE>
-constexpr int final_threads() {
-  return (ColGeo<N, TX, RE>::THREADS + 63) / 64 * 64;
+// The tile's sums of (acc, bad): one partial pair per G columns, where G is the
+// narrowest tile of the pass.  A group's values are added in the order that a
+// tile of G columns has its threads in, so the sums, and with them the step
+// sizes of an adaptive run, do not depend on the tile width that a tuner picks.
+// W lanes at a time (a wavefront, or what the narrowest tile has of one; a
+// block's last threads past a multiple of W take no part).  lds: 16 bytes per
+// thread of the tile; NT: threads of the block.
+template <int N, int TX, int RE, int G, int NT>
+__device__ inline void tile_sums(double acc, double bad, const Geo& g, int item, int tid, double* lds,
+                                 double* partial) {
+  using CG = ColGeo<N, TX, RE>;
+  static_assert(TX % G == 0 && NT >= CG::THREADS, "whole groups");
+  constexpr int K = TX / G, GT = G * CG::TL;  // groups, values of a group
+  constexpr int W = GT >= 64 ? 64 : GT >= 32 ? 32 : GT >= 16 ? 16 : 8;
+  static_assert(GT >= W, "lanes");
+  const int nbx = (g.nxh + TX - 1) / TX, nbg = (g.nxh + G - 1) / G;
+  const int col = tid % TX, bf = tid / TX;
+  __syncthreads();
+  if (tid < CG::THREADS) {
+    const int i = (col / G) * GT + bf * G + col % G;
+    lds[i] = acc;
+    lds[CG::THREADS + i] = bad;
+  }
+  __syncthreads();
+  const int lane = tid % W;
+  for (int h = tid / W; tid < NT / W * W && h < K; h += NT / W) {
+    double a = 0.0, b = 0.0;
+    for (int i = lane; i < GT; i += W) {
+      a += lds[h * GT + i];
+      b += lds[CG::THREADS + h * GT + i];
+    }
+#pragma unroll
+    for (int o = W / 2; o > 0; o >>= 1) {
+      a += __shfl_xor(a, o, 64);
+      b += __shfl_xor(b, o, 64);
+    }
+    const int grp = (item % nbx) * K + h;  // group of columns; item / nbx: field and y
+    if (lane == 0 && grp < nbg) {
+      double* p = partial + 2 * ((long long)(item / nbx) * nbg + grp);
+      p[0] = a;
+      p[1] = b;
+    }
+  }
 }
 
-template <typename T, typename TE, int N, int TX, int RE, int S>
-__global__ void __launch_bounds__((final_threads<N, TX, RE>()))
+template <typename T, typename TE, int N, int TX, int RE, int S, int G>
+__global__ void __launch_bounds__((ColGeo<N, TX, RE>::THREADS))
 k_finalize(StepArgs<TE> sa, ArkTab tb, Geo g, ModelK m, const cx<T>* gk, const cx<T>* twz, double* partial) {
-  __shared__ cx<T> lds[N * ColGeo<N, TX, RE>::LD];
-  __shared__ double sh[16];
+  using CG = ColGeo<N, TX, RE>;
+  __shared__ cx<T> lds[N * CG::LD];
+  static_assert(sizeof(lds) >= 16 * CG::THREADS, "the sums");
   double acc, bad;
-  constexpr bool fill = final_threads<N, TX, RE>() != ColGeo<N, TX, RE>::THREADS;
-  body_final<T, TE, N, TX, RE, S, fill>(sa, &tb, g, m, gk, twz, xcd_tile(blockIdx.x, gridDim.x), threadIdx.x, lds,
-                                        acc, bad);
-  acc = block_sum(acc, sh);
-  bad = block_sum(bad, sh);
-  if (threadIdx.x == 0) {
-    partial[2 * blockIdx.x] = acc;
-    partial[2 * blockIdx.x + 1] = bad;
-  }
+  const int item = xcd_tile(blockIdx.x, gridDim.x);
+  body_final<T, TE, N, TX, RE, S>(sa, &tb, g, m, gk, twz, item, threadIdx.x, lds, acc, bad);
+  tile_sums<N, TX, RE, G, CG::THREADS>(acc, bad, g, item, threadIdx.x, reinterpret_cast<double*>(lds), partial);
 }
 
 // Non-template kernels get internal linkage: this header is included by more

@@ -585,12 +585,11 @@ static pf_status stages_and_finalize(pf_ctx* c, double dt, int* n_rhs) {
   const double nv = (double)c->g.nz * c->g.ny * c->g.nxh;
   const double fT = nv * sizeof(cx<T>), fE = nv * sizeof(cx<TE>), f64 = nv * sizeof(cx<double>);
   prof_begin(c);
-  const int nb = launch_final<T, TE>(c, sa, T3);
-  if (nb == 0) return PF_ERR_UNSUPPORTED_SIZE;
+  int np = launch_final<T, TE>(c, sa, T3);
+  if (np == 0) return PF_ERR_UNSUPPORTED_SIZE;
   const double* part = c->partial;
-  int np = nb;
-  if (nb > kReduceOne) {
-    double* second = c->partial + 2 * (size_t)final_blocks_max(c->g);
+  if (np > kReduceOne) {
+    double* second = c->partial + 2 * (size_t)final_pairs_max(c->g);
     k_reduce_pairs<<<dim3(kReduceBlocks), dim3(256), 0, c->stream>>>(part, np, second);
     part = second;
     np = kReduceBlocks;
@@ -888,7 +887,7 @@ pf_status pf_init(const pf_params* p, void* stream, pf_ctx** out) {
     if (c->fe_need[i] || i == 0) s = dalloc(c, &c->FE[i], fe_bytes);
   if (s == PF_OK) s = dalloc(c, &c->scratch, c->scratch_bytes);
   if (s == PF_OK) s = dalloc(c, (void**)&c->partial, sizeof(double) * (size_t)std::max(
-                                       4 * c->nblk_red, 2 * (final_blocks_max(g) + kReduceBlocks)));
+                                       4 * c->nblk_red, 2 * (final_pairs_max(g) + kReduceBlocks)));
   if (s == PF_OK) s = dalloc(c, (void**)&c->red, sizeof(double) * 8);
   if (s == PF_OK && hipHostMalloc((void**)&c->host_red, sizeof(double) * 8, 0) != hipSuccess) s = PF_ERR_OOM;
   if (s == PF_OK) s = upload_twiddles(c, 0, g.nz);

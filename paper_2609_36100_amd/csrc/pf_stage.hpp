@@ -15,13 +15,14 @@ template <typename T, typename TE>
 bool launch_stage(pf_ctx* c, const StepArgs<TE>& sa, int np, const cx<T>* gk, cx<T>* out);
 
 // Update, error estimate and WRMS partial sums (c->partial) of the step, whose
-// newest driving force is in gk.  Returns the number of partial pairs, 0 for
-// an unsupported size.
+// newest driving force is in gk.  Returns the number of partial pairs (the same
+// for every tile variant), 0 for an unsupported size.
 template <typename T, typename TE>
 int launch_final(pf_ctx* c, const StepArgs<TE>& sa, const cx<T>* gk);
 
-// Largest number of partial pairs launch_final writes on this grid.
-int final_blocks_max(const Geo& g);
+// Number of partial pairs launch_final writes on this grid, in the precision
+// that has more.
+int final_pairs_max(const Geo& g);
 
 #ifdef PF_STAGE_DEFINITIONS
 template <typename T, typename TE, int NP>
@@ -57,19 +58,20 @@ bool launch_stage(pf_ctx* c, const StepArgs<TE>& sa, int np, const cx<T>* gk, cx
 template <typename T, typename TE, int S>
 static int launch_final_s(pf_ctx* c, const StepArgs<TE>& sa, const cx<T>* gk) {
   const Geo& g = c->g;
-  int nb = 0;
+  int pairs = 0;
   col_dispatch(g.nz, [&](auto NC) {
     constexpr int N = decltype(NC)::value;
     with_variant(c->var[CK_STAGE], [&](auto VC) {
       constexpr int RE = col_re(CK_STAGE);
       constexpr int TX = col_tx(N, CK_STAGE, sizeof(cx<T>), decltype(VC)::value);
+      constexpr int G = col_tx(N, CK_STAGE, sizeof(cx<T>), 0);
       const int nbx = (g.nxh + TX - 1) / TX;
-      nb = 4 * nbx * g.ny;
-      k_finalize<T, TE, N, TX, RE, S><<<dim3(nb), dim3(final_threads<N, TX, RE>()), 0, c->stream>>>(
+      pairs = 4 * ((g.nxh + G - 1) / G) * g.ny;
+      k_finalize<T, TE, N, TX, RE, S, G><<<dim3(4 * nbx * g.ny), dim3(ColGeo<N, TX, RE>::THREADS), 0, c->stream>>>(
           sa, c->at, g, c->mk, gk, tw<T>(c, 0), c->partial);
     });
   });
-  return nb;
+  return pairs;
 }
 
 template <typename T, typename TE>
