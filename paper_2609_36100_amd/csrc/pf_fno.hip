@@ -184,7 +184,7 @@ template <int NT>
 __global__ void __launch_bounds__(256)
 k_cm_gemm(const u16* __restrict__ In, int ldin, int K, const u16* __restrict__ Bt, int N,
           const float* __restrict__ bias, const float* __restrict__ resid, int ldres, float* __restrict__ outf,
-          u16* __restrict__ outpre, u16* __restrict__ outact, int ldout, int accumulate, LineTerm lt,
+          u16* __restrict__ outpre, u16* __restrict__ outact, int ldout, LineTerm lt,
           const u16* __restrict__ gpre, const float* __restrict__ gtab) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const long long p0 = ((long long)blockIdx.x * 4 + wave) * 32;
@@ -247,10 +247,8 @@ k_cm_gemm(const u16* __restrict__ In, int ldin, int K, const u16* __restrict__ B
           v[4 * q + j] = r;
         }
         if (outf) {
-          f32x4* o = reinterpret_cast<f32x4*>(outf + p * ldout + c);
-          f32x4 r = {v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-          if (accumulate) r = *o + r;
-          *o = r;
+          *reinterpret_cast<f32x4*>(outf + p * ldout + c) =
+              f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
         }
       } else {  // f32 results of a channel count that 4 does not divide
 #pragma unroll
@@ -258,8 +256,7 @@ k_cm_gemm(const u16* __restrict__ In, int ldin, int K, const u16* __restrict__ B
           if (c + j >= N) continue;
           float r = v[4 * q + j] + (bias ? bias[c + j] : 0.0f);
           if (resid) r += resid[p * ldres + c + j];
-          const long long o = p * ldout + c + j;
-          if (outf) outf[o] = accumulate ? outf[o] + r : r;
+          if (outf) outf[p * ldout + c + j] = r;
         }
       }
     }
@@ -605,7 +602,7 @@ k_lm_gemm(const u16* __restrict__ G, int R, int K, const u16* __restrict__ X, lo
           const long long o = b * obs + (long long)row * ldo + n;
           const float v = acc[t][i];
           if (outf) outf[o] = accumulate ? outf[o] + v : v;
-          if (outb) outb[o] = f2bf(accumulate ? bf2f(outb[o]) + v : v);
+          if (outb) outb[o] = f2bf(v);
         }
     }
   }
@@ -1362,10 +1359,10 @@ static pf_status upload_bf16(pf_fno* F, const std::vector<float>& h, u16** d) {
 
 // algorithmic bytes of one channel-mixing GEMM over `points` points
 static double cm_bytes(double points, int K, int N, const float* bias, const float* resid, const float* outf,
-                       const u16* outpre, const u16* outact, int accumulate) {
+                       const u16* outpre, const u16* outact) {
   double b = points * K * 2.0 + 2.0 * N * K + (bias ? 4.0 * N : 0.0);
   if (resid) b += points * N * 4.0;
-  if (outf) b += points * N * (accumulate ? 8.0 : 4.0);
+  if (outf) b += points * N * 4.0;
   if (outpre) b += points * N * 2.0;
   if (outact) b += points * N * 2.0;
   return b;
@@ -1411,7 +1408,7 @@ static void xline(pf_fno* F, XLineArgs a, long long samples) {
   a.gtab = F->gtab;
   const double points = (double)F->P * samples;
   if (a.Bt) {
-    double bytes = cm_bytes(points, a.K, a.N, a.bias, nullptr, nullptr, a.outpre, a.outact, 0);
+    double bytes = cm_bytes(points, a.K, a.N, a.bias, nullptr, nullptr, a.outpre, a.outact);
     double flops = 2.0 * points * a.K * a.N;
     if (a.G) {
       bytes += 2.0 * a.n * a.m2 + (double)a.lines * a.m2 * a.N * 2.0;
@@ -1432,9 +1429,9 @@ static void xline(pf_fno* F, XLineArgs a, long long samples) {
 
 static void cm_launch(pf_fno* F, long long points, const u16* In, int ldin, int K, const u16* Bt, int N,
                       const float* bias, const float* resid, int ldres, float* outf, u16* outpre, u16* outact,
-                      int ldout, int accumulate, const LineTerm& lt, const u16* gpre = nullptr) {
+                      int ldout, const LineTerm& lt, const u16* gpre = nullptr) {
   const unsigned grid = (unsigned)(points / 128);
-  double bytes = cm_bytes((double)points, K, N, bias, resid, outf, outpre, outact, accumulate);
+  double bytes = cm_bytes((double)points, K, N, bias, resid, outf, outpre, outact);
   double flops = 2.0 * points * K * N;
   if (lt.G) {
     bytes += 2.0 * lt.R * lt.K + (double)(points / lt.R) * lt.K * N * 2.0;
@@ -1444,7 +1441,7 @@ static void cm_launch(pf_fno* F, long long points, const u16* In, int ldin, int 
   account(F, FK_CM, bytes, flops);
   auto go = [&](auto NC) {
     k_cm_gemm<decltype(NC)::value><<<grid, 256, 0, F->stream>>>(In, ldin, K, Bt, N, bias, resid, ldres, outf, outpre,
-                                                                outact, ldout, accumulate, lt, gpre, F->gtab);
+                                                                outact, ldout, lt, gpre, F->gtab);
   };
   if (N <= 32)
     go(std::integral_constant<int, 1>{});
@@ -1455,9 +1452,9 @@ static void cm_launch(pf_fno* F, long long points, const u16* In, int ldin, int 
 }
 
 static void cm(pf_fno* F, const u16* In, int ldin, int K, const u16* Bt, int N, const float* bias, const float* resid,
-               int ldres, float* outf, u16* outpre, u16* outact, int ldout, int accumulate,
+               int ldres, float* outf, u16* outpre, u16* outact, int ldout,
                const LineTerm& lt = LineTerm(), const u16* gpre = nullptr) {
-  cm_launch(F, F->P, In, ldin, K, Bt, N, bias, resid, ldres, outf, outpre, outact, ldout, accumulate, lt, gpre);
+  cm_launch(F, F->P, In, ldin, K, Bt, N, bias, resid, ldres, outf, outpre, outact, ldout, lt, gpre);
 }
 
 static void sum_partials(pf_fno* F, const float* part, int nb, int K, int N, float* gW, float* gb) {
@@ -1643,7 +1640,7 @@ static void forward_layers(pf_fno* F, const FwdBufs& u, int B, V v, Pre pre, Sp 
     xline(F, a, B);
   } else {
     cm_launch(F, points, u.xin, F->cinp, F->cinp, F->bWliftT, w, th + F->o_bl, nullptr, 0, nullptr, v(0), nullptr, w,
-              0, LineTerm());
+              LineTerm());
   }
   for (int l = 0; l < c.layers; ++l) {
     const bool last = l == c.layers - 1;  // linear
@@ -1667,11 +1664,11 @@ static void forward_layers(pf_fno* F, const FwdBufs& u, int B, V v, Pre pre, Sp 
       xline(F, a, B);
     } else if (F->fuse_x) {
       cm_launch(F, points, v(l), w, w, F->bWT[l], w, th + F->o_b[l], nullptr, 0, nullptr, pre(l),
-                last ? nullptr : v(l + 1), w, 0, x_inverse(F, u.B2));
+                last ? nullptr : v(l + 1), w, x_inverse(F, u.B2));
     } else {
       lm(F, F->Gxi, n, 2 * m, u.B2, (long long)2 * m * w, w, w, B * n * n, u.B1, nullptr, (long long)n * w, w, 0);
       cm_launch(F, points, v(l), w, w, F->bWT[l], w, th + F->o_b[l], u.B1, w, nullptr, pre(l),
-                last ? nullptr : v(l + 1), w, 0, LineTerm());
+                last ? nullptr : v(l + 1), w, LineTerm());
     }
   }
 }
@@ -1691,8 +1688,8 @@ static void project_gemms(pf_fno* F) {
   const pf_fno_config& c = F->cfg;
   const int w = c.width, h = c.hidden;
   const float* th = F->th;
-  cm(F, F->pre[c.layers - 1], w, w, F->bP1T, h, th + F->o_c1, nullptr, 0, nullptr, F->hpre, F->hact, h, 0);
-  cm(F, F->hact, h, h, F->bP2T, c.cout, th + F->o_c2, nullptr, 0, F->outf, nullptr, nullptr, c.cout, 0);
+  cm(F, F->pre[c.layers - 1], w, w, F->bP1T, h, th + F->o_c1, nullptr, 0, nullptr, F->hpre, F->hact, h);
+  cm(F, F->hact, h, h, F->bP2T, c.cout, th + F->o_c2, nullptr, 0, F->outf, nullptr, nullptr, c.cout);
 }
 
 // forward pass for the packed input F->xin; leaves the result in F->outf
@@ -1724,10 +1721,10 @@ static void loss_backward(pf_fno* F, const float* x, const float* y) {
     // out = hact P2 + c2
     wgrad(F, F->hact, h, h, F->douthb, F->coutp, co, g + F->o_P2, g + F->o_c2);
     // d hpre = (d out P2^T) GELU'(hpre), formed in the GEMM's epilogue
-    cm(F, F->douthb, F->coutp, F->coutp, F->bP2, h, nullptr, nullptr, 0, nullptr, F->dhb, nullptr, h, 0, LineTerm(),
+    cm(F, F->douthb, F->coutp, F->coutp, F->bP2, h, nullptr, nullptr, 0, nullptr, F->dhb, nullptr, h, LineTerm(),
        F->hpre);
     wgrad(F, F->pre[c.layers - 1], w, w, F->dhb, h, h, g + F->o_P1, g + F->o_c1);
-    cm(F, F->dhb, h, h, F->bP1, w, nullptr, nullptr, 0, nullptr, db[0], nullptr, w, 0);
+    cm(F, F->dhb, h, h, F->bP1, w, nullptr, nullptr, 0, nullptr, db[0], nullptr, w);
   }
   const int Nz = m2 * m * w;
   // the spectral path's transposed stages from the x stage's output (B2) down to A1
@@ -1787,10 +1784,10 @@ static void loss_backward(pf_fno* F, const float* x, const float* y) {
       lt.X = F->A1;
       lt.xbs = (long long)2 * m * w;
       lt.ldx = w;
-      cm(F, db[0], w, w, F->bW[l], w, nullptr, nullptr, 0, nullptr, db[1], nullptr, w, 0, lt, gp);
+      cm(F, db[0], w, w, F->bW[l], w, nullptr, nullptr, 0, nullptr, db[1], nullptr, w, lt, gp);
       std::swap(db[0], db[1]);
     } else {
-      cm(F, db[0], w, w, F->bW[l], w, nullptr, nullptr, 0, F->dvf, nullptr, nullptr, w, 0);
+      cm(F, db[0], w, w, F->bW[l], w, nullptr, nullptr, 0, F->dvf, nullptr, nullptr, w);
       lm(F, F->GxfT, n, 2 * m, F->A1, (long long)2 * m * w, w, w, n * n, F->dvf, nullptr, (long long)n * w, w, 1);
       account(F, FK_GELU, (double)P * w * (4.0 + 2.0 + 2.0), 20.0 * P * w);
       k_gelu_bwd<<<gdiv(P * w, 256), 256, 0, F->stream>>>(F->dvf, gp, F->gtab, db[0], P * w, l > 0 ? 0 : 1);
@@ -2193,7 +2190,7 @@ static pf_status ensure_batch(pf_fno* F, int B) {
 static void cm_points(pf_fno* F, long long points, const u16* In, int ldin, int K, const u16* Bt, int N,
                       const float* bias, const float* resid, int ldres, float* outf, u16* outpre, u16* outact,
                       int ldout, const LineTerm& lt = LineTerm()) {
-  cm_launch(F, points, In, ldin, K, Bt, N, bias, resid, ldres, outf, outpre, outact, ldout, 0, lt);
+  cm_launch(F, points, In, ldin, K, Bt, N, bias, resid, ldres, outf, outpre, outact, ldout, lt);
 }
 
 // The forward pass of B samples at once (inputs packed in bxin, outputs in
