@@ -396,7 +396,8 @@ pf_status pf_fno_set_input_norm(pf_fno* f, const float* host_shift, const float*
  * [n^3][cout], point-major) */
 pf_status pf_fno_forward(pf_fno* f, const float* x, float* out);
 /* forward + mean-squared loss against the target (y - x) / scale (x, y device
- * float32 [cin][n^3]) + backward; gradients are ADDED to the gradient buffer */
+ * float32 [cin][n^3]; with cout > cin the target reads channels up to cout of
+ * both) + backward; gradients are ADDED to the gradient buffer */
 pf_status pf_fno_grad(pf_fno* f, const float* x, const float* y, double* loss);
 pf_status pf_fno_get_grad(pf_fno* f, float* host_grad);
 pf_status pf_fno_zero_grad(pf_fno* f);

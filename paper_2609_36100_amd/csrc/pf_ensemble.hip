@@ -942,8 +942,9 @@ pf_status pf_ensemble_advance(pf_ens* E, const double* t_final, int32_t max_step
 
 pf_status pf_ensemble_autotune(pf_ens* E, int32_t reps) {
   if (!E || reps < 1) return PF_ERR_ARG;
-  // time each kind on all members (state untouched: the stage arrays and
-  // temporaries are overwritten, the state buffers only read)
+  // time each kind on all members (the states are only read; the stage arrays,
+  // the temporaries and, by the timed update, each member's spare state buffer
+  // are overwritten)
   for (int m = 0; m < E->M; ++m) E->st_host[m].done = 0;
   pf_status up = upload_states(E);
   if (up != PF_OK) return up;

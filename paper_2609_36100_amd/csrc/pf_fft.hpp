@@ -7,7 +7,7 @@
 // this header holds the per-line pieces every pass shares:
 //
 //  * cx<T>          interleaved complex value (T = float or double);
-//  * dft<R,S>()     in-register R-point DFT, R in {2,3,4,5,8}, S = -1 forward
+//  * dft<R,S>()     in-register R-point DFT, R in {2,..,8}, S = -1 forward
 //                   (exp(-i...)), S = +1 inverse (unnormalised);
 //  * Plan / plan()  compile-time radix sequence for a line of length n whose
 //                   first and last radix are equal, so that a thread owns the

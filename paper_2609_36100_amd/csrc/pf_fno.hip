@@ -10,14 +10,17 @@
 // frequencies.  Activations are channel-last [point][channel] BF16.
 //
 // Dense contractions run on MFMA (gfx950 v_mfma_f32_32x32x16_bf16, FP32 accumulate):
-//  * channel mixing (lift, W_l, P1, P2 and their data gradients) as
-//    [points x K] x [K x N] GEMMs;
-//  * every truncated-DFT stage as a small constant matrix G times batched
-//    activation blocks, Out_b = G X_b, with layouts chosen so each stage is a
-//    plain strided GEMM (and its backward the same kernel with G^T).
-// The per-mode complex w x w mixing and the weight-gradient reductions over
-// points run on FP32 vector ALUs.  Adam updates FP32 master weights and
-// refreshes the BF16 working copies.
+//  * a layer along whole x lines (width <= 64, at most 16 modes): channel
+//    mixing, the inverse x stage, the activation and the next layer's x stage
+//    in one pass (k_xline); else channel mixing as [points x K] x [K x N] GEMMs
+//    (k_cm_gemm) and the x stages as GEMMs of their own (k_lm_gemm);
+//  * the y and z stages of the truncated DFT as a small constant matrix G times
+//    batched activation blocks, Out_b = G X_b (k_lm_rows; backward: G^T);
+//  * the projection with the loss and its backward pass in one kernel (width
+//    <= 32, k_proj), else as GEMMs through the hidden layer;
+//  * the weight gradients, reductions over points (k_wgrad_mfma).
+// The per-mode complex w x w mixing and its gradients run on FP32 vector ALUs.
+// Adam updates FP32 master weights and refreshes the BF16 working copies.
 #include <hip/hip_runtime.h>
 
 #include <chrono>
