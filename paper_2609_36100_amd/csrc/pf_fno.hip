@@ -287,8 +287,9 @@ k_cm_gemm(const u16* __restrict__ In, int ldin, int K, const u16* __restrict__ B
 // (y - x) / scale, the data gradient d v_L (dpre) and the gradients of P1, c1, P2
 // and c2 (one partial set per block: part1 rows k = 0 .. w, part2 rows
 // 0 .. h, the last row the bias's): with the hidden layer's activations and
-// gradients in HBM that took 4.6 GB and 3.9 ms per sample.  What bounds it
-// now is the exact GELU's erf: 2.7e8 of them per sample at 128^3.
+// gradients in HBM that took 4.6 GB and 3.9 ms per sample.  Now 0.17 ms per
+// sample, bound by the exact GELUs (the vector units issue in 62 % of the
+// cycles), and 0.58 with TRAIN, by its registers (two waves per SIMD, 35 %).
 // A wave takes 32 points at a time; points are the B operand throughout, so
 // every product's accumulator holds one point per lane, and the next product
 // takes it as an operand (to_operand).  The weight gradients contract over
